@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/moe355.h"
 
@@ -243,12 +244,48 @@ inline void set_control(GemmArgs& a, char* ws, const WsLayout& L)
 void launch_segment_sums(const moe_desc_t& D, const WsLayout& L, const void* src, int width, const int32_t* counts,
                          const int32_t* offsets, float* out, char* ws, hipStream_t st);
 void launch_ggemm_f32(const GemmArgs& a, hipStream_t st);
+void launch_ggemm_pair_f32(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st);   // as launch_ggemm_pair_bf16_sk
 void launch_ggemm_bf16_sk(const GemmArgs& a, hipStream_t st);
 // A rows kind (dZ or dXs) and a weight-gradient product that does not depend on it, in one launch.
 void launch_ggemm_pair_bf16_sk(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st);
 bool ggemm_pair_pays(const GemmArgs& rows);   // whether the pair launch is expected to beat two launches
 
 // ---- small device helpers ------------------------------------------------------------------
+// The expert whose tiles hold tile number t, from a prefix table P [E+1]: the largest e with P[e] <= t (t < P[E]), with
+// what a tile needs of it.  All lanes of a wavefront call it with the same t.  The lanes look at 64 experts at a time and
+// count those that begin at or before t: two dependent round trips to memory instead of the log2(E) + 1 of a binary
+// search, one of them for up to 64 experts.
+struct Segment { int e, first, next, count, offset; };   // first, next: P[e], P[e+1]
+__device__ __forceinline__ Segment find_segment(const int32_t* __restrict__ P, int E, int t, const int32_t* __restrict__ counts,
+                                                const int32_t* __restrict__ offsets)
+{
+    const int lane = __lane_id();
+    Segment s;
+    if (E <= 64) {
+        const int i = min(lane, E - 1);
+        const int p = P[i], pn = P[i + 1], c = counts[i], o = offsets[i];
+        s.e = __popcll(__ballot(lane < E && p <= t)) - 1;
+        s.first = __builtin_amdgcn_readlane(p, s.e);
+        s.next = __builtin_amdgcn_readlane(pn, s.e);
+        s.count = __builtin_amdgcn_readlane(c, s.e);
+        s.offset = __builtin_amdgcn_readlane(o, s.e);
+        return s;
+    }
+    int below = 0;
+    for (int e0 = 0; e0 < E; e0 += 256) {
+        int p[4];                      // four loads in flight
+#pragma unroll
+        for (int u = 0; u < 4; ++u) p[u] = P[min(e0 + u * 64 + lane, E - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) below += __popcll(__ballot(e0 + u * 64 + lane < E && p[u] <= t));
+    }
+    s.e = below - 1;
+    s.first = P[s.e];
+    s.next = P[s.e + 1];
+    s.count = counts[s.e];
+    s.offset = offsets[s.e];
+    return s;
+}
 __device__ __forceinline__ float bf16_to_f32(unsigned short v) { return __uint_as_float(((unsigned)v) << 16); }
 __device__ __forceinline__ unsigned short f32_to_bf16(float f)
 {

@@ -397,9 +397,15 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
     dw1.A = ws + L.Xs; dw1.B = ws + L.dZ; dw1.C = dW1; dw1.K = D.d; dw1.Nout = D.h;
     // dZ and dW2 need only dYs, and dXs and dW1 only dZ: where it pays, each pair is one launch in which a workgroup
     // that has finished its share of the first product goes on with tiles of the second.
-    const bool can_pair = D.dtype == MOE_BF16 && D.N > 0;
-    if (can_pair && ggemm_pair_pays(dh)) {
-        { ScopedTimer tm(S_DH_DW2, st); launch_ggemm_pair_bf16_sk(dh, dw2, st); }
+    // (fp32: always - a workgroup there has one tile of either product, so the pair costs nothing and saves a launch)
+    const bool f32 = D.dtype == MOE_F32;
+    auto pays = [&](const GemmArgs& rows) { return D.N > 0 && (f32 || ggemm_pair_pays(rows)); };
+    auto run_pair = [&](const GemmArgs& rows, const GemmArgs& cols) {
+        if (f32) launch_ggemm_pair_f32(rows, cols, st);
+        else launch_ggemm_pair_bf16_sk(rows, cols, st);
+    };
+    if (pays(dh)) {
+        { ScopedTimer tm(S_DH_DW2, st); run_pair(dh, dw2); }
         if ((s = check_launch("expert layer 2 gradients")) != MOE_OK) return s;
     } else {
         if (D.N > 0) {
@@ -410,8 +416,8 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
         { ScopedTimer tm(S_DW2, st); run_gemm(D, dw2, st); }
         if ((s = check_launch("expert layer 2 weight gradient")) != MOE_OK) return s;
     }
-    if (can_pair && ggemm_pair_pays(dxs)) {
-        { ScopedTimer tm(S_DXS_DW1, st); launch_ggemm_pair_bf16_sk(dxs, dw1, st); }
+    if (pays(dxs)) {
+        { ScopedTimer tm(S_DXS_DW1, st); run_pair(dxs, dw1); }
         if ((s = check_launch("expert layer 1 gradients")) != MOE_OK) return s;
     } else {
         if (D.N > 0) {
