@@ -14,6 +14,8 @@ namespace moe {
 constexpr int kMaxE = 1024;
 constexpr int kMaxK = 8;
 constexpr int kPlanChunk = 1024;  // assignments ranked by one workgroup of the plan kernels
+constexpr int kBalanceChunk = 256;  // tokens whose gate probabilities one workgroup of the load-balance monitor sums
+inline int gate_r_stride(int E) { return (E + 3) / 4 * 4; }   // floats per row of gate_R: 16-byte pieces, the last padded with zeros
 constexpr int kNumTileHeights = 4;  // row-tile prefix tables are kept for 32, 64, 128, 256 rows
 constexpr int kMaxPersistentWgs = 256;               // persistent grouped-GEMM workgroups (one per compute unit)
 constexpr size_t kPartialBytesPerWg = 256 * 256 * 4;  // one fp32 output tile of partial sums per workgroup
@@ -42,16 +44,13 @@ struct WsLayout {
     size_t dbg_part;  // [pieces] float
     size_t bias_part; // [pieces][max(d,h)] float: partial column sums for the expert-bias gradients
     // only with desc.score_all or desc.balance_stats:
-    size_t logits;    // [N][E] double: the gate logits
-    size_t lse;       // [N] double: log of the sum of exp of a token's logits
-    size_t prob_part; // [ceil(N/512)][E] double: sums of the gate probabilities by chunk of 512 tokens
+    size_t logits;    // [N][E] double: the gate logits, then (same place) the gate probabilities
+    size_t prob_part; // [ceil(N/kBalanceChunk)][E] double: sums of the gate probabilities by chunk of tokens
     // only with desc.score_all (scores = softmax over all experts):
-    size_t gate_S;    // [N] float: sum_j w_j dL/dw_j of a token
-    size_t gate_R;    // [N][E] float: dL/dlogit of the experts that were not selected (0 at the selected ones)
-    size_t dx_dense;  // [N][d] float: their contribution to dX
-    size_t dense_part;   // [ceil(N/512)][E][d] float: their contribution to dWg, by chunk of 512 tokens
-    size_t dense_bpart;  // [ceil(N/512)][E] float: and to dbg
-    int dense_chunks;
+    size_t gate_R;    // [N][gate_r_stride(E)] float: dL/dlogit of every expert
+    size_t dense_part;   // [dense_chunks][E][d] float: sums of dWg by chunk of dense_chunk tokens
+    size_t dense_bpart;  // [dense_chunks][E] float: and of dbg
+    int dense_chunk, dense_chunks;
     size_t gate_fail; // [1 + N] int32: how many tokens the fast gate kernel could not certify, then their ids
     size_t WgT;       // [E][d] gate matrix transposed (written by the plan step for E > 32 and by the backward pass), element type = desc.dtype
     size_t zeros;     // the control block (see Ctl below): 1 KB of zeros, source of masked reduction rows, then the control words
@@ -109,16 +108,17 @@ inline WsLayout ws_layout(const moe_desc_t& D)
     L.bias_part = take((size_t)L.dwg_pieces * (D.d > D.h ? D.d : D.h) * sizeof(float));
     L.gate_fail = take(((size_t)D.N + 1) * sizeof(int32_t));
     L.WgT = take((size_t)D.E * D.d * b);
-    L.dense_chunks = (D.N + 511) / 512;
+    // chunks of the dense weight gradient: as long as it takes to give two compute-unit loads of 64 x 64 tiles, 64 to 512 tokens
+    L.dense_chunk = 512;
+    while (L.dense_chunk > 64 && (size_t)((D.N + L.dense_chunk - 1) / L.dense_chunk) * ((D.d + 63) / 64) * ((D.E + 63) / 64) < 512)
+        L.dense_chunk /= 2;
+    L.dense_chunks = (D.N + L.dense_chunk - 1) / L.dense_chunk;
     if (D.score_all || D.balance_stats) {
         L.logits = take((size_t)D.N * D.E * sizeof(double));
-        L.lse = take((size_t)D.N * sizeof(double));
-        L.prob_part = take((size_t)(L.dense_chunks > 0 ? L.dense_chunks : 1) * D.E * sizeof(double));
+        L.prob_part = take((size_t)((D.N + kBalanceChunk - 1) / kBalanceChunk + 1) * D.E * sizeof(double));
     }
     if (D.score_all) {
-        L.gate_S = take((size_t)D.N * sizeof(float));
-        L.gate_R = take((size_t)D.N * D.E * sizeof(float));
-        L.dx_dense = take((size_t)D.N * D.d * sizeof(float));
+        L.gate_R = take((size_t)D.N * gate_r_stride(D.E) * sizeof(float));
         L.dense_part = take((size_t)L.dense_chunks * D.E * D.d * sizeof(float));
         L.dense_bpart = take((size_t)L.dense_chunks * D.E * sizeof(float));
     }
@@ -159,29 +159,37 @@ template <typename Kern> static bool allow_dynamic_lds(Kern kern, int bytes)
 
 // ---- kernel launchers (each enqueues on `st`; operand shapes are validated by the callers) ----
 void launch_gate_topk(const moe_desc_t& D, const void* X, const void* Wg, const float* bg, int32_t* topk_idx,
-                      float* topk_w, void* WgT, double* logits, double* lse, int32_t* gate_fail, hipStream_t st);
+                      float* topk_w, void* WgT, double* logits, int32_t* gate_fail, hipStream_t st);
 // bf16 with 17 to 256 experts and no caller of the stored logits: fp32 logits on the bf16 matrix cores with a certified
 // margin, fp64 for the k selected logits and for the tokens that cannot be certified (gate_fail: [1 + N] int32 scratch)
 void launch_gate_bf16(const moe_desc_t& D, const void* X, const void* Wg, const float* bg, int32_t* topk_idx, float* topk_w,
                       void* WgT, int32_t* gate_fail, hipStream_t st);
-// (WgT: [E][d] scratch for the transposed gate matrix; logits [N][E] and lse [N]: only with desc.score_all, else NULL)
+// (WgT: [E][d] scratch for the transposed gate matrix; logits [N][E]: only with desc.score_all or desc.balance_stats, else NULL; holds the
+// gate probabilities afterwards)
 void launch_plan(const moe_desc_t& D, const WsLayout& L, const int32_t* topk_idx, int32_t* counts,
                  int32_t* offsets, int32_t* pos, int32_t* perm, char* ws, hipStream_t st);
 
 void launch_scatter(const moe_desc_t& D, const void* X, const int32_t* perm, void* Xs, hipStream_t st);
 void launch_combine(const moe_desc_t& D, const void* Ys, const float* topk_w, const int32_t* pos, void* Y,
                     hipStream_t st);
+// With scores over all experts the combine backward also writes the gradient of every logit (R NULL: it does not).
+struct GateDense {
+    const double* p;           // [N][E] gate probabilities
+    const int32_t* topk_idx;   // [N][k]
+    float* R;                  // [N][stride]
+    int E, stride;
+};
 void launch_dcombine(const moe_desc_t& D, const void* dY, const void* Ys, const float* topk_w,
-                     const int32_t* pos, void* dYs, float* dl, float* S_out, const void* X, void* Xs, hipStream_t st);
+                     const int32_t* pos, void* dYs, float* dl, const GateDense& gate, const void* X, void* Xs, hipStream_t st);
 // (X, Xs: the scatter Xs[pos[a],:] = X[t,:] rides along, or NULL, NULL)
 void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
                      const float* dl, const int32_t* topk_idx, const int32_t* pos, const int32_t* perm,
-                     const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws,
-                     const void* X_dense, hipStream_t st);
+                     const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws, hipStream_t st);
 void launch_balance_stats(const moe_desc_t& D, const WsLayout& L, const int32_t* counts, float* fraction, float* mean_prob,
                           float* loss, char* ws, hipStream_t st);
-void launch_gate_dense(const moe_desc_t& D, const WsLayout& L, const void* X, const void* Wg, const int32_t* topk_idx,
-                       char* ws, hipStream_t st);
+// launch_gate_bwd for scores over all experts: from the gradient of every logit (GateDense::R)
+void launch_gate_dense_bwd(const moe_desc_t& D, const WsLayout& L, const void* X, const void* Wg, const void* dXs, const int32_t* pos,
+                           void* dX, void* dWg, float* dbg, char* ws, hipStream_t st);
 
 // Grouped matrix products over the expert segments.
 //   kRows*: C[r,:] (r in segment e) = A[r,:] * op(B[e]);  A is [M,K] row-major, C is [M,Nout] row-major.

@@ -520,27 +520,38 @@ static void launch_mfma(const moe_desc_t& D, const T* X, const T* Wg, const floa
     else launch_wide_mt<T, 1>(D, X, WgT, bg, idx, w, logits, st);
 }
 
-// One wavefront per token sums exp(l - top) over the stored logits (lanes stride the experts, then a fixed
-// butterfly) and keeps log-sum-exp for the backward pass and the load-balance monitor; with scores taken from the
-// softmax over all E logits (rewrite) it also replaces the k scores.
-__global__ __launch_bounds__(256) void gate_scores_all(const double* __restrict__ logits, const int32_t* __restrict__ topk_idx,
-                                                       int N, int E, int k, float* __restrict__ topk_w,
-                                                       double* __restrict__ lse, int rewrite)
+// One wavefront per token turns the stored logits into the gate probabilities p = softmax(l), in place (lanes stride the
+// experts, the sum is a fixed butterfly): the backward pass and the load-balance monitor read them.  With scores taken
+// from the softmax over all E logits (rewrite) it also replaces the k scores.
+__global__ __launch_bounds__(256) void gate_scores_all(double* __restrict__ logits, const int32_t* __restrict__ topk_idx,
+                                                       int N, int E, int k, float* __restrict__ topk_w, int rewrite)
 {
     const int lane = threadIdx.x & 63;
     const long t = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= N) return;
-    const double* l = logits + (size_t)t * E;
+    double* l = logits + (size_t)t * E;
     const double top = l[topk_idx[t * k]];           // slot 0 holds the largest logit
-    double s = 0.0;
-    for (int e = lane; e < E; e += 64) s += exp(l[e] - top);
+    const double sel = l[topk_idx[t * k + min(lane, k - 1)]];
+    double ex[kMaxE / 64], s = 0.0;
+#pragma unroll
+    for (int c = 0; c < kMaxE / 64; ++c) {
+        const int e = c * 64 + lane;
+        if (c * 64 < E) {
+            ex[c] = e < E ? exp(l[e] - top) : 0.0;
+            s += ex[c];
+        }
+    }
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (rewrite && lane < k) topk_w[t * k + lane] = (float)(exp(l[topk_idx[t * k + lane]] - top) / s);
-    if (lane == 0) lse[t] = top + log(s);
+    if (rewrite && lane < k) topk_w[t * k + lane] = (float)(exp(sel - top) / s);
+#pragma unroll
+    for (int c = 0; c < kMaxE / 64; ++c) {
+        const int e = c * 64 + lane;
+        if (e < E) l[e] = ex[c] / s;
+    }
 }
 
 void launch_gate_topk(const moe_desc_t& D, const void* X, const void* Wg, const float* bg, int32_t* topk_idx,
-                      float* topk_w, void* WgT, double* logits, double* lse, int32_t* gate_fail, hipStream_t st)
+                      float* topk_w, void* WgT, double* logits, int32_t* gate_fail, hipStream_t st)
 {
     if (D.dtype == MOE_BF16 && D.E > 16 && D.E <= 256 && !logits) {
         launch_gate_bf16(D, X, Wg, bg, topk_idx, topk_w, WgT, gate_fail, st);
@@ -556,8 +567,8 @@ void launch_gate_topk(const moe_desc_t& D, const void* X, const void* Wg, const 
         else launch_mfma<T>(D, (const T*)X, (const T*)Wg, bg, topk_idx, topk_w, (T*)WgT, logits, st);
     }
     if (logits)
-        hipLaunchKernelGGL(gate_scores_all, dim3((unsigned)((D.N + 3) / 4)), dim3(256), 0, st, (const double*)logits,
-                           (const int32_t*)topk_idx, D.N, D.E, D.k, topk_w, lse, D.score_all);
+        hipLaunchKernelGGL(gate_scores_all, dim3((unsigned)((D.N + 3) / 4)), dim3(256), 0, st, logits,
+                           (const int32_t*)topk_idx, D.N, D.E, D.k, topk_w, D.score_all);
 }
 
 }  // namespace moe

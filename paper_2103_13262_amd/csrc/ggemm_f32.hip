@@ -18,23 +18,14 @@
 // sliced; N 2048, d 256, h 512, 8 experts (288 tiles): 31 against 29 us; above 512 tiles every compute unit has two
 // tiled workgroups to overlap and the sliced form only moves more data per product.
 //
-// LDS layouts of the tiled form: source rows with the reduction index fastest are kept as [row][36 floats], read 16 bytes
-// per lane (4 consecutive reduction indices: matrix step s of four takes element s of every lane); sources with the
-// reduction index slowest as [k][72 floats], read 4 bytes per lane.  Both pitches spread a wavefront's read evenly over
-// the banks.
+// The tiled form's staging and LDS layouts: tile_f32.h.
 #include "common.h"
+#include "tile_f32.h"
 
 namespace moe {
 
 namespace {
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-constexpr int TM = 64, TN = 64, TK = 32;
-constexpr int kPitchK = TK + 4;    // floats per LDS row, reduction index fastest
-constexpr int kPitchR = TM + 8;    // floats per LDS row, reduction index slowest
-static_assert(TM == TN, "one pitch for both operands");
-
-template <bool TRANS> constexpr int operand_floats() { return TRANS ? TK * kPitchR : TM * kPitchK; }
+using namespace tile_f32;
 
 template <int KIND> struct Kind {
     static constexpr bool A_TRANS = KIND == kColsT;                                              // A is [k][row]
@@ -104,60 +95,6 @@ __device__ __forceinline__ void store_element(const GemmArgs& g, const Tile& t, 
     } else C[o] = x;
 }
 
-// One operand's share of a thread (tid: number inside its group of 256): two 16-byte pieces per block.
-template <bool TRANS> struct Stream {
-    const float* p[2];
-    int k_of[2];                     // TRANS: reduction index of the piece inside a block
-    long step;                       // floats from one block to the next
-    // valid: rows (columns) of the tile that exist; others repeat an existing one and are never stored
-    __device__ __forceinline__ void init(const float* base, long ld, int valid, int tid, const int32_t* gather, long row0, int div)
-    {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            if constexpr (!TRANS) {
-                const int row = min((tid >> 3) + 32 * i, valid - 1);
-                const long src = gather ? (long)(gather[row0 + row] / div) : (long)row;
-                p[i] = base + src * ld + (tid & 7) * 4;
-                k_of[i] = 0;
-            } else {
-                const int k = (tid >> 4) + 16 * i, c = (tid & 15) * 4;
-                p[i] = base + (long)k * ld + (c < valid ? c : 0);
-                k_of[i] = k;
-            }
-        }
-        step = TRANS ? (long)TK * ld : TK;
-    }
-    // block b; k_left: reduction indices from the block's first on that exist (<= 0: the block does not)
-    __device__ __forceinline__ void fetch(float4 (&r)[2], long b, int k_left) const
-    {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            r[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (k_of[i] < k_left) r[i] = *(const float4*)(p[i] + b * step);
-        }
-    }
-    __device__ __forceinline__ static void stash(float* lds, const float4 (&r)[2], int tid)
-    {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            if constexpr (!TRANS) *(float4*)(lds + ((tid >> 3) + 32 * i) * kPitchK + (tid & 7) * 4) = r[i];
-            else *(float4*)(lds + ((tid >> 4) + 16 * i) * kPitchR + (tid & 15) * 4) = r[i];
-        }
-    }
-    // reduction indices 8 kk + 4 (lane / 32) .. + 3 of row / column rb + lane % 32
-    __device__ __forceinline__ static void operand(const float* lds, int rb, int kk, int lane, float (&v)[4])
-    {
-        if constexpr (!TRANS) {
-            const float4 q = *(const float4*)(lds + (rb + (lane & 31)) * kPitchK + kk * 8 + (lane >> 5) * 4);
-            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-        } else {
-            const float* q = lds + (kk * 8 + (lane >> 5) * 4) * kPitchR + rb + (lane & 31);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) v[s] = q[s * kPitchR];
-        }
-    }
-};
-
 template <int KIND>
 __device__ __forceinline__ void tiled_product(const GemmArgs& g, int tile, int ntn, int ntm, float* smem)
 {
@@ -167,8 +104,8 @@ __device__ __forceinline__ void tiled_product(const GemmArgs& g, int tile, int n
     const int wm = wave >> 1, wn = wave & 1;
     Tile t;
     if (!locate<KIND, TM>(g, tile, ntn, ntm, t)) return;
-    Stream<K::A_TRANS> sa;
-    Stream<K::B_TRANS> sb;
+    Stream<K::A_TRANS, float> sa;
+    Stream<K::B_TRANS, float> sb;
     sa.init(t.A, g.K, t.Mt, tid, KIND == kColsT ? nullptr : g.a_gather, t.r0, g.a_gather_div);
     sb.init(t.B, K::B_TRANS ? g.Nout : g.K, t.Nt, tid, nullptr, 0, 1);
     const int nblk = (t.Kt + TK - 1) / TK;
@@ -183,8 +120,8 @@ __device__ __forceinline__ void tiled_product(const GemmArgs& g, int tile, int n
     };
     auto stash = [&](auto par) {
         constexpr int p = decltype(par)::value;
-        Stream<K::A_TRANS>::stash(smem + p * K::BUF, ra[p], tid);
-        Stream<K::B_TRANS>::stash(smem + p * K::BUF + operand_floats<K::A_TRANS>(), rb[p], tid);
+        stash_block<K::A_TRANS>(smem + p * K::BUF, ra[p], tid);
+        stash_block<K::B_TRANS>(smem + p * K::BUF + operand_floats<K::A_TRANS>(), rb[p], tid);
     };
     auto multiply = [&](auto par) {
         const float* A = smem + decltype(par)::value * K::BUF;
@@ -192,8 +129,8 @@ __device__ __forceinline__ void tiled_product(const GemmArgs& g, int tile, int n
 #pragma unroll
         for (int kk = 0; kk < TK / 8; ++kk) {
             float a[4], b[4];
-            Stream<K::A_TRANS>::operand(A, wm * 32, kk, lane, a);
-            Stream<K::B_TRANS>::operand(B, wn * 32, kk, lane, b);
+            operand<K::A_TRANS>(A, wm * 32, kk, lane, a);
+            operand<K::B_TRANS>(B, wn * 32, kk, lane, b);
 #pragma unroll
             for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0);
         }

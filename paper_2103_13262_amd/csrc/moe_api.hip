@@ -272,7 +272,6 @@ moe_status_t moe_plan(const moe_desc_t* desc, const void* X, const void* Wg, con
         ScopedTimer tm(S_GATE, st);
         launch_gate_topk(D, X, Wg, bg, plan->topk_idx, plan->topk_w, (char*)workspace + L.WgT,
                          (D.score_all || D.balance_stats) ? (double*)((char*)workspace + L.logits) : nullptr,
-                         (D.score_all || D.balance_stats) ? (double*)((char*)workspace + L.lse) : nullptr,
                          (int32_t*)((char*)workspace + L.gate_fail), st);
         if ((s = check_launch("gate/top-k")) != MOE_OK) return s;
     }
@@ -368,8 +367,11 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
         // The same launch writes Xs for the first layer's weight gradient and the gate's (the forward pass read X
         // through perm instead).
         ScopedTimer tm(S_DCOMBINE, st);
+        GateDense gate{};
+        if (D.score_all)
+            gate = GateDense{(const double*)(ws + L.logits), plan->topk_idx, (float*)(ws + L.gate_R), D.E, gate_r_stride(D.E)};
         launch_dcombine(D, dY, direct_top1(D) ? nullptr : ws + L.Ys, plan->topk_w, plan->pos, ws + L.dYs, (float*)(ws + L.dl),
-                        D.score_all ? (float*)(ws + L.gate_S) : nullptr, X, ws + L.Xs, st);
+                        gate, X, ws + L.Xs, st);
         if ((s = check_launch("combine backward")) != MOE_OK) return s;
     }
 
@@ -430,8 +432,10 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
 
     {
         ScopedTimer tm(S_GATEBWD, st);
-        launch_gate_bwd(D, L, ws + L.Xs, ws + L.dXs, Wg, (const float*)(ws + L.dl), plan->topk_idx, plan->pos,
-                        plan->perm, plan->counts, plan->offsets, dX, dWg, dbg, ws, D.score_all ? X : nullptr, st);
+        if (D.score_all) launch_gate_dense_bwd(D, L, X, Wg, ws + L.dXs, plan->pos, dX, dWg, dbg, ws, st);
+        else
+            launch_gate_bwd(D, L, ws + L.Xs, ws + L.dXs, Wg, (const float*)(ws + L.dl), plan->topk_idx, plan->pos,
+                            plan->perm, plan->counts, plan->offsets, dX, dWg, dbg, ws, st);
     }
     return check_launch("gate backward");
 }
@@ -515,7 +519,7 @@ moe_status_t moe_gather_backward(const moe_desc_t* desc, const moe_plan_t* plan,
     if (!dl || (reinterpret_cast<uintptr_t>(dl) & 3u)) { set_error("dl is NULL or not 4-byte aligned"); return MOE_ERR_INVALID_ARG; }
     if (desc->score_all) { set_error("moe_gather_backward / moe_scatter_backward carry the gradient of the selected experts only (score_all must be 0)"); return MOE_ERR_UNSUPPORTED; }
     if (desc->N == 0) return MOE_OK;
-    launch_dcombine(*desc, dY, Ys, plan->topk_w, plan->pos, dYs, dl, nullptr, nullptr, nullptr, (hipStream_t)stream);
+    launch_dcombine(*desc, dY, Ys, plan->topk_w, plan->pos, dYs, dl, GateDense{}, nullptr, nullptr, (hipStream_t)stream);
     return check_launch("gather backward");
 }
 
@@ -540,7 +544,7 @@ moe_status_t moe_scatter_backward(const moe_desc_t* desc, const moe_plan_t* plan
     }
     if (desc->score_all) { set_error("moe_gather_backward / moe_scatter_backward carry the gradient of the selected experts only (score_all must be 0)"); return MOE_ERR_UNSUPPORTED; }
     launch_gate_bwd(*desc, L, Xs, dXs, Wg, dl, plan->topk_idx, plan->pos, plan->perm, plan->counts, plan->offsets, dX,
-                    dWg, dbg, (char*)workspace, nullptr, (hipStream_t)stream);
+                    dWg, dbg, (char*)workspace, (hipStream_t)stream);
     return check_launch("scatter backward");
 }
 

@@ -99,6 +99,6 @@ extern "C" moe_status_t moe_scatter_backward_static(const moe_desc_t* desc, cons
     int32_t* P64 = (int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
     hipLaunchKernelGGL(piece_prefix_64, dim3(1), dim3(1024), 0, st, (const int32_t*)plan->counts, D.E, P64);
     launch_gate_bwd(D, L, Xs, dXs, Wg, dl, plan->topk_idx, plan->pos, plan->perm, plan->counts, plan->offsets, dX, dWg, dbg,
-                    ws, nullptr, st);
+                    ws, st);
     return check_launch("scatter backward (static scratch)");
 }

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY
                                                      const float* __restrict__ topk_w,
                                                      const int32_t* __restrict__ pos, void* __restrict__ dYs,
                                                      float* __restrict__ dl, long N, int k, int cpr,
-                                                     float* __restrict__ S_out,   // S_out: sum_i w_i dw_i per token, or NULL
+                                                     const GateDense gate,   // (R NULL: only the selected logits have a gradient)
                                                      const uint4* __restrict__ X, uint4* __restrict__ Xs)
 {
     constexpr int V = Vec<T>::N;
@@ -140,7 +140,15 @@ __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY
 #pragma unroll
         for (int j = 0; j < kMaxK; ++j)
             if (j < k) dl[t * k + j] = w[j] * (dw[j] - s);
-        if (S_out) S_out[t] = s;
+    }
+    if (gate.R) {      // scores over all experts: -p_e s for the experts outside the selection
+        for (int e = lane; e < gate.stride; e += 64) {
+            float g = e < gate.E ? (float)(-gate.p[(size_t)t * gate.E + e] * (double)s) : 0.f;
+#pragma unroll
+            for (int j = 0; j < kMaxK; ++j)
+                if (j < k && gate.topk_idx[t * k + j] == e) g = w[j] * (dw[j] - s);
+            gate.R[(size_t)t * gate.stride + e] = g;
+        }
     }
 }
 
@@ -149,7 +157,7 @@ template <typename T>
 __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const void* __restrict__ dXs, const void* __restrict__ WgT,
                                                  const float* __restrict__ dl, const int32_t* __restrict__ topk_idx,
                                                  const int32_t* __restrict__ pos, void* __restrict__ dX, long N, int k,
-                                                 int cpr, const float* __restrict__ dxd)   // dxd: [N][d] float to add, or NULL
+                                                 int cpr)
 {
     constexpr int V = Vec<T>::N;
     const long total = N * cpr;
@@ -172,10 +180,6 @@ __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const 
             Vec<T>::load(WgT, (size_t)topk_idx[a] * cpr + c, wv);
 #pragma unroll
             for (int u = 0; u < V; ++u) acc[u] = fmaf(g, wv[u], acc[u]);
-        }
-        if (dxd) {
-#pragma unroll
-            for (int u = 0; u < V; ++u) acc[u] += dxd[(size_t)i * V + u];
         }
         Vec<T>::store(dX, (size_t)i, acc);
     }
@@ -268,9 +272,7 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
 template <typename G>
 __device__ __forceinline__ void dwg_final_body(int bx, int e, const float* __restrict__ part, const float* __restrict__ bpart,
                                                const int32_t* __restrict__ P64, G* __restrict__ dWg,
-                                               float* __restrict__ dbg, int d, int E, int accumulate,
-                                               const float* __restrict__ dense_part,     // [nch][E][d] to add, or NULL
-                                               const float* __restrict__ dense_bpart, int nch)
+                                               float* __restrict__ dbg, int d, int E, int accumulate)
 {
     const int row = bx * 256 + threadIdx.x;
     const int q1 = P64[e + 1];
@@ -283,8 +285,6 @@ __device__ __forceinline__ void dwg_final_body(int bx, int e, const float* __res
             s = (((s + a0) + a1) + a2) + a3;
         }
         for (; q < q1; ++q) s += part[(size_t)q * d + row];
-        if (dense_part)
-            for (int c = 0; c < nch; ++c) s += dense_part[((size_t)c * E + e) * d + row];
         const size_t i = (size_t)row * E + e;
         if constexpr (sizeof(G) == 2) {
             if (accumulate) s += bf16_to_f32(dWg[i]);
@@ -297,8 +297,6 @@ __device__ __forceinline__ void dwg_final_body(int bx, int e, const float* __res
     if (dbg && row == 0) {
         float s = 0.f;
         for (int q = P64[e]; q < q1; ++q) s += bpart[q];
-        if (dense_bpart)
-            for (int c = 0; c < nch; ++c) s += dense_bpart[(size_t)c * E + e];
         if (accumulate) s += dbg[e];
         dbg[e] = s;
     }
@@ -309,19 +307,15 @@ __device__ __forceinline__ void dwg_final_body(int bx, int e, const float* __res
 template <typename T, typename G>
 __global__ __launch_bounds__(256) void gate_bwd_tail(int fgx, const float* __restrict__ part, const float* __restrict__ bpart,
                                                      const int32_t* __restrict__ P64, G* __restrict__ dWg, float* __restrict__ dbg,
-                                                     int d, int E, int accumulate, const float* __restrict__ dense_part,
-                                                     const float* __restrict__ dense_bpart, int nch,
-                                                     const void* __restrict__ dXs, const void* __restrict__ WgT,
+                                                     int d, int E, int accumulate, const void* __restrict__ dXs, const void* __restrict__ WgT,
                                                      const float* __restrict__ dl, const int32_t* __restrict__ topk_idx,
-                                                     const int32_t* __restrict__ pos, void* __restrict__ dX, long N, int k, int cpr,
-                                                     const float* __restrict__ dxd)
+                                                     const int32_t* __restrict__ pos, void* __restrict__ dX, long N, int k, int cpr)
 {
     const int nfinal = fgx * E;
     if ((int)blockIdx.x < nfinal)
-        dwg_final_body<G>((int)blockIdx.x % fgx, (int)blockIdx.x / fgx, part, bpart, P64, dWg, dbg, d, E, accumulate, dense_part,
-                          dense_bpart, nch);
+        dwg_final_body<G>((int)blockIdx.x % fgx, (int)blockIdx.x / fgx, part, bpart, P64, dWg, dbg, d, E, accumulate);
     else
-        gate_bwd_dx_body<T>((long)blockIdx.x - nfinal, (long)gridDim.x - nfinal, dXs, WgT, dl, topk_idx, pos, dX, N, k, cpr, dxd);
+        gate_bwd_dx_body<T>((long)blockIdx.x - nfinal, (long)gridDim.x - nfinal, dXs, WgT, dl, topk_idx, pos, dX, N, k, cpr);
 }
 
 // out[e][c] = sum of the pieces of expert e, in ascending order (the column sums of its segment).
@@ -365,33 +359,22 @@ void launch_combine(const moe_desc_t& D, const void* Ys, const float* topk_w, co
 }
 
 void launch_dcombine(const moe_desc_t& D, const void* dY, const void* Ys, const float* topk_w,
-                     const int32_t* pos, void* dYs, float* dl, float* S_out, const void* X, void* Xs, hipStream_t st)
+                     const int32_t* pos, void* dYs, float* dl, const GateDense& gate, const void* X, void* Xs, hipStream_t st)
 {
     const int cpr = (int)((size_t)D.d * dtype_size(D.dtype) / 16);
     const unsigned g = (unsigned)((D.N + 3) / 4);
     if (D.dtype == MOE_BF16)
         hipLaunchKernelGGL(dcombine_rows<unsigned short>, dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl,
-                           (long)D.N, D.k, cpr, S_out, (const uint4*)X, (uint4*)Xs);
+                           (long)D.N, D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
     else
         hipLaunchKernelGGL(dcombine_rows<float>, dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl, (long)D.N,
-                           D.k, cpr, S_out, (const uint4*)X, (uint4*)Xs);
+                           D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
 }
 
 void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
                      const float* dl, const int32_t* topk_idx, const int32_t* pos, const int32_t* perm,
-                     const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws,
-                     const void* X_dense, hipStream_t st)
+                     const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws, hipStream_t st)
 {
-    // X_dense != NULL (scores over all experts): the experts that were not selected receive gradient too; their
-    // dense terms are computed first and added inside the kernels below that round dWg, dbg and dX.
-    const float *dpart = nullptr, *dbpart = nullptr, *dxd = nullptr;
-    if (X_dense) {
-        launch_gate_dense(D, L, X_dense, Wg, topk_idx, ws, st);
-        dpart = (const float*)(ws + L.dense_part);
-        dbpart = (const float*)(ws + L.dense_bpart);
-        if (D.N > 0) dxd = (const float*)(ws + L.dx_dense);
-    }
-    const int nch = D.N > 0 ? L.dense_chunks : 0;
     const int cpr = (int)((size_t)D.d * dtype_size(D.dtype) / 16);
     float* part = (float*)(ws + L.dwg_part);
     float* bpart = (float*)(ws + L.dbg_part);
@@ -407,19 +390,19 @@ void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, con
                            (const T*)Wg, (T*)WgT);
         if (D.grad_dtype == MOE_BF16)
             hipLaunchKernelGGL((gate_bwd_tail<T, unsigned short>), tg, dim3(256), 0, st, fgx, (const float*)part, (const float*)bpart, P64,
-                               (unsigned short*)dWg, dbg, D.d, D.E, D.accumulate, dpart, dbpart, nch, dXs, (const void*)WgT, dl,
-                               topk_idx, pos, dX, (long)D.N, D.k, cpr, dxd);
+                               (unsigned short*)dWg, dbg, D.d, D.E, D.accumulate, dXs, (const void*)WgT, dl,
+                               topk_idx, pos, dX, (long)D.N, D.k, cpr);
         else
             hipLaunchKernelGGL((gate_bwd_tail<T, float>), tg, dim3(256), 0, st, fgx, (const float*)part, (const float*)bpart, P64,
-                               (float*)dWg, dbg, D.d, D.E, D.accumulate, dpart, dbpart, nch, dXs, (const void*)WgT, dl, topk_idx,
-                               pos, dX, (long)D.N, D.k, cpr, dxd);
+                               (float*)dWg, dbg, D.d, D.E, D.accumulate, dXs, (const void*)WgT, dl, topk_idx,
+                               pos, dX, (long)D.N, D.k, cpr);
     } else {
         using T = float;
         hipLaunchKernelGGL(dwg_partial<T>, pg, dim3(512), 0, st, Xs, dl, perm, counts, offsets, P64, part, bpart, D.E, D.d, cpr,
                            (const T*)Wg, (T*)WgT);
         hipLaunchKernelGGL((gate_bwd_tail<T, float>), tg, dim3(256), 0, st, fgx, (const float*)part, (const float*)bpart, P64,
-                           (float*)dWg, dbg, D.d, D.E, D.accumulate, dpart, dbpart, nch, dXs, (const void*)WgT, dl, topk_idx, pos,
-                           dX, (long)D.N, D.k, cpr, dxd);
+                           (float*)dWg, dbg, D.d, D.E, D.accumulate, dXs, (const void*)WgT, dl, topk_idx, pos,
+                           dX, (long)D.N, D.k, cpr);
     }
 }
 

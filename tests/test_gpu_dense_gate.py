@@ -1,0 +1,49 @@
+"""Gate gradients with scores over all experts (dense products on 64 x 64 tiles, chunks of tokens) at the edges of tiles and
+chunks, against the fp64 oracle; and the load-balance sums at the edge of their chunks of 256 tokens."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _full_check
+from paper_2103_13262_amd.synth import Workload
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    Workload("one_token_one_expert", 1, 32, 32, 1, 1, "bf16", 0.0, 601, 0.0, True),
+    Workload("expert_count_no_multiple_of_4", 65, 96, 64, 66, 2, "f32", 0.0, 602, 0.0, True),
+    Workload("one_token_past_a_chunk", 577, 160, 32, 61, 3, "bf16", 0.0, 603, 0.0, True),
+    Workload("most_experts", 130, 64, 32, 1024, 8, "f32", 0.0, 604, 0.0, True),
+    Workload("long_chunks", 16500, 544, 32, 130, 1, "bf16", 0.4, 605, 0.0, True),      # 512-token chunks
+]
+
+
+@pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
+def test_dense_gate_gradient(w):
+    _full_check(w)
+
+
+@pytest.mark.parametrize("N,E", [(1, 3), (257, 70), (600, 1024), (3000, 2)])
+def test_balance_sums(N, E):
+    import torch
+
+    from paper_2103_13262_amd import binding as B
+
+    d = 64
+    desc = B.make_desc(N, d, 32, E, 1, B.MOE_F32, balance_stats=1)
+    buf = B.MoeLayerBuffers(desc)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(N)
+    X = torch.randn((N, d), device="cuda:0", generator=gen)
+    Wg = torch.randn((d, E), device="cuda:0", generator=gen)
+    fraction, prob, loss = (torch.empty(n, device="cuda:0") for n in (E, E, 1))
+    st = buf.stream()
+    B.moe_plan(desc, X, Wg, None, buf.plan, buf.workspace, buf.ws_bytes, st)
+    B.moe_balance_stats(desc, buf.plan, fraction, prob, loss, buf.workspace, buf.ws_bytes, st)
+    l = X.double().cpu().numpy() @ Wg.double().cpu().numpy()
+    p = np.exp(l - l.max(1, keepdims=True))
+    p = (p / p.sum(1, keepdims=True)).mean(0)
+    f = np.bincount(l.argmax(1), minlength=E) / N
+    # sums in fp64, one rounding to fp32 (2^-24) at the end; fp64 logits and exponentials: 1e-13
+    np.testing.assert_allclose(prob.cpu().numpy(), p, rtol=1e-6, atol=1e-12)
+    np.testing.assert_allclose(fraction.cpu().numpy(), f, rtol=1e-6)
+    np.testing.assert_allclose(loss.item(), E * (f * p).sum(), rtol=1e-6)
