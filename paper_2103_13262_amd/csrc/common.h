@@ -13,7 +13,8 @@ namespace moe {
 
 constexpr int kMaxE = 1024;
 constexpr int kMaxK = 8;
-constexpr int kPlanChunk = 1024;  // assignments ranked by one workgroup of the plan kernels
+// Assignments placed by one workgroup of the plan kernels: 1024, or as many more as keep the chunks at 256.
+inline long plan_chunk(long M) { return 1024 * (M > 256 * 1024 ? (M + 256 * 1024 - 1) / (256 * 1024) : 1); }
 constexpr int kBalanceChunk = 256;  // tokens whose gate probabilities one workgroup of the load-balance monitor sums
 inline int gate_r_stride(int E) { return (E + 3) / 4 * 4; }   // floats per row of gate_R: 16-byte pieces, the last padded with zeros
 constexpr int kNumTileHeights = 4;  // row-tile prefix tables are kept for 32, 64, 128, 256 rows
@@ -39,7 +40,7 @@ struct WsLayout {
     size_t tileP;     // [4][E+1] int32: prefix of ceil(counts/BM) for BM = 32,64,128,256
     size_t order;     // [E] int32: experts by descending count (ties: lower id first)
     size_t cls;       // [5][E+1] int32: the experts' rows in two size classes (see kCls* below)
-    size_t hist;      // [nb][E] int32: per plan-chunk histogram, then exclusive base inside the expert
+    size_t hist;      // [nb][E] int32: per plan-chunk histogram
     size_t dwg_part;  // [pieces][d] float: partial sums of dWg over pieces of 64 rows
     size_t dbg_part;  // [pieces] float
     size_t bias_part; // [pieces][max(d,h)] float: partial column sums for the expert-bias gradients
@@ -58,7 +59,7 @@ struct WsLayout {
     size_t sk_error;  // int32: set if a wait for a partial sum ran out
     size_t sk_part;   // [kSkPhases][kMaxPersistentWgs] fp32 tiles: partial sums of split output tiles (bf16 only)
     size_t total;
-    int nb;           // plan chunks = ceil(M / kPlanChunk)
+    int nb;           // plan chunks = ceil(M / plan_chunk(M))
     long dwg_pieces;  // upper bound of 64-row pieces over all experts: floor(M/64) + E
 };
 
@@ -100,7 +101,7 @@ inline WsLayout ws_layout(const moe_desc_t& D)
     L.tileP = take((size_t)kNumTileHeights * (D.E + 1) * sizeof(int32_t));
     L.order = take((size_t)D.E * sizeof(int32_t));
     L.cls = take((size_t)kClsTables * (D.E + 1) * sizeof(int32_t));
-    L.nb = (int)((M + kPlanChunk - 1) / kPlanChunk);
+    L.nb = (int)((M + plan_chunk((long)M) - 1) / plan_chunk((long)M));
     L.hist = take((size_t)(L.nb > 0 ? L.nb : 1) * D.E * sizeof(int32_t));
     L.dwg_pieces = (long)(M / 64) + D.E;
     L.dwg_part = take((size_t)L.dwg_pieces * D.d * sizeof(float));

@@ -2,33 +2,34 @@
 // (Section 3.2: the samples per expert are counted first and the buffer offsets follow from
 // the counts; Section 4: the samples of one expert lie contiguously).  Integer work only.
 //
-//   plan_hist : per chunk of kPlanChunk assignments, an LDS histogram over experts (small problems: done by
-//               plan_scan itself, which saves the launch).
-//   plan_scan : one workgroup; column scan over chunks -> counts and per-chunk bases, exclusive
-//               scan over experts -> offsets, tile prefix tables for four row-tile heights,
-//               experts ordered by descending count.
-//   plan_rank : per chunk, each wavefront ranks 64 assignments at a time with ballots (lanes
-//               that hold the same expert are found bit by bit), so rows keep assignment order.
+//   plan_hist  : per chunk of assignments, an LDS histogram over experts (batches of more than kOwnCounts assignments only).
+//   plan_place : workgroup 0 writes the tables - counts, offsets, tile prefix tables for four row-tile heights, size
+//                classes, experts ordered by descending count, the control block; every other workgroup places the
+//                assignments of one chunk.  All of them work out the counts and offsets they need for themselves (from the
+//                chunk histograms, or from the indices where those are few), so that the placing does not wait for a
+//                launch of one workgroup in front of it.  Ranks inside a wavefront come from ballots (lanes that hold the same
+//                expert are found bit by bit), so rows keep assignment order.
+// Bound by latency.  With the tables in a launch of one workgroup and the placing behind it: 12.4 us at 8192 assignments and 16
+// experts, 17.2 us at 200 and 256, 21.5 us at 16384 and 256, 29.0 us at 65536 and 32; now 8.8, 8.4, 14.2 and 11.0 us.
 #include "common.h"
 
 namespace moe {
 
-__global__ __launch_bounds__(256) void plan_hist(const int32_t* __restrict__ idx, long M, int E,
-                                                 int32_t* __restrict__ hist)
+constexpr int kThreads = 1024, kWaves = kThreads / 64;
+constexpr int kOwnCounts = 8 * 1024;   // assignments up to which every workgroup counts them itself
+
+__global__ __launch_bounds__(kThreads) void plan_hist(const int32_t* __restrict__ idx, long M, int E, int chunk, int32_t* __restrict__ hist)
 {
     __shared__ int sh[kMaxE];
-    for (int e = threadIdx.x; e < E; e += 256) sh[e] = 0;
+    for (int e = threadIdx.x; e < E; e += kThreads) sh[e] = 0;
     __syncthreads();
-    const long base = (long)blockIdx.x * kPlanChunk;
-    for (int q = 0; q < kPlanChunk / 256; ++q) {
-        const long a = base + q * 256 + threadIdx.x;
-        if (a < M) {
-            const int e = idx[a];
-            if (e >= 0 && e < E) atomicAdd(&sh[e], 1);
-        }
+    const long base = (long)blockIdx.x * chunk, end = min(base + chunk, M);
+    for (long a = base + threadIdx.x; a < end; a += kThreads) {
+        const int e = idx[a];
+        if (e >= 0 && e < E) atomicAdd(&sh[e], 1);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < E; e += 256) hist[(size_t)blockIdx.x * E + e] = sh[e];
+    for (int e = threadIdx.x; e < E; e += kThreads) hist[(size_t)blockIdx.x * E + e] = sh[e];
 }
 
 // Exclusive scans of NV ints per thread over a 1024-thread workgroup, all at once (v[i] -> sum of v[i] over the
@@ -55,78 +56,125 @@ __device__ __forceinline__ void block_excl_scan_1024(int (&v)[NV], int (*s_wave)
         for (int i = 0; i < NV; ++i) s_wave[wave][i] = inc[i];
     }
     __syncthreads();
+    int wbase[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        int wbase = 0, tot = 0;
-        for (int w = 0; w * 64 < n_used; ++w) {
+    for (int i = 0; i < NV; ++i) wbase[i] = total[i] = 0;
+    for (int w = 0; w * 64 < n_used; ++w) {           // (a wavefront's NV sums are read together)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
             const int c = s_wave[w][i];
-            if (w < wave) wbase += c;
-            tot += c;
+            if (w < wave) wbase[i] += c;
+            total[i] += c;
         }
-        total[i] = tot;
-        v[i] = wbase + inc[i] - v[i];
     }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = wbase[i] + inc[i] - v[i];
 }
 
-constexpr int kFusedHistInts = 8192;   // chunk histograms that plan_scan builds itself when they fit (32 KB of LDS)
-
-// idx == nullptr: the chunk histograms were written to `hist` by plan_hist.  Otherwise (nb * E <= kFusedHistInts)
-// this workgroup counts the assignments itself, into LDS, and saves that launch.
-__global__ __launch_bounds__(1024) void plan_scan(const int32_t* __restrict__ idx, int32_t* __restrict__ hist, int nb,
-                                                  int E, long M, int32_t* __restrict__ counts,
-                                                  int32_t* __restrict__ offsets, int32_t* __restrict__ tileP,
-                                                  int32_t* __restrict__ order, int32_t* __restrict__ cls,
-                                                  int32_t* __restrict__ zeros)
+// hist == nullptr: every workgroup counts the assignments itself.
+__global__ __launch_bounds__(kThreads) void plan_place(const int32_t* __restrict__ idx, const int32_t* __restrict__ hist, int nb, int chunk,
+                                                       int E, int nbits, long M, int32_t* __restrict__ counts,
+                                                       int32_t* __restrict__ offsets, int32_t* __restrict__ tileP,
+                                                       int32_t* __restrict__ order, int32_t* __restrict__ cls,
+                                                       int32_t* __restrict__ zeros, int32_t* __restrict__ pos, int32_t* __restrict__ perm)
 {
+    extern __shared__ __align__(16) int smem_plan[];
+    const int Ep = (E + 3) & ~3;
+    int* const s_total = smem_plan;                 // [Ep] rows of every expert
+    int* const s_below = s_total + Ep;              // [Ep] those in the chunks before this workgroup's; then the next free row
+    int* const s_w = s_below + Ep;                  // [kWaves][Ep] (placing)
+    __shared__ int s_wave[kWaves * (3 + kNumTileHeights)];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool tables = blockIdx.x == 0;
+    const int b = (int)blockIdx.x - 1;              // this workgroup's chunk
+    const long base = (long)b * chunk;
+    auto index = [&](long a) {                      // (an index out of range cannot come from the gate kernels)
+        int e = -1;
+        if (a < M) { e = idx[a]; if (e < 0 || e >= E) e = -1; }
+        return e;
+    };
+    int ev = tables ? -1 : index(base + tid);       // first round, on its way while the counts are taken
     // the control block: the page read in place of masked rows and the control words of the grouped products
-    if (threadIdx.x < kCtlWords) zeros[threadIdx.x] = 0;
-    __shared__ __align__(16) int s_cnt[kMaxE];
-    __shared__ int s_wave[16][3 + kNumTileHeights];
-    __shared__ int s_hist[kFusedHistInts];
-    const int e = threadIdx.x;
-    int cnt = 0;
-    if (idx) {
-        for (int i = threadIdx.x; i < nb * E; i += 1024) s_hist[i] = 0;
-        __syncthreads();
-        for (long a0 = 0; a0 < M; a0 += 8 * 1024) {       // eight loads in flight per thread
-            int ev[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const long a = a0 + u * 1024 + threadIdx.x;
-                ev[u] = a < M ? idx[a] : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const long a = a0 + u * 1024 + threadIdx.x;
-                if (ev[u] >= 0 && ev[u] < E) atomicAdd(&s_hist[(int)(a / kPlanChunk) * E + ev[u]], 1);
-            }
-        }
-        __syncthreads();
+    if (tables && tid < kCtlWords) zeros[tid] = 0;
+    for (int e = tid; e < 2 * Ep; e += kThreads) s_total[e] = 0;
+    __syncthreads();
+    if (hist) {
+        int width = 1;
+        while (width < E) width <<= 1;
+        const int e = tid & (width - 1), groups = kThreads / width;
         if (e < E) {
-            for (int b = 0; b < nb; ++b) {                // exclusive bases inside the expert, for plan_rank
-                const int v = s_hist[b * E + e];
-                hist[(size_t)b * E + e] = cnt;
-                cnt += v;
+            int total = 0, below = 0;
+            for (int r0 = tid / width; r0 < nb; r0 += 8 * groups) {     // eight rows in flight
+                int v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)min(r0 + u * groups, nb - 1) * E + e];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int r = r0 + u * groups;
+                    if (r < nb) { total += v[u]; if (r < b) below += v[u]; }
+                }
             }
-            counts[e] = cnt;
+            atomicAdd(&s_total[e], total);
+            if (below) atomicAdd(&s_below[e], below);
         }
-    } else if (e < E) {
-        // chunk histograms -> exclusive bases inside the expert, eight chunks at a time so that their loads are in
-        // flight together (one after the other, each load would wait for the store before it)
-        for (int b0 = 0; b0 < nb; b0 += 8) {
+    } else {
+        for (long a0 = 0; a0 < M; a0 += 8 * kThreads) {
             int v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)min(b0 + u, nb - 1) * E + e];
+            for (int u = 0; u < 8; ++u) v[u] = index(a0 + u * kThreads + tid);
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (b0 + u < nb) {
-                    hist[(size_t)(b0 + u) * E + e] = cnt;
-                    cnt += v[u];
+                if (v[u] >= 0) {
+                    atomicAdd(&s_total[v[u]], 1);
+                    if (a0 + u * kThreads + tid < base) atomicAdd(&s_below[v[u]], 1);
                 }
         }
-        counts[e] = cnt;
     }
-    s_cnt[e] = e < E ? cnt : -1;
+    __syncthreads();
+
+    if (!tables) {
+        int sc[1] = {tid < E ? s_total[tid] : 0}, total[1];
+        block_excl_scan_1024<1>(sc, (int (*)[1])s_wave, total, E);
+        if (tid < E) s_below[tid] += sc[0];
+        for (long a0 = base; a0 < min(base + chunk, M); a0 += kThreads) {
+            const long a = a0 + tid;
+            const int next = a0 + kThreads < base + chunk ? index(a + kThreads) : -1;
+            for (int i = tid; i < kWaves * Ep; i += kThreads) s_w[i] = 0;
+            __syncthreads();
+            const bool valid = ev >= 0;
+            unsigned long long mask = __ballot(valid);
+            for (int bit = 0; bit < nbits; ++bit) {
+                const bool on = valid && ((ev >> bit) & 1);
+                const unsigned long long bal = __ballot(on);
+                mask &= on ? bal : ~bal;
+            }
+            const int rank = __popcll(mask & ((1ull << lane) - 1ull));
+            if (valid && rank == 0) s_w[wave * Ep + ev] = __popcll(mask);
+            __syncthreads();
+            if (tid < E) {
+                int run = s_below[tid], c[kWaves];
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) c[w] = s_w[w * Ep + tid];
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) { s_w[w * Ep + tid] = run; run += c[w]; }
+                s_below[tid] = run;
+            }
+            __syncthreads();
+            if (valid) {
+                const int p = s_w[wave * Ep + ev] + rank;
+                pos[a] = p;
+                perm[p] = (int32_t)a;
+            }
+            __syncthreads();                        // the counters are done with
+            ev = next;
+        }
+        return;
+    }
+
+    // ---- the tables ----
+    const int e = tid;
+    const int cnt = e < E ? s_total[e] : 0;
+    if (e < E) counts[e] = cnt;
     // one pass of scans: offsets, the tile prefix tables of every tile height, the two size classes of every expert's rows
     int nbig = cnt / kClsBigRows, last = cnt - nbig * kClsBigRows;
     if (last > kClsSmallRows) { ++nbig; last = 0; }
@@ -137,7 +185,7 @@ __global__ __launch_bounds__(1024) void plan_scan(const int32_t* __restrict__ id
     sc[2] = e < E && last > 0 ? 1 : 0;
 #pragma unroll
     for (int q = 0; q < kNumTileHeights; ++q) sc[3 + q] = e < E ? (cnt + tile_height(q) - 1) / tile_height(q) : 0;
-    block_excl_scan_1024<NV>(sc, s_wave, total, E);
+    block_excl_scan_1024<NV>(sc, (int (*)[NV])s_wave, total, E);
     const int off = sc[0];
     if (e < E) {
         offsets[e] = off;
@@ -156,89 +204,73 @@ __global__ __launch_bounds__(1024) void plan_scan(const int32_t* __restrict__ id
 #pragma unroll
         for (int q = 0; q < kNumTileHeights; ++q) tileP[q * (E + 1) + E] = total[3 + q];
     }
-    __syncthreads();
-    int rank = 0;                         // experts by descending count, ties by ascending id
-    if (e < E) {
-#pragma unroll 4
-        for (int o = 0; o < E; o += 4) {          // (the counts past E are -1: they never rank before an expert)
-            const int4 c = *(const int4*)&s_cnt[o];
-            rank += (c.x > cnt || (c.x == cnt && o < e)) ? 1 : 0;
-            rank += (c.y > cnt || (c.y == cnt && o + 1 < e)) ? 1 : 0;
-            rank += (c.z > cnt || (c.z == cnt && o + 2 < e)) ? 1 : 0;
-            rank += (c.w > cnt || (c.w == cnt && o + 3 < e)) ? 1 : 0;
-        }
-        order[rank] = e;
-    }
+    // Experts by descending count, ties by ascending id.  Up to 256: everybody's rank is counted, 1024 / (E rounded up to a
+    // power of two) threads per expert sharing the comparisons.  More (the comparisons grow with E^2: 1000 experts
+    // took 27 us of them): a bitonic sort of one key per thread.
     // Can the weight-gradient products give every XCD whole experts (expert of rank r to XCD r%8, every other
     // group of eight reversed)?  Then each operand panel is fetched by one XCD only.  Only if the reduction blocks
     // that each XCD would get stay within 10 % of the mean; the answer is control word kCtlByExpert.
-    __shared__ int s_xcd[8], s_big;
-    if (threadIdx.x < 8) s_xcd[threadIdx.x] = 0;
-    if (e < E && rank == 0) s_big = cnt;      // the largest expert
+    __shared__ int s_xcd[8];
+    if (tid < 8) s_xcd[tid] = 0;
+    int* const s_sorted = s_w;                      // counts in descending order
+    if (E <= 256) {
+        int* const s_rank = s_below;
+        for (int i = tid; i < Ep; i += kThreads) { s_rank[i] = 0; if (i >= E) s_total[i] = -1; }   // (they never rank before an expert)
+        __syncthreads();
+        int width = 1;
+        while (width < E) width <<= 1;
+        const int me = tid & (width - 1), groups = kThreads / width;
+        if (me < E) {
+            const int mine = s_total[me];
+            int rank = 0;
+#pragma unroll 4
+            for (int o = 4 * (tid / width); o < E; o += 4 * groups) {
+                const int4 c = *(const int4*)&s_total[o];
+                rank += (c.x > mine || (c.x == mine && o < me)) ? 1 : 0;
+                rank += (c.y > mine || (c.y == mine && o + 1 < me)) ? 1 : 0;
+                rank += (c.z > mine || (c.z == mine && o + 2 < me)) ? 1 : 0;
+                rank += (c.w > mine || (c.w == mine && o + 3 < me)) ? 1 : 0;
+            }
+            if (rank) atomicAdd(&s_rank[me], rank);
+        }
+        __syncthreads();
+        if (e < E) { order[s_rank[e]] = e; s_sorted[s_rank[e]] = cnt; }
+    } else {
+        unsigned long long* const s_key = (unsigned long long*)s_w;   // (kWaves * Ep ints: 1024 keys fit)
+        unsigned long long key = e < E ? ((unsigned long long)(cnt + 1u) << 32) | (unsigned)(kMaxE - 1 - e) : 0ull;
+        for (int k = 2; k <= kThreads; k <<= 1) {
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                unsigned long long other;
+                if (j < 64) other = __shfl_xor(key, j, 64);
+                else {
+                    __syncthreads();
+                    s_key[tid] = key;
+                    __syncthreads();
+                    other = s_key[tid ^ j];
+                }
+                const bool larger = ((tid & k) == 0) == ((tid & j) == 0);   // descending: the lower thread of a pair keeps the larger key
+                key = (key > other) == larger ? key : other;
+            }
+        }
+        __syncthreads();                            // (the keys are done with)
+        if (tid < E) { order[tid] = kMaxE - 1 - (int)(key & 0xffffffffu); s_sorted[tid] = (int)(key >> 32) - 1; }
+    }
     __syncthreads();
-    if (e < E) atomicAdd(&s_xcd[(rank >> 3) & 1 ? 7 - (rank & 7) : rank & 7], (cnt + 63) / 64);
+    if (wave * 64 < E) {                            // ranks r and r + 16 go to one XCD, and so do r and 15 - r
+        int v = tid < E ? (s_sorted[tid] + 63) / 64 : 0;
+        v += __shfl_xor(v, 32, 64);
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 15, 64);
+        if (lane < 8) atomicAdd(&s_xcd[lane], v);
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         int mx = 0, sum = 0;
         for (int x = 0; x < 8; ++x) { mx = max(mx, s_xcd[x]); sum += s_xcd[x]; }
         zeros[kCtlByExpert] = (E >= 8 && (long)mx * 80 <= (long)sum * 11) ? 1 : 0;
         // Strongly skewed sizes (largest expert above three times the mean): the weight-gradient products hand out
         // their tiles on demand instead of in fixed rounds; (control word kCtlSkewed).
-        zeros[kCtlSkewed] = (E >= 2 && (long)s_big * E > 3 * M) ? 1 : 0;
-    }
-}
-
-__global__ __launch_bounds__(256) void plan_rank(const int32_t* __restrict__ idx, long M, int E, int nbits,
-                                                 const int32_t* __restrict__ base, const int32_t* __restrict__ offsets,
-                                                 int32_t* __restrict__ pos, int32_t* __restrict__ perm)
-{
-    __shared__ int wcnt[4][kMaxE];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int e = threadIdx.x; e < E; e += 256)
-        for (int w = 0; w < 4; ++w) wcnt[w][e] = 0;
-    __syncthreads();
-    const long cbase = (long)blockIdx.x * kPlanChunk + wave * 256;
-    int ev[4];
-    for (int s = 0; s < 4; ++s) {
-        const long a = cbase + s * 64 + lane;
-        int e = -1;
-        if (a < M) {
-            e = idx[a];
-            if (e < 0 || e >= E) e = -1;  // cannot happen for indices written by the gate kernel
-        }
-        ev[s] = e;
-        if (e >= 0) atomicAdd(&wcnt[wave][e], 1);
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += 256) {
-        int run = base[(size_t)blockIdx.x * E + e] + offsets[e];
-        for (int w = 0; w < 4; ++w) {
-            const int c = wcnt[w][e];
-            wcnt[w][e] = run;
-            run += c;
-        }
-    }
-    __syncthreads();
-    for (int s = 0; s < 4; ++s) {
-        const int e = ev[s];
-        const bool valid = e >= 0;
-        unsigned long long mask = __ballot(valid);
-        for (int b = 0; b < nbits; ++b) {
-            const bool bit = valid && ((e >> b) & 1);
-            const unsigned long long bal = __ballot(bit);
-            mask &= bit ? bal : ~bal;
-        }
-        int p = 0;
-        if (valid) {
-            const int rank = __popcll(mask & ((1ull << lane) - 1ull));
-            p = wcnt[wave][e] + rank;
-            const long a = cbase + s * 64 + lane;
-            pos[a] = p;
-            perm[p] = (int32_t)a;
-        }
-        __syncthreads();  // every lane has read its counter before the group leader advances it
-        if (valid && (mask >> lane) == 1ull) wcnt[wave][e] = p + 1;
-        __syncthreads();
+        zeros[kCtlSkewed] = (E >= 2 && (long)s_sorted[0] * E > 3 * M) ? 1 : 0;
     }
 }
 
@@ -247,17 +279,15 @@ void launch_plan(const moe_desc_t& D, const WsLayout& L, const int32_t* topk_idx
 {
     const long M = (long)D.N * D.k;
     int32_t* hist = (int32_t*)(ws + L.hist);
-    int32_t* tileP = (int32_t*)(ws + L.tileP);
-    int32_t* order = (int32_t*)(ws + L.order);
     int nbits = 0;
     while ((1 << nbits) < D.E) ++nbits;
-    const bool fused = L.nb > 0 && (long)L.nb * D.E <= kFusedHistInts;
-    if (L.nb > 0 && !fused) hipLaunchKernelGGL(plan_hist, dim3(L.nb), dim3(256), 0, st, topk_idx, M, D.E, hist);
-    hipLaunchKernelGGL(plan_scan, dim3(1), dim3(1024), 0, st, fused ? topk_idx : (const int32_t*)nullptr, hist, L.nb, D.E,
-                       M, counts, offsets, tileP, order, (int32_t*)(ws + L.cls), (int32_t*)(ws + L.zeros));
-    if (L.nb > 0)
-        hipLaunchKernelGGL(plan_rank, dim3(L.nb), dim3(256), 0, st, topk_idx, M, D.E, nbits, (const int32_t*)hist,
-                           (const int32_t*)offsets, pos, perm);
+    const int chunk = (int)plan_chunk(M), Ep = (D.E + 3) & ~3;
+    const bool own = M <= kOwnCounts;
+    if (!own) hipLaunchKernelGGL(plan_hist, dim3(L.nb), dim3(kThreads), 0, st, topk_idx, M, D.E, chunk, hist);
+    if (!allow_dynamic_lds(plan_place, (2 + kWaves) * kMaxE * (int)sizeof(int))) return;
+    hipLaunchKernelGGL(plan_place, dim3(L.nb + 1), dim3(kThreads), (2 + kWaves) * Ep * sizeof(int), st, topk_idx,
+                       own ? (const int32_t*)nullptr : hist, L.nb, chunk, D.E, nbits, M, counts, offsets, (int32_t*)(ws + L.tileP),
+                       (int32_t*)(ws + L.order), (int32_t*)(ws + L.cls), (int32_t*)(ws + L.zeros), pos, perm);
 }
 
 }  // namespace moe
