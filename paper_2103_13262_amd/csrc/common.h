@@ -167,6 +167,10 @@ void launch_gate_bf16(const moe_desc_t& D, const void* X, const void* Wg, const 
                       void* WgT, int32_t* gate_fail, hipStream_t st);
 // (WgT: [E][d] scratch for the transposed gate matrix; logits [N][E]: only with desc.score_all or desc.balance_stats, else NULL; holds the
 // gate probabilities afterwards)
+// small batches: one workgroup per token, one launch (probs: as logits above)
+constexpr int kGateSmallMaxD = 16384;   // the token's features are kept in LDS as floats
+void launch_gate_small(const moe_desc_t& D, const void* X, const void* Wg, const float* bg, int32_t* topk_idx, float* topk_w,
+                       double* probs, int32_t* gate_fail, hipStream_t st);
 void launch_plan(const moe_desc_t& D, const WsLayout& L, const int32_t* topk_idx, int32_t* counts,
                  int32_t* offsets, int32_t* pos, int32_t* perm, char* ws, hipStream_t st);
 

@@ -8,7 +8,6 @@
 // at depth l/16; result register r of lane l is token 4r + l/16, expert l%16.  Up to 16 experts: one workgroup
 // per 16 tokens with the reduction split over its four wavefronts; up to 32: 64 tokens per workgroup, a wavefront
 // per 16 tokens; more: blocks of 64 experts, a wavefront per 16 experts.
-#include <cstdlib>
 #include <type_traits>
 
 #include "common.h"
@@ -550,9 +549,31 @@ __global__ __launch_bounds__(256) void gate_scores_all(double* __restrict__ logi
     }
 }
 
+// Whether a workgroup per token (gate_small.hip) beats the tiled kernels: there every workgroup reads the gate matrix, so its
+// time grows with every 256 tokens (one workgroup per compute unit) by about 2 us and the matrix at 78 bytes per nanosecond,
+// 2.7 times that where E is no multiple of the elements in 16 bytes; the tiled kernels' time does not depend on the token
+// count until the chip is full.  Estimates in microseconds, from sweeps over d 256 / 1024 / 2048 (tiled -> small, event overhead of 4
+// us included in both).  bf16, N 256: E 16: 8 / 12 / 17 -> 8 / 8 / 9, E 24: 19 / 26 / 36 -> 8 / 9 / 10, E 57: 18 / 25 / 36 -> 11 / 14 / 19, E
+// 256: 24 / 34 / 52 -> 10 / 17 / 26, E 1000: 149 / 301 / 504 -> 17 / 39 / 68; N 1024: E 16: 8 / 12 / 17 -> 15 / 15 / 17, E 24: 19 / 27 / 36 -> 15 /
+// 16 / 18, E 57: 19 / 26 / 36 -> 20 / 31 / 43, E 256: 24 / 35 / 52 -> 20 / 40 / 66.  fp32, N 256: E 24: 20 / 50 / 90 -> 8 / 9 / 9.
+static bool small_batch(const moe_desc_t& D, bool logits)
+{
+    if (D.d > kGateSmallMaxD) return false;
+    const int V = 16 / (int)dtype_size(D.dtype);
+    const double bytes = (double)D.d * D.E * dtype_size(D.dtype);
+    const double small = 2.0 + (D.N + 255) / 256 * (1.8 + bytes / 78e3 * (D.E % V ? 2.7 : 1.0));
+    const bool fast_bf16 = D.dtype == MOE_BF16 && D.E <= 256 && !logits;
+    const double tiled = D.E <= 16 ? 3.0 + D.d * 0.0047 : fast_bf16 ? 11.5 + D.d * 0.01 : 12.0 + (double)D.d * D.E * 3e-4;
+    return small <= tiled;
+}
+
 void launch_gate_topk(const moe_desc_t& D, const void* X, const void* Wg, const float* bg, int32_t* topk_idx,
                       float* topk_w, void* WgT, double* logits, int32_t* gate_fail, hipStream_t st)
 {
+    if (small_batch(D, logits != nullptr)) {
+        launch_gate_small(D, X, Wg, bg, topk_idx, topk_w, logits, gate_fail, st);
+        return;
+    }
     if (D.dtype == MOE_BF16 && D.E > 16 && D.E <= 256 && !logits) {
         launch_gate_bf16(D, X, Wg, bg, topk_idx, topk_w, WgT, gate_fail, st);
         return;
