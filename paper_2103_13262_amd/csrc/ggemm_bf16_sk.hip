@@ -200,8 +200,9 @@ struct Fin {              // what finishing an item needs once the streams have 
 
 // CLS: 0 = all rows of every expert (tables counts / offsets / tileP); 1 = the rows in whole blocks of
 // kClsBigRows, 2 = the experts' last pieces (the plan step's size-class tables; rows kinds only).
-// Of every XCD's workgroups, those numbered wj_base .. wj_base + wj_count - 1 take part (wj_count <= 0: all); the
-// others return at once.
+// Of every XCD's workgroups, those numbered wj_base .. wj_base + wj_count - 1 take part and the others return at once;
+// wj_count <= 0: all take part, counted round from wj_base (which only a launch of whole tiles may set then: a split
+// tile's partial sums go from one workgroup to the one numbered next).
 template <int KIND, int WM, int WN, int TM, int TN, int STAGES, int BK, int CLS = 0>
 __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int ntn, int wj_base = 0, int wj_count = 0)
 {
@@ -225,7 +226,9 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
     const long long probe_cycles0 = clock64(), probe_ticks0 = wall_clock64();
 
     // ---------------- schedule of this workgroup ----------------
-    const int xcd = blockIdx.x & 7, wj = (int)(blockIdx.x >> 3) - wj_base, W = wj_count > 0 ? wj_count : (int)(gridDim.x >> 3);
+    const int xcd = blockIdx.x & 7, W = wj_count > 0 ? wj_count : (int)(gridDim.x >> 3);
+    int wj = (int)(blockIdx.x >> 3) - wj_base;
+    if (wj_count <= 0 && wj < 0) wj += W;
     if (wj < 0 || wj >= W) return;
     const int32_t* P = CLS == 0 ? g.tileP + tile_height_index(BM) * (g.E + 1)
                                 : g.cls + (CLS == 1 ? kClsPBig : kClsPSmall) * (g.E + 1);
@@ -927,12 +930,17 @@ __device__ __forceinline__ void ggemm_classes(const GemmArgs& g, int ntn_big, in
     if (g.whole_tiles) {
         // Followed by another product in the same launch: whole tiles only.  The big tiles go round the workgroups
         // from the first on; the last pieces, in 128 x 256 tiles (a 128 x 512 tile of a deep reduction would be the
-        // longest item of the launch), start behind the big tiles' last round, so that no workgroup gets one of each.
+        // longest item of the launch), start behind the big tiles' last round: up to two of them stay with each of the
+        // workgroups that got no tile of that round (a big tile moves 4/3 of what a last piece's moves), more go round
+        // all workgroups from there on.  (Left to those workgroups alone, whatever their number, a load whose big
+        // tiles nearly filled the last round gave two workgroups of 32 all last pieces: dXs and dW1 of 16384 rows in
+        // 64 experts, Zipf 1.2, d 1024, h 4096, took 1123 us with one seed and 415 with others.)
         ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big);
         if (Ts == 0) return;
         __syncthreads();
         const int after = (int)(((Tb >> 3) + ((Tb & 7) ? 1 : 0)) % W);
-        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2>(g, 0, ntn_big, after < W - 1 ? after : 0, after < W - 1 ? W - after : W);
+        const bool behind = Ts <= 16L * (W - after);
+        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2>(g, 0, ntn_big, after, behind ? W - after : 0);
         return;
     }
     if (Ts == 0) { ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big); return; }
