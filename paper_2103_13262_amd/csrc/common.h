@@ -114,6 +114,7 @@ inline WsLayout ws_layout(const moe_desc_t& D)
     while (L.dense_chunk > 64 && (size_t)((D.N + L.dense_chunk - 1) / L.dense_chunk) * ((D.d + 63) / 64) * ((D.E + 63) / 64) < 512)
         L.dense_chunk /= 2;
     L.dense_chunks = (D.N + L.dense_chunk - 1) / L.dense_chunk;
+    const size_t before_scores = o;
     if (D.score_all || D.balance_stats) {
         L.logits = take((size_t)D.N * D.E * sizeof(double));
         L.prob_part = take((size_t)((D.N + kBalanceChunk - 1) / kBalanceChunk + 1) * D.E * sizeof(double));
@@ -122,6 +123,10 @@ inline WsLayout ws_layout(const moe_desc_t& D)
         L.gate_R = take((size_t)D.N * gate_r_stride(D.E) * sizeof(float));
         L.dense_part = take((size_t)L.dense_chunks * D.E * D.d * sizeof(float));
         L.dense_bpart = take((size_t)L.dense_chunks * D.E * sizeof(float));
+        // With scores over all experts the workspace stays at least N (12 E + 4 d) bytes larger than without, the size that
+        // callers count on; the products need less of it when N is small (no [N][d] sums).
+        const size_t least = before_scores + (size_t)D.N * (12 * (size_t)D.E + 4 * (size_t)D.d);
+        if (o < least) o = (least + 255) / 256 * 256;
     }
     L.zeros = take(kZeroedBytes);
     L.sk_flags = L.zeros + kCtlFlags * sizeof(int32_t);
