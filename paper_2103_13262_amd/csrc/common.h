@@ -179,7 +179,7 @@ void launch_gate_small(const moe_desc_t& D, const void* X, const void* Wg, const
 void launch_plan(const moe_desc_t& D, const WsLayout& L, const int32_t* topk_idx, int32_t* counts,
                  int32_t* offsets, int32_t* pos, int32_t* perm, char* ws, hipStream_t st);
 
-void launch_scatter(const moe_desc_t& D, const void* X, const int32_t* perm, void* Xs, hipStream_t st);
+void launch_scatter(const moe_desc_t& D, const void* X, const int32_t* pos, void* Xs, hipStream_t st);
 void launch_combine(const moe_desc_t& D, const void* Ys, const float* topk_w, const int32_t* pos, void* Y,
                     hipStream_t st);
 // With scores over all experts the combine backward also writes the gradient of every logit (R NULL: it does not).

@@ -489,7 +489,7 @@ moe_status_t moe_scatter(const moe_desc_t* desc, const moe_plan_t* plan, const v
     MOE_REQUIRE_PTR(X);
     MOE_REQUIRE_PTR(Xs);
     if (desc->N == 0) return MOE_OK;
-    launch_scatter(*desc, X, plan->perm, Xs, (hipStream_t)stream);
+    launch_scatter(*desc, X, plan->pos, Xs, (hipStream_t)stream);
     return check_launch("scatter");
 }
 
