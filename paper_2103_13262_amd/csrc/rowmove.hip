@@ -2,8 +2,8 @@
 // samples of one expert into contiguous memory, "gather" puts the rows back in their original
 // order; Algorithm 1: y accumulates score_i * E_i(x)), and their gradients.  All are bound by
 // HBM traffic: every thread moves 16-byte pieces of a row, rows are addressed through pos/perm.
-// The four movements and the plan of 32768 tokens, d 2048, 32 experts, top-2, bf16: 597 -> 560 us since scatter goes by token,
-// rows are found with 32-bit divisions and the k slots' loads are issued together (2.9 TB/s of what has to move at least,
+// The four movements and the plan of 32768 tokens, d 2048, 32 experts, top-2, bf16: 597 -> 551 us since scatter goes by token,
+// rows are found with 32-bit divisions and the loads of a thread are issued together (2.9 TB/s of what has to move at least,
 // the gate's product included; a plain copy reaches 5.1).
 #include "common.h"
 
@@ -120,22 +120,24 @@ __global__ __launch_bounds__(256) void combine_rows(const void* __restrict__ Ys,
 //   (Ys == NULL: the expert outputs were not kept - top-1 with the score fixed at 1, where dl is exactly zero)
 //   Rides along (X != NULL): Xs[pos[a],:] = X[t,:], the scatter that the weight gradients of the first layer and of
 //   the gate read; the token's row is in hand anyway, and the backward pass saves a launch.
-template <typename T>
+//   KC = k where it is 1, 2 or 4, so that no branch stands between the slots' loads; 0: any k.
+template <typename T, int KC>
 __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY, const void* __restrict__ Ys,
                                                      const float* __restrict__ topk_w,
                                                      const int32_t* __restrict__ pos, void* __restrict__ dYs,
-                                                     float* __restrict__ dl, long N, int k, int cpr,
+                                                     float* __restrict__ dl, long N, int kArg, int cpr,
                                                      const GateDense gate,   // (R NULL: only the selected logits have a gradient)
                                                      const uint4* __restrict__ X, uint4* __restrict__ Xs)
 {
-    constexpr int V = Vec<T>::N;
+    constexpr int V = Vec<T>::N, KM = KC > 0 ? KC : kMaxK;
+    const int k = KC > 0 ? KC : kArg;
     const int lane = threadIdx.x & 63;
     const long t = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= N) return;
-    float w[kMaxK], dw[kMaxK];
-    size_t r[kMaxK];
+    float w[KM], dw[KM];
+    size_t r[KM];
 #pragma unroll
-    for (int j = 0; j < kMaxK; ++j) {
+    for (int j = 0; j < KM; ++j) {
         dw[j] = 0.f;
         if (j < k) { r[j] = (size_t)pos[t * k + j]; w[j] = topk_w[t * k + j]; }
     }
@@ -144,19 +146,25 @@ __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY
         Vec<T>::load(dY, (size_t)t * cpr + c, g);
         uint4 x = make_uint4(0, 0, 0, 0);
         if (X) x = X[(size_t)t * cpr + c];
+        constexpr int YN = KC > 0 ? KC : 1;       // (any k: one slot after the other, in the registers of one)
+        float y[YN][V];
 #pragma unroll
-        for (int j = 0; j < kMaxK; ++j) {
+        for (int j = 0; j < YN; ++j)
+#pragma unroll
+            for (int u = 0; u < V; ++u) y[j][u] = 0.f;
+        if (KC > 0 && Ys) {
+#pragma unroll
+            for (int j = 0; j < YN; ++j) Vec<T>::load(Ys, r[j] * cpr + c, y[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
             if (j >= k) break;
-            float y[V], o[V];
-            if (Ys) Vec<T>::load(Ys, r[j] * cpr + c, y);
-            else {
-#pragma unroll
-                for (int u = 0; u < V; ++u) y[u] = 0.f;
-            }
+            if (KC == 0 && Ys) Vec<T>::load(Ys, r[j] * cpr + c, y[0]);
+            float o[V];
 #pragma unroll
             for (int u = 0; u < V; ++u) {
                 o[u] = w[j] * g[u];
-                dw[j] = fmaf(g[u], y[u], dw[j]);
+                dw[j] = fmaf(g[u], y[KC > 0 ? j : 0][u], dw[j]);
             }
             Vec<T>::store(dYs, r[j] * cpr + c, o);
             if (X) Xs[r[j] * cpr + c] = x;
@@ -164,7 +172,7 @@ __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY
     }
     float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < kMaxK; ++j) {
+    for (int j = 0; j < KM; ++j) {
         if (j >= k) break;
         float part = dw[j];
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
@@ -173,14 +181,14 @@ __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY
     }
     if (lane == 0) {
 #pragma unroll
-        for (int j = 0; j < kMaxK; ++j)
+        for (int j = 0; j < KM; ++j)
             if (j < k) dl[t * k + j] = w[j] * (dw[j] - s);
     }
     if (gate.R) {      // scores over all experts: -p_e s for the experts outside the selection
         for (int e = lane; e < gate.stride; e += 64) {
             float g = e < gate.E ? (float)(-gate.p[(size_t)t * gate.E + e] * (double)s) : 0.f;
 #pragma unroll
-            for (int j = 0; j < kMaxK; ++j)
+            for (int j = 0; j < KM; ++j)
                 if (j < k && gate.topk_idx[t * k + j] == e) g = w[j] * (dw[j] - s);
             gate.R[(size_t)t * gate.stride + e] = g;
         }
@@ -269,39 +277,33 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
     __shared__ float s_g[64];
     __shared__ float s_acc[7][64][V];
     const int piece = blockIdx.x;
-    if (piece >= P64[E]) return;          // uniform over the workgroup
-    int lo = 0, hi = E;                   // largest e with P64[e] <= piece
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (P64[mid] <= piece) lo = mid; else hi = mid;
-    }
-    const int e = lo;
-    const int r0 = offsets[e] + (piece - P64[e]) * 64;
-    const int r1 = min(r0 + 64, offsets[e] + counts[e]);
-    // (dl == nullptr: plain column sums of the segment, every row with weight 1: the expert-bias gradients)
-    if (threadIdx.x < 64) s_g[threadIdx.x] = r0 + (int)threadIdx.x < r1 ? (dl ? dl[perm[r0 + threadIdx.x]] : 1.f) : 0.f;
-    __syncthreads();
+    const int pieces = P64[E];
+    const Segment sg = find_segment(P64, E, piece, counts, offsets);   // (a piece past the last finds the last expert)
+    if (piece >= pieces) return;          // uniform over the workgroup
+    const int r0 = sg.offset + (piece - sg.first) * 64;
+    const int r1 = min(r0 + 64, sg.offset + sg.count);
     const int ct = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int c = blockIdx.y * 64 + ct;
     const bool active = c < cpr;
+    // The rows are asked for before the weights, whose two dependent loads and barrier then pass under them.
+    // (No branch around a load: it would wait for each before the next.  Rows past the end of the piece load its last row,
+    // columns past the last the last; what they loaded is not used.)  A step of 1000 tokens, d 768, h 3072, 8 experts with
+    // biases, whose gradients are such sums too: 347 -> 339 us.
+    float v[8][V];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) Vec<T>::load(Xs, (size_t)min(r0 + q * 8 + i, r1 - 1) * cpr + min(c, cpr - 1), v[i]);
+    // (dl == nullptr: plain column sums of the segment, every row with weight 1: the expert-bias gradients)
+    if (threadIdx.x < 64) s_g[threadIdx.x] = r0 + (int)threadIdx.x < r1 ? (dl ? dl[perm[r0 + threadIdx.x]] : 1.f) : 0.f;
+    __syncthreads();
     float acc[V];
 #pragma unroll
     for (int u = 0; u < V; ++u) acc[u] = 0.f;
-    if (active) {
-        float v[8][V];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {         // rows past the end of the piece contribute g = 0; their loads are skipped
-            const int r = r0 + q * 8 + i;
+    for (int i = 0; i < 8; ++i) {
+        const float g = s_g[q * 8 + i];
+        const bool row = r0 + q * 8 + i < r1;
 #pragma unroll
-            for (int u = 0; u < V; ++u) v[i][u] = 0.f;
-            if (r < r1) Vec<T>::load(Xs, (size_t)r * cpr + c, v[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float g = s_g[q * 8 + i];
-#pragma unroll
-            for (int u = 0; u < V; ++u) acc[u] = fmaf(g, v[i][u], acc[u]);
-        }
+        for (int u = 0; u < V; ++u) acc[u] = fmaf(g, row ? v[i][u] : 0.f, acc[u]);
     }
     if (q > 0) {
 #pragma unroll
@@ -432,12 +434,15 @@ void launch_dcombine(const moe_desc_t& D, const void* dY, const void* Ys, const 
 {
     const int cpr = (int)((size_t)D.d * dtype_size(D.dtype) / 16);
     const unsigned g = (unsigned)((D.N + 3) / 4);
-    if (D.dtype == MOE_BF16)
-        hipLaunchKernelGGL(dcombine_rows<unsigned short>, dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl,
-                           (long)D.N, D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
-    else
-        hipLaunchKernelGGL(dcombine_rows<float>, dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl, (long)D.N,
-                           D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
+    with_k(D.k, [&](auto kc) {
+        constexpr int K = decltype(kc)::value;
+        if (D.dtype == MOE_BF16)
+            hipLaunchKernelGGL((dcombine_rows<unsigned short, K>), dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl,
+                               (long)D.N, D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
+        else
+            hipLaunchKernelGGL((dcombine_rows<float, K>), dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl, (long)D.N,
+                               D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
+    });
 }
 
 void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
