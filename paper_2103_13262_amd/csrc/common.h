@@ -163,6 +163,13 @@ template <typename Kern> static bool allow_dynamic_lds(Kern kern, int bytes)
     return true;
 }
 
+// Whether two operands share memory: launches that write one while they read the other are taken apart then.
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes)
+{
+    const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+    return p < q + b_bytes && q < p + a_bytes;
+}
+
 // ---- kernel launchers (each enqueues on `st`; operand shapes are validated by the callers) ----
 void launch_gate_topk(const moe_desc_t& D, const void* X, const void* Wg, const float* bg, int32_t* topk_idx,
                       float* topk_w, void* WgT, double* logits, int32_t* gate_fail, hipStream_t st);

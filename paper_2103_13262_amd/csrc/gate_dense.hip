@@ -169,7 +169,8 @@ __device__ __forceinline__ void dense_dx_tile(const T* __restrict__ Wg, const fl
 constexpr int kDenseSmem = 2 * 2 * (operand_floats<true>() > operand_floats<false>() ? operand_floats<true>() : operand_floats<false>());
 static_assert(TM * kOutPitch <= kDenseSmem, "the output tile fits where the blocks were");
 
-// The first ndx workgroups write dX, the others the weight gradient's chunks.  Neither reads what the other writes.
+// The first ndx workgroups write dX, the others the weight gradient's chunks.  Neither reads what the other writes, unless
+// the caller has dX take the place of X: then the launcher has the two follow one another.
 template <typename T>
 __global__ __launch_bounds__(256) void gate_dense_pair(const T* __restrict__ X, const T* __restrict__ Wg, const float* __restrict__ R,
                                                        const T* __restrict__ dXs, const int32_t* __restrict__ pos, T* __restrict__ dX,
@@ -296,10 +297,17 @@ static void gate_dense_bwd(const moe_desc_t& D, const WsLayout& L, const void* X
     const long N = D.N;
     if (N > 0) {
         const int nti = (D.d + TN - 1) / TN, nte = (D.E + TM - 1) / TM;
-        const int ndx = (int)((N + TM - 1) / TM) * nti;
-        hipLaunchKernelGGL(gate_dense_pair<T>, dim3((unsigned)(ndx + L.dense_chunks * nti * nte)), dim3(256), 0, st, (const T*)X,
-                           (const T*)Wg, (const float*)(ws + L.gate_R), (const T*)dXs, pos, (T*)dX, N, D.d, D.E, gate_r_stride(D.E), D.k, ndx,
-                           L.dense_chunk, part, bpart);
+        const int ndx = (int)((N + TM - 1) / TM) * nti, ndw = L.dense_chunks * nti * nte;
+        auto launch = [&](int blocks, int dx_blocks) {
+            hipLaunchKernelGGL(gate_dense_pair<T>, dim3((unsigned)blocks), dim3(256), 0, st, (const T*)X, (const T*)Wg,
+                               (const float*)(ws + L.gate_R), (const T*)dXs, pos, (T*)dX, N, D.d, D.E, gate_r_stride(D.E), D.k, dx_blocks,
+                               L.dense_chunk, part, bpart);
+        };
+        const size_t bytes = (size_t)N * D.d * sizeof(T);
+        if (overlap(X, bytes, dX, bytes)) {
+            launch(ndw, 0);
+            launch(ndx, ndx);
+        } else launch(ndx + ndw, ndx);
     }
     hipLaunchKernelGGL(dense_final<G>, dim3((unsigned)((D.d + 255) / 256), (unsigned)D.E), dim3(256), 0, st, (const float*)part,
                        (const float*)bpart, N > 0 ? L.dense_chunks : 0, (G*)dWg, dbg, D.d, D.E, D.accumulate);
