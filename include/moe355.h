@@ -145,7 +145,7 @@ moe_status_t moe_forward(const moe_desc_t *desc, const moe_plan_t *plan, const v
  *   dWg device [d,E], dW1 device [E,d,h], dW2 device [E,h,d] in grad_dtype; written or
  *   accumulated per desc->accumulate.  dbg device [E] float or NULL, same rule.
  * Weight gradients are reduced in a fixed order: repeated calls give identical bits.
- * dX may take the place of X or of dY.
+ * dX may take the place of X or of dY, and dWg, dW1 and dW2 that of Wg, W1 and W2.
  */
 moe_status_t moe_backward(const moe_desc_t *desc, const moe_plan_t *plan, const void *X, const void *Wg,
                           const void *W1, const void *W2, const void *dY, void *dX, void *dWg, float *dbg,

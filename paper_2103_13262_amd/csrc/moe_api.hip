@@ -400,13 +400,18 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
     // dZ and dW2 need only dYs, and dXs and dW1 only dZ: where it pays, each pair is one launch in which a workgroup
     // that has finished its share of the first product goes on with tiles of the second.
     // (fp32: always - a workgroup there has one tile of either product, so the pair costs nothing and saves a launch)
+    // A weight's gradient that takes the place of the weight must wait for the product that reads the weight.
     const bool f32 = D.dtype == MOE_F32;
-    auto pays = [&](const GemmArgs& rows) { return D.N > 0 && (f32 || ggemm_pair_pays(rows)); };
+    const size_t weights = (size_t)D.E * D.d * D.h;
+    auto pays = [&](const GemmArgs& rows, const GemmArgs& cols) {
+        return D.N > 0 && (f32 || ggemm_pair_pays(rows)) &&
+               !overlap(rows.B, weights * dtype_size(D.dtype), cols.C, weights * dtype_size(D.grad_dtype));
+    };
     auto run_pair = [&](const GemmArgs& rows, const GemmArgs& cols) {
         if (f32) launch_ggemm_pair_f32(rows, cols, st);
         else launch_ggemm_pair_bf16_sk(rows, cols, st);
     };
-    if (pays(dh)) {
+    if (pays(dh, dw2)) {
         { ScopedTimer tm(S_DH_DW2, st); run_pair(dh, dw2); }
         if ((s = check_launch("expert layer 2 gradients")) != MOE_OK) return s;
     } else {
@@ -418,7 +423,7 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
         { ScopedTimer tm(S_DW2, st); run_gemm(D, dw2, st); }
         if ((s = check_launch("expert layer 2 weight gradient")) != MOE_OK) return s;
     }
-    if (pays(dxs)) {
+    if (pays(dxs, dw1)) {
         { ScopedTimer tm(S_DXS_DW1, st); run_pair(dxs, dw1); }
         if ((s = check_launch("expert layer 1 gradients")) != MOE_OK) return s;
     } else {

@@ -2,7 +2,7 @@
 one has yet to read."""
 import pytest
 
-from harness import GpuRun
+from harness import TOL, GpuRun, strict_err, to_numpy64
 from paper_2103_13262_amd.synth import Workload, make_inputs
 
 pytestmark = pytest.mark.gpu
@@ -25,3 +25,29 @@ def test_dx_in_the_place_of(w, place):
     run.torch.cuda.synchronize()
     for name in ("dX", "dWg", "dbg", "dW1", "dW2"):      # the same sums in the same order
         assert run.torch.equal(getattr(run, name), getattr(apart, name)), name
+
+
+WEIGHTS = [Workload("sliced", 130, 96, 64, 5, 2, "f32", 0.0, 811), Workload("tiled", 2100, 96, 512, 6, 2, "f32", 0.7, 812),
+           Workload("pair", 700, 256, 512, 6, 2, "bf16", 0.3, 813), Workload("dense", 300, 160, 64, 40, 2, "f32", 0.0, 814, 0.0, True)]
+
+
+@pytest.mark.parametrize("accumulate", [0, 1])
+@pytest.mark.parametrize("w", WEIGHTS, ids=lambda w: f"{w.name}_{w.dtype}")
+def test_weight_gradients_in_the_place_of_the_weights(w, accumulate):
+    print(f"[case] {w} accumulate {accumulate}", flush=True)
+    inputs = make_inputs(w)
+    apart = GpuRun(w, inputs, accumulate=accumulate)
+    run = GpuRun(w, inputs, accumulate=accumulate)
+    for name in ("Wg", "W1", "W2"):
+        getattr(apart, "d" + name).copy_(getattr(apart, name))      # (what an accumulating call adds to)
+        setattr(run, "d" + name, getattr(run, name))
+    apart.dbg.zero_()
+    run.dbg.zero_()
+    for r in (apart, run):
+        r.plan()
+        r.forward()
+        r.backward()
+        assert r.status() == 0
+    # Two launches in the place of one may sum in another order: the bar of a tensor against the oracle holds between them.
+    for name in ("dX", "dWg", "dbg", "dW1", "dW2"):
+        assert strict_err(to_numpy64(getattr(run, name)), to_numpy64(getattr(apart, name))) <= TOL[w.dtype], name
