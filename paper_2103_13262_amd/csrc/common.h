@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "../../include/moe355.h"
+#include "dynamic_lds.h"
 
 namespace moe {
 
@@ -138,30 +139,8 @@ inline WsLayout ws_layout(const moe_desc_t& D)
 
 // ---- error reporting -------------------------------------------------------------------
 void set_error(const char* fmt, ...);
-// A launcher that could not launch (a function attribute was refused, no usable device): records the text and makes
-// the next check_launch on this thread return MOE_ERR_HIP.
-void fail_launch(const char* fmt, ...);
 moe_status_t check_launch(const char* what);
-constexpr int kMaxDevices = 64;   // per-device caches (function attributes, compute-unit counts) are indexed by the HIP device id
-int current_device();             // the calling thread's HIP device, or -1 (after fail_launch)
 moe_status_t check_desc(const moe_desc_t* D);   // host-side validation of a problem description (sets the error text)
-
-// Kernels whose dynamic LDS exceeds the default limit: the kernel's limit is raised once per device (the static
-// state is per kernel: one instance of this template each).  False after fail_launch.
-template <typename Kern> static bool allow_dynamic_lds(Kern kern, int bytes)
-{
-    static std::mutex mu;
-    static bool done[kMaxDevices] = {};
-    const int dev = current_device();
-    if (dev < 0) return false;
-    std::lock_guard<std::mutex> lk(mu);
-    if (!done[dev]) {
-        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e != hipSuccess) { fail_launch("%d bytes of dynamic LDS refused on device %d: %s", bytes, dev, hipGetErrorString(e)); return false; }
-        done[dev] = true;
-    }
-    return true;
-}
 
 // Whether two operands share memory: launches that write one while they read the other are taken apart then.
 inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes)

@@ -424,7 +424,7 @@ template <int G>
 static void launch_fast(const moe_desc_t& D, const u16* X, const u16* WgT, const float* bg, int32_t* topk_idx, float* topk_w,
                         int32_t* fail, hipStream_t st)
 {
-    if (!allow_dynamic_lds(gate_bf16_kernel<G>, Lds<G>::kTotal)) return;
+    if (!allow_dynamic_lds<gate_bf16_kernel<G>>(Lds<G>::kTotal)) return;
     hipLaunchKernelGGL(gate_bf16_kernel<G>, dim3((unsigned)((D.N + kTok - 1) / kTok)), dim3(kWaves * 64), Lds<G>::kTotal, st, X, WgT, bg,
                        D.N, D.d, D.E, D.k, topk_idx, topk_w, fail);
 }

@@ -197,8 +197,8 @@ void launch(const moe_desc_t& D, const T* X, const T* Wg, const float* bg, int32
 {
     constexpr int V = Elems<T>::V, kSums = kThreads * V * (int)sizeof(double);
     const int q = D.E / std::gcd(D.E, V), Tn = kThreads / q * q;
-    auto kern = gate_small_kernel<T, WHOLE, CPL, SHARED>;
-    if (!allow_dynamic_lds(kern, kSums + kGateSmallMaxD * (int)sizeof(float))) return;
+    constexpr auto kern = gate_small_kernel<T, WHOLE, CPL, SHARED>;
+    if (!allow_dynamic_lds<kern>(kSums + kGateSmallMaxD * (int)sizeof(float))) return;
     hipLaunchKernelGGL(kern, dim3((unsigned)D.N), dim3(kThreads), kSums + D.d * (int)sizeof(float), st, X, Wg, bg, D.d, D.E, D.k, Tn,
                        topk_idx, topk_w, probs, D.score_all, fail);
 }

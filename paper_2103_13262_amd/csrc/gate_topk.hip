@@ -495,8 +495,8 @@ static void launch_wide_mt(const moe_desc_t& D, const T* X, const T* WgT, const 
     constexpr int S = 512 / (int)sizeof(T) + 16 / (int)sizeof(T);
     constexpr int slab = (16 * MT + 64) * S * (int)sizeof(T), merge = 4 * kMaxK * 64 * (8 + 4);
     constexpr int smem = slab > merge ? slab : merge;      // the logit patch (16*MT x 64 doubles) is smaller than the slabs
-    auto kern = gate_mfma_wide_kernel<T, MT>;
-    if (!allow_dynamic_lds(kern, smem)) return;
+    constexpr auto kern = gate_mfma_wide_kernel<T, MT>;
+    if (!allow_dynamic_lds<kern>(smem)) return;
     hipLaunchKernelGGL(kern, dim3((unsigned)((D.N + 16 * MT - 1) / (16 * MT))), dim3(256), smem, st, X, WgT, bg, D.N, D.d,
                        D.E, D.k, idx, w, logits);
 }

@@ -1007,8 +1007,8 @@ void launch_cfg(const GemmArgs& a, hipStream_t st)
 {
     using C = Cfg<KIND, WM, WN, TM, TN, STAGES, BK>;
     static_assert((size_t)C::BM * C::BN * 4 <= kPartialBytesPerWg, "partial-sum buffer");
-    auto kern = ggemm_sk_kernel<KIND, WM, WN, TM, TN, STAGES, BK>;
-    if (!allow_dynamic_lds(kern, C::SMEM)) return;
+    constexpr auto kern = ggemm_sk_kernel<KIND, WM, WN, TM, TN, STAGES, BK>;
+    if (!allow_dynamic_lds<kern>(C::SMEM)) return;
     const int wgs = persistent_wgs();
     if (wgs < 8) return;
     const int ntn = (a.Nout + C::BN - 1) / C::BN;
@@ -1026,8 +1026,8 @@ void launch_cls_cfg(const GemmArgs& a, hipStream_t st)
     using C2 = CfgWide<KIND>;
     static_assert((size_t)C2::BM * C2::BN * 4 <= kPartialBytesPerWg, "partial-sum buffer");
     constexpr int SMEM = std::max({C1::SMEM, C2::SMEM, DEEP ? CfgDeep<KIND>::SMEM : 0});
-    auto kern = ggemm_cls_kernel<KIND, STAGES, BK, DEEP>;
-    if (!allow_dynamic_lds(kern, SMEM)) return;
+    constexpr auto kern = ggemm_cls_kernel<KIND, STAGES, BK, DEEP>;
+    if (!allow_dynamic_lds<kern>(SMEM)) return;
     const int wgs = persistent_wgs();
     if (wgs < 8) return;
     hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(512), SMEM, st, a, (a.Nout + C1::BN - 1) / C1::BN,
@@ -1072,8 +1072,8 @@ void launch_pair_cfg(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
     using C1s = CfgWide<KIND>;
     using C2 = Cfg<kColsT, 2, 4, 4, 2, 4, 32>;
     constexpr int SMEM = std::max({C1::SMEM, CLASSES ? C1s::SMEM : 0, CLASSES && DEEP ? CfgDeep<KIND>::SMEM : 0, C2::SMEM});
-    auto kern = ggemm_pair_kernel<KIND, CLASSES, DEEP>;
-    if (!allow_dynamic_lds(kern, SMEM)) return;
+    constexpr auto kern = ggemm_pair_kernel<KIND, CLASSES, DEEP>;
+    if (!allow_dynamic_lds<kern>(SMEM)) return;
     const int wgs = persistent_wgs();
     if (wgs < 8) return;
     GemmArgs r = rows, c = cols;

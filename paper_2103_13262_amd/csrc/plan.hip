@@ -284,7 +284,7 @@ void launch_plan(const moe_desc_t& D, const WsLayout& L, const int32_t* topk_idx
     const int chunk = (int)plan_chunk(M), Ep = (D.E + 3) & ~3;
     const bool own = M <= kOwnCounts;
     if (!own) hipLaunchKernelGGL(plan_hist, dim3(L.nb), dim3(kThreads), 0, st, topk_idx, M, D.E, chunk, hist);
-    if (!allow_dynamic_lds(plan_place, (2 + kWaves) * kMaxE * (int)sizeof(int))) return;
+    if (!allow_dynamic_lds<plan_place>((2 + kWaves) * kMaxE * (int)sizeof(int))) return;
     hipLaunchKernelGGL(plan_place, dim3(L.nb + 1), dim3(kThreads), (2 + kWaves) * Ep * sizeof(int), st, topk_idx,
                        own ? (const int32_t*)nullptr : hist, L.nb, chunk, D.E, nbits, M, counts, offsets, (int32_t*)(ws + L.tileP),
                        (int32_t*)(ws + L.order), (int32_t*)(ws + L.cls), (int32_t*)(ws + L.zeros), pos, perm);
