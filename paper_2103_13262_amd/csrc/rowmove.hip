@@ -13,9 +13,9 @@ namespace moe {
 template <typename T> struct Vec;
 template <> struct Vec<unsigned short> {
     static constexpr int N = 8;
-    static __device__ __forceinline__ void load(const void* base, size_t chunk, float* f)
+    static __device__ __forceinline__ void load(const void* base, size_t chunk, float* f) { widen(((const uint4*)base)[chunk], f); }
+    static __device__ __forceinline__ void widen(const uint4& v, float* f)
     {
-        const uint4 v = ((const uint4*)base)[chunk];
         const unsigned w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -33,10 +33,10 @@ template <> struct Vec<unsigned short> {
 };
 template <> struct Vec<float> {
     static constexpr int N = 4;
-    static __device__ __forceinline__ void load(const void* base, size_t chunk, float* f)
+    static __device__ __forceinline__ void load(const void* base, size_t chunk, float* f) { widen(((const uint4*)base)[chunk], f); }
+    static __device__ __forceinline__ void widen(const uint4& v, float* f)
     {
-        const float4 v = ((const float4*)base)[chunk];
-        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+        f[0] = __uint_as_float(v.x); f[1] = __uint_as_float(v.y); f[2] = __uint_as_float(v.z); f[3] = __uint_as_float(v.w);
     }
     static __device__ __forceinline__ void store(void* base, size_t chunk, const float* f)
     {
@@ -278,20 +278,45 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
     __shared__ float s_acc[7][64][V];
     const int piece = blockIdx.x;
     const int pieces = P64[E];
-    const Segment sg = find_segment(P64, E, piece, counts, offsets);   // (a piece past the last finds the last expert)
-    if (piece >= pieces) return;          // uniform over the workgroup
+    Segment sg;
+    if (E <= 256) {
+        sg = find_segment(P64, E, piece, counts, offsets);   // (a piece past the last finds the last expert)
+        if (piece >= pieces) return;      // uniform over the workgroup
+    } else {
+        // Beyond 256 experts find_segment takes several round trips, which the many pieces past the last would wait for too:
+        // those leave first, and the search is one of halves over scalar loads.
+        if (piece >= pieces) return;
+        int lo = 0, hi = E;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (P64[mid] <= piece) lo = mid; else hi = mid;
+        }
+        sg = Segment{lo, P64[lo], P64[lo + 1], counts[lo], offsets[lo]};
+    }
     const int r0 = sg.offset + (piece - sg.first) * 64;
     const int r1 = min(r0 + 64, sg.offset + sg.count);
     const int ct = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int c = blockIdx.y * 64 + ct;
     const bool active = c < cpr;
-    // The rows are asked for before the weights, whose two dependent loads and barrier then pass under them.
-    // (No branch around a load: it would wait for each before the next.  Rows past the end of the piece load its last row,
-    // columns past the last the last; what they loaded is not used.)  A step of 1000 tokens, d 768, h 3072, 8 experts with
-    // biases, whose gradients are such sums too: 347 -> 339 us.
-    float v[8][V];
+    // The rows are asked for before the weights, whose two dependent loads and barrier then pass under them, and are widened
+    // behind the barrier (widening waits for them).  A wavefront asks for its eight rows with no branch between the loads, rows
+    // past the end of the piece being its last row once more, for two where it has no more, and for none where it has
+    // none: an expert with few rows has one piece with a row or two in the first wavefront.  Column sums of bf16 rows
+    // 3072 wide: 100 experts with 64 rows on average 11.2 us (rows behind the weights, each under a branch of its own: 13.6; widened as
+    // they arrive: 11.6); 854 experts with one row on average 20.2 us (20.8; with eight loads in every wavefront and the longer
+    // search in front of the exit: 33.7).
+    uint4 v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) Vec<T>::load(Xs, (size_t)min(r0 + q * 8 + i, r1 - 1) * cpr + min(c, cpr - 1), v[i]);
+    for (int i = 0; i < 8; ++i) v[i] = make_uint4(0, 0, 0, 0);
+    const uint4* const rows = (const uint4*)Xs + min(c, cpr - 1);
+    const int first = __builtin_amdgcn_readfirstlane(r0 + q * 8), left = r1 - first;
+    if (left > 2) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = rows[(size_t)min(first + i, r1 - 1) * cpr];
+    } else if (left > 0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) v[i] = rows[(size_t)min(first + i, r1 - 1) * cpr];
+    }
     // (dl == nullptr: plain column sums of the segment, every row with weight 1: the expert-bias gradients)
     if (threadIdx.x < 64) s_g[threadIdx.x] = r0 + (int)threadIdx.x < r1 ? (dl ? dl[perm[r0 + threadIdx.x]] : 1.f) : 0.f;
     __syncthreads();
@@ -301,9 +326,10 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float g = s_g[q * 8 + i];
-        const bool row = r0 + q * 8 + i < r1;
+        float x[V];
+        Vec<T>::widen(v[i], x);
 #pragma unroll
-        for (int u = 0; u < V; ++u) acc[u] = fmaf(g, row ? v[i][u] : 0.f, acc[u]);
+        for (int u = 0; u < V; ++u) acc[u] = fmaf(g, i < left ? x[u] : 0.f, acc[u]);
     }
     if (q > 0) {
 #pragma unroll
