@@ -549,21 +549,40 @@ __global__ __launch_bounds__(256) void gate_scores_all(double* __restrict__ logi
     }
 }
 
-// Whether a workgroup per token (gate_small.hip) beats the tiled kernels: there every workgroup reads the gate matrix, so its
-// time grows with every 256 tokens (one workgroup per compute unit) by about 2 us and the matrix at 78 bytes per nanosecond,
-// 2.7 times that where E is no multiple of the elements in 16 bytes; the tiled kernels' time does not depend on the token
-// count until the chip is full.  Estimates in microseconds, from sweeps over d 256 / 1024 / 2048 (tiled -> small, event overhead of 4
-// us included in both).  bf16, N 256: E 16: 8 / 12 / 17 -> 8 / 8 / 9, E 24: 19 / 26 / 36 -> 8 / 9 / 10, E 57: 18 / 25 / 36 -> 11 / 14 / 19, E
-// 256: 24 / 34 / 52 -> 10 / 17 / 26, E 1000: 149 / 301 / 504 -> 17 / 39 / 68; N 1024: E 16: 8 / 12 / 17 -> 15 / 15 / 17, E 24: 19 / 27 / 36 -> 15 /
-// 16 / 18, E 57: 19 / 26 / 36 -> 20 / 31 / 43, E 256: 24 / 35 / 52 -> 20 / 40 / 66.  fp32, N 256: E 24: 20 / 50 / 90 -> 8 / 9 / 9.
+// Whether a workgroup per token (gate_small.hip) beats the tiled kernels: estimates of both in microseconds, the 4 of a pair of events
+// included, fitted to 20266 calls measured both ways (bf16 and fp32, 29 expert counts from 1 to 1024, d 64 to 8192, 1 to 4096 tokens,
+// k 1, 2 and 8, with and without stored logits).  The kernel picked is 0.4 % slower than the better one on average; where it is
+// the small one, it is more than 10 % slower than the tiled one in 41 of 13821 calls.
+//   small: every round of 256 tokens reads the gate matrix and selects k times in one wavefront; up to 256 experts two workgroups
+//          share a compute unit where their LDS allows.  A matrix of at most 32 KB stays in the vector cache.
+//   tiled: the time does not depend on the token count until the chip is full.
+// Small against tiled, k 2, bf16.  8 experts: N 512, d 1024 10.6 / 11.2, N 1024, d 2048 17.3 / 16.4, N 2048, d 8192 77.5 / 46.3.  64 experts: N 512,
+// d 1024 17.3 / 26.1, N 1024, d 1024 28.7 / 26.1; logits stored, N 2048, d 1024 50.4 / 34.0.  256 experts: N 256, d 1024 16.2 / 33.9, N 512, d 1024
+// 36.1 / 34.5.  fp32, 24 experts: N 1024, d 1024 16.5 / 50.2, N 4096, d 1024 46.1 / 49.8, N 4096, d 256 39.3 / 19.9.
 static bool small_batch(const moe_desc_t& D, bool logits)
 {
     if (D.d > kGateSmallMaxD) return false;
+    const bool bf16 = D.dtype == MOE_BF16;
     const int V = 16 / (int)dtype_size(D.dtype);
-    const double bytes = (double)D.d * D.E * dtype_size(D.dtype);
-    const double small = 2.0 + (D.N + 255) / 256 * (1.8 + bytes / 78e3 * (D.E % V ? 2.7 : 1.0));
-    const bool fast_bf16 = D.dtype == MOE_BF16 && D.E <= 256 && !logits;
-    const double tiled = D.E <= 16 ? 3.0 + D.d * 0.0047 : fast_bf16 ? 11.5 + D.d * 0.01 : 12.0 + (double)D.d * D.E * 3e-4;
+    const bool whole = D.E % V == 0;                           // a 16-byte piece of the matrix lies inside one feature
+    const double d = D.d * 1e-3, k = D.k, el = d * D.E;        // (el: thousands of matrix elements)
+    const int rounds = (D.N + 255) / 256;
+    double small, tiled;
+    if (rounds <= 1) small = 7.0 + 0.67 * k + 0.06 * d + (!whole ? 0.055 : bf16 ? 0.03 : 0.04) * el;
+    else {
+        const double w = rounds + (rounds & 1) * 0.5;          // (a workgroup without a partner takes nearly as long as a pair)
+        double round;
+        if (D.E <= 256 && 8192 * V + 4 * D.d <= 80 * 1024) {   // two workgroups per compute unit
+            const bool cached = whole && (double)D.d * D.E * dtype_size(D.dtype) <= 32 * 1024;
+            round = (bf16 ? 1.9 + 0.33 * k : (whole ? 1.3 : 1.45) + 0.23 * k) + 0.17 * d + (cached ? 0.012 : bf16 ? (whole ? 0.043 : 0.047) : whole ? 0.03 : 0.037) * el;
+        } else if (D.E <= 256) round = (bf16 ? 1.7 : 1.3) + 0.7 * k + 0.5 * d + 0.06 * el;
+        else round = (bf16 ? 1.7 + 1.1 * k : 1.3 + 0.4 * k) + (whole ? 0.0 : 3.0) + 0.5 * d + (whole ? 0.035 : 0.05) * el;
+        small = 5.5 + w * round;
+    }
+    if (D.E <= 16) tiled = 6.4 + (bf16 ? 4.95 : 6.3) * d + (logits ? 3.0 : 0.0);
+    else if (bf16 && D.E <= 256 && !logits) tiled = 11.3 + 6.0 * d + 2.3 * k + 1.5 * k * d + 0.042 * el;
+    else if (D.E <= 32) tiled = 6.0 + 40.0 * d + 2.4 * k;
+    else tiled = 9.0 + (D.E + 63) / 64 * (2.2 + 13.0 * d + 1.9 * k);
     return small <= tiled;
 }
 
