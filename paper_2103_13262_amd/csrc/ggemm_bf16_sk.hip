@@ -54,6 +54,7 @@
 #include <vector>
 
 #include "common.h"
+#include "last_pieces.h"
 
 namespace moe {
 namespace sk {
@@ -930,17 +931,17 @@ __device__ __forceinline__ void ggemm_classes(const GemmArgs& g, int ntn_big, in
     if (g.whole_tiles) {
         // Followed by another product in the same launch: whole tiles only.  The big tiles go round the workgroups
         // from the first on; the last pieces, in 128 x 256 tiles (a 128 x 512 tile of a deep reduction would be the
-        // longest item of the launch), start behind the big tiles' last round: up to two of them stay with each of the
-        // workgroups that got no tile of that round (a big tile moves 4/3 of what a last piece's moves), more go round
-        // all workgroups from there on.  (Left to those workgroups alone, whatever their number, a load whose big
-        // tiles nearly filled the last round gave two workgroups of 32 all last pieces: dXs and dW1 of 16384 rows in
-        // 64 experts, Zipf 1.2, d 1024, h 4096, took 1123 us with one seed and 415 with others.)
+        // longest item of the launch), start behind the big tiles' last round: few of them stay with the workgroups that
+        // got no tile of that round, more go round all workgroups from there on (last_pieces.h).  (Left to those
+        // workgroups alone, whatever their number, a load whose big tiles nearly filled the last round gave two workgroups
+        // of 32 all last pieces: dXs and dW1 of 16384 rows in 64 experts, Zipf 1.2, d 1024, h 4096, took 1123 us with one
+        // seed and 415 with others.)
         ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big);
         if (Ts == 0) return;
         __syncthreads();
-        const int after = (int)(((Tb >> 3) + ((Tb & 7) ? 1 : 0)) % W);
-        const bool behind = Ts <= 16L * (W - after);
-        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2>(g, 0, ntn_big, after, behind ? W - after : 0);
+        const int after = first_free_workgroup(Tb, W);
+        const bool stay = last_pieces_stay((long)g.cls[kClsPSmall * (g.E + 1) + g.E] * ntn_big, after, W);   // (both kinds of tile are 256 wide)
+        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2>(g, 0, ntn_big, after, stay ? W - after : 0);
         return;
     }
     if (Ts == 0) { ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big); return; }
