@@ -1,0 +1,35 @@
+"""The error of the gate-matrix gradient's sums over many tokens with scores over all experts: sums by blocks of 32 tokens inside a
+chunk, not one running sum over the chunk."""
+import pytest
+
+from harness import GpuRun
+from paper_2103_13262_amd import binding as B
+from paper_2103_13262_amd.synth import Workload, make_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,E", [(20000, 2), (32768, 2)])
+def test_dense_gate_sums(N, E):
+    print(f"[case] N {N}", flush=True)
+    w = Workload("sums", N, 1024, 32, E, 1, "f32", 0.0, 820, 0.0, True)      # (chunks of 512 tokens)
+    inputs = make_inputs(w)
+    run = GpuRun(w, inputs).run()
+    torch = run.torch
+    off, n = B.moe_workspace_region(run.desc, "dl")
+    dl = run.workspace[off:off + n].view(torch.float32)[:N].double()
+    # With two experts the unselected logit's gradient is the selected one's with the other sign, so the reference is a sum of the path's
+    # own gradients and what is left is the error of the sums (and one rounding of 2^-24 per term, which averages out).
+    R = torch.zeros((N, E), dtype=torch.float64, device=run.device)
+    idx = run.topk_idx[:, 0].long()
+    R[torch.arange(N, device=run.device), idx] = dl
+    R[torch.arange(N, device=run.device), 1 - idx] = -dl
+    ref = run.X.double().T @ R
+    err = float((run.dWg.double() - ref).norm() / ref.norm())
+    # Terms of random sign: every step of a running sum rounds by c = 0.42 * 2^-24 of the sum it has reached (uniform rounding errors,
+    # averaged over the binade), whose square grows as the number of terms, so s steps leave c sqrt(s / 2) of the result.  32 tokens in a
+    # block, 16 blocks in a chunk, 8 chunks at a time and up to 8 times that: c sqrt((32 + 16 + 8 + 8) / 2) = 1.4e-7, and half as
+    # much again.  (One running sum over a chunk's 512 tokens and one over 64 chunks: 4.2e-7.)
+    print(f"relative error {err:.3e}", flush=True)
+    assert err <= 2.1e-7
+
