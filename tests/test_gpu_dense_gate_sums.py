@@ -1,5 +1,5 @@
-"""The error of the gate-matrix gradient's sums over many tokens with scores over all experts: sums by blocks of 32 tokens inside a
-chunk, not one running sum over the chunk."""
+"""The error of the gate gradients' sums with scores over all experts: over many tokens (dWg) and over many experts (dX), by blocks of 32
+and not in one running sum."""
 import pytest
 
 from harness import GpuRun
@@ -33,3 +33,32 @@ def test_dense_gate_sums(N, E):
     print(f"relative error {err:.3e}", flush=True)
     assert err <= 2.1e-7
 
+
+
+@pytest.mark.parametrize("E", [1000, 1024])
+def test_dense_dx_sums(E):
+    print(f"[case] E {E}", flush=True)
+    w = Workload("sums", 700, 256, 32, E, 1, "f32", 0.0, 821, 0.0, True)
+    inputs = make_inputs(w)
+    inputs["Wg"] = inputs["Wg"] * 10                       # (so that the gate's share of dX is the larger one)
+    run = GpuRun(w, inputs).run()
+    torch = run.torch
+
+    def region(name, *shape):
+        off, n = B.moe_workspace_region(run.desc, name)
+        return run.workspace[off:off + n].view(torch.float32).view(*shape).double()
+
+    # The reference is made of the path's own gradients: a token's selected logit has dl = w (dw - s) with s = w dw, so s = dl / (1 - w),
+    # and the other logits have -p_e s with p in fp64.
+    dl, dXs = region("dl", w.N), region("dXs", w.N, w.d)
+    p = torch.softmax(run.X.double() @ run.Wg.double(), 1)
+    t, idx = torch.arange(w.N, device=run.device), run.topk_idx[:, 0].long()
+    R = -p * (dl / (1 - p[t, idx]))[:, None]
+    R[t, idx] = dl
+    ref = dXs[run.pos[:w.N].long()] + R @ run.Wg.double().T
+    err = float((run.dX.double() - ref).norm() / ref.norm())
+    # As above: a running sum that holds the selected expert's term rounds at its size at every further step, on average half of them:
+    # c sqrt(32 / 2 + 32 / 2) = 1.4e-7 with 32 experts in a block and 32 blocks, and up to 2^-24 more that all terms of a token share
+    # (the rounding of dl, from which s is taken back): 2.0e-7.  (One running sum: c sqrt(1024 / 2) = 5.7e-7.)
+    print(f"relative error {err:.3e}", flush=True)
+    assert err <= 2.0e-7
