@@ -284,7 +284,8 @@ __global__ __launch_bounds__(1024) void balance_final(const double* __restrict__
     s_part[threadIdx.x] = p;
     __syncthreads();
     if (q == 0 && e < E) {
-        for (int g = 1; g < nq; ++g) p += s_part[g * width + e];
+        // (groups past the chunks hold zeros: with two experts there are 512, 5 us of additions in a row)
+        for (int g = 1; g < min(nq, nch); ++g) p += s_part[g * width + e];
         p = N > 0 ? p / (double)N : 0.0;
         const double f = N > 0 ? (double)counts[e] / ((double)N * k) : 0.0;
         if (fraction) fraction[e] = (float)f;

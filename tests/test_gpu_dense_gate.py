@@ -22,7 +22,7 @@ def test_dense_gate_gradient(w):
     _full_check(w)
 
 
-@pytest.mark.parametrize("N,E", [(1, 3), (257, 70), (600, 1024), (3000, 2)])
+@pytest.mark.parametrize("N,E", [(1, 3), (257, 70), (600, 1024), (3000, 2), (9000, 1), (9000, 40), (9000, 600)])
 def test_balance_sums(N, E):
     import torch
 
