@@ -1,7 +1,8 @@
 """Routing (gate, selection, counting, placing) at the sizes where its kernels change over, bit for bit against the oracle.
 
 The gate takes a workgroup per token for small batches (pieces of 16 bytes that hold one feature or several; one or more pieces
-per expert row; up to 1024 experts; two workgroups per compute unit above 256 tokens).  The plan counts the assignments itself up
+per expert row; up to 1024 experts; two workgroups per compute unit above 256 tokens); where it stops doing so is
+test_gpu_gate_paths.py's subject.  The plan counts the assignments itself up
 to 8192, from chunk histograms above, orders up to 256 experts by counting and more by sorting, and makes its chunks longer than 1024
 assignments above 262144.  Inputs are small integers with duplicated gate columns and a zero row: exact ties everywhere.
 """
