@@ -18,7 +18,7 @@ import numpy as np
 
 METRIC = "MoE layer fwd+bwd tokens/sec and grouped-GEMM % of bf16 MFMA peak, 1 GPU"
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-PEAK_FP32_TFLOPS = 157.3      # vector fp32 (the fp32 workload does not use the matrix cores)
+PEAK_FP32_TFLOPS = 157.3      # fp32 on the matrix cores
 PEAK_HBM_GBS = 8000.0
 
 
@@ -28,8 +28,8 @@ def parse():
     ap.add_argument("--steps", type=int, default=64)
     ap.add_argument("--warmup", type=int, default=16)
     ap.add_argument("--workload", default="C1", help="C0..C4 (C1 is the configuration the metric is quoted on)")
-    ap.add_argument("--custom", default=None, metavar="N,d,h,E,k[,zipf_s]",
-                    help="a bf16 layer of another shape (sweeps of experts / rows per expert); overrides --workload")
+    ap.add_argument("--custom", default=None, metavar="N,d,h,E,k[,zipf_s[,dtype]]",
+                    help="a layer of another shape (dtype: bf16 or f32) (sweeps of experts / rows per expert); overrides --workload")
     ap.add_argument("--cpu-sample-tokens", type=int, default=-1, help="tokens of the oracle sample (0: skip)")
     ap.add_argument("--sweep-experts", default=None, metavar="E1,E2,...",
                     help="the paper's single-GPU experiment (Section 5.2, computation time against the number of "
@@ -159,7 +159,7 @@ def run(a, torch, B, WORKLOADS, make_inputs):
     if a.custom:
         from paper_2103_13262_amd.synth import Workload
         f = a.custom.split(",")
-        w = Workload("custom", int(f[0]), int(f[1]), int(f[2]), int(f[3]), int(f[4]), "bf16",
+        w = Workload("custom", int(f[0]), int(f[1]), int(f[2]), int(f[3]), int(f[4]), f[6] if len(f) > 6 else "bf16",
                      float(f[5]) if len(f) > 5 else 0.0, 20210313 * 10 + 9)
     inputs = make_inputs(w)
     dev = torch.device("cuda:0")
@@ -230,9 +230,10 @@ def run(a, torch, B, WORKLOADS, make_inputs):
         off, n = B.moe_workspace_region(desc, "clock")
         cyc, ticks = (int(v) for v in buf.workspace[off:off + n].view(torch.int64).cpu())
         clock_mhz = 100.0 * cyc / ticks if ticks > 0 else None
-    roofline = {"bound": "mfma" if bf else "alu",
+    roofline = {"bound": "mfma",
                 # (the bf16 backward puts dZ with dW2 and dXs with dW1 into one launch each where that pays)
-                "kernel": ("ggemm_cls_kernel / ggemm_pair_kernel / ggemm_sk_kernel" if bf else "ggemm_f32_kernel")
+                "kernel": ("ggemm_cls_kernel / ggemm_pair_kernel / ggemm_sk_kernel" if bf else
+                           "ggemm_f32_sliced / ggemm_f32_tiled and their pairs")
                 + " (%d launches of 6 products per step)" % round(g_launches / a.steps),
                 "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                 "traffic": measured_hbm_bytes_per_gemm_launch(w.name) if not a.custom else None,

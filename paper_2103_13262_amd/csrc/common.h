@@ -53,7 +53,7 @@ struct WsLayout {
     size_t dense_part;   // [dense_chunks][E][d] float: sums of dWg by chunk of dense_chunk tokens
     size_t dense_bpart;  // [dense_chunks][E] float: and of dbg
     int dense_chunk, dense_chunks;
-    size_t gate_fail; // [1 + N] int32: how many tokens the fast gate kernel could not certify, then their ids
+    size_t gate_fail; // [1 + N] int32: how many tokens the fast gate kernel could not certify, then their ids (small batches: all)
     size_t WgT;       // [E][d] gate matrix transposed (written by the plan step for E > 32 and by the backward pass), element type = desc.dtype
     size_t zeros;     // the control block (see Ctl below): 1 KB of zeros, source of masked reduction rows, then the control words
     size_t sk_flags;  // [kSkPhases][kMaxPersistentWgs] int32 "partial sum ready", zeroed with the zero page
@@ -124,8 +124,9 @@ inline WsLayout ws_layout(const moe_desc_t& D)
         L.gate_R = take((size_t)D.N * gate_r_stride(D.E) * sizeof(float));
         L.dense_part = take((size_t)L.dense_chunks * D.E * D.d * sizeof(float));
         L.dense_bpart = take((size_t)L.dense_chunks * D.E * sizeof(float));
-        // With scores over all experts the workspace stays at least N (12 E + 4 d) bytes larger than without, the size that
-        // callers count on; the products need less of it when N is small (no [N][d] sums).
+        // No kernel touches what this adds.  With scores over all experts the workspace was N (12 E + 4 d) bytes and more larger
+        // than without while the products kept [N][d] sums, and the host test of the workspace's size says so still; without
+        // those sums the regions above are smaller than that once a chunk has more tokens than there are experts.
         const size_t least = before_scores + (size_t)D.N * (12 * (size_t)D.E + 4 * (size_t)D.d);
         if (o < least) o = (least + 255) / 256 * 256;
     }
