@@ -252,7 +252,7 @@ __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const 
 
 // ---- dWg[:,e] = sum over rows r of segment e of dl[perm[r]] * Xs[r,:]  (fixed order) ----------
 // Every expert's segment is cut into pieces of 64 rows (the 64-row tile table of the plan step), so the
-// work per workgroup is the same however skewed the load is.  grid (max pieces, ceil(cpr/64)); each thread
+// work per workgroup is the same however skewed the load is.  grid: piece_grid; each thread
 // owns one 16-byte column piece and walks the rows of its piece; a second kernel adds an expert's pieces
 // in ascending order.
 template <typename T>
@@ -265,8 +265,9 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
     // Rides along (WgT != nullptr): WgT[e][i] = Wg[i][e], which lets the kernel that follows the reduction read a
     // gate column as contiguous 16-byte pieces; spread over all workgroups of the launch.
     if (WgT) {
-        const long nel = (long)d * E, nthr = (long)gridDim.x * gridDim.y * 512;
-        for (long i = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 512 + threadIdx.x; i < nel; i += nthr) {
+        const long nel = (long)d * E, nthr = (long)gridDim.x * gridDim.y * gridDim.z * 512;
+        const long block = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        for (long i = block * 512 + threadIdx.x; i < nel; i += nthr) {
             const int ee = (int)(i / d), row = (int)(i - (long)ee * d);
             WgT[i] = Wg[(size_t)row * E + ee];
         }
@@ -276,7 +277,11 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
     constexpr int V = Vec<T>::N;
     __shared__ float s_g[64];
     __shared__ float s_acc[7][64][V];
-    const int piece = blockIdx.x;
+    // The column blocks of a piece are neighbours, so that rows of several KB are read while their pages of memory are open (gate
+    // backward of 32768 tokens, d 2048, 32 experts, top-2, bf16: 149 us with a launch's pieces of the first column block in front
+    // of those of the second, 137 so).  Two of them change places every four pieces: otherwise every other XCD (workgroup number
+    // modulo 8) would get all the second ones, which may be mostly empty.
+    const int piece = (int)(blockIdx.z * gridDim.y + blockIdx.y), col = gridDim.x == 2 ? (int)blockIdx.x ^ (piece >> 2 & 1) : (int)blockIdx.x;
     const int pieces = P64[E];
     Segment sg;
     if (E <= 256) {
@@ -296,7 +301,7 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
     const int r0 = sg.offset + (piece - sg.first) * 64;
     const int r1 = min(r0 + 64, sg.offset + sg.count);
     const int ct = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int c = blockIdx.y * 64 + ct;
+    const int c = col * 64 + ct;
     const bool active = c < cpr;
     // The rows are asked for before the weights, whose two dependent loads and barrier then pass under them, and are widened
     // behind the barrier (widening waits for them).  A wavefront asks for its eight rows with no branch between the loads, rows
@@ -474,6 +479,13 @@ void launch_dcombine(const moe_desc_t& D, const void* dY, const void* Ys, const 
     });
 }
 
+// grid of dwg_partial: column blocks, then pieces (over two dimensions: one holds 65535 workgroups)
+static dim3 piece_grid(long pieces, int cpr)
+{
+    const unsigned y = (unsigned)(pieces < 32768 ? pieces : 32768);
+    return dim3((unsigned)((cpr + 63) / 64), y, (unsigned)((pieces + y - 1) / y));
+}
+
 void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
                      const float* dl, const int32_t* topk_idx, const int32_t* pos, const int32_t* perm,
                      const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws, hipStream_t st)
@@ -482,7 +494,7 @@ void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, con
     float* part = (float*)(ws + L.dwg_part);
     float* bpart = (float*)(ws + L.dbg_part);
     const int32_t* P64 = (const int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
-    const dim3 pg((unsigned)L.dwg_pieces, (cpr + 63) / 64);
+    const dim3 pg = piece_grid(L.dwg_pieces, cpr);
     const unsigned xg = grid_for((long)D.N * cpr);
     void* WgT = ws + L.WgT;
     const int fgx = (D.d + 255) / 256;
@@ -510,7 +522,7 @@ void launch_segment_sums(const moe_desc_t& D, const WsLayout& L, const void* src
     const int cpr = (int)((size_t)width * dtype_size(D.dtype) / 16);
     float* part = (float*)(ws + L.bias_part);
     const int32_t* P64 = (const int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
-    const dim3 pg((unsigned)L.dwg_pieces, (cpr + 63) / 64);
+    const dim3 pg = piece_grid(L.dwg_pieces, cpr);
     if (D.dtype == MOE_BF16)
         hipLaunchKernelGGL(dwg_partial<unsigned short>, pg, dim3(512), 0, st, src, (const float*)nullptr,
                            (const int32_t*)nullptr, counts, offsets, P64, part, (float*)nullptr, D.E, width, cpr,

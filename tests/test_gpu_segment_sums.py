@@ -1,6 +1,7 @@
 """Sums over an expert's rows (expert-bias gradients, gate-matrix gradient) where the kernel changes over: a wavefront of eight rows
 that has none, one, two, three and all of them, a piece of 64 rows with one more row, experts without rows, and both searches for
-a piece's expert (up to 256 experts and more).  All numbers are small integers, so every sum is exact."""
+a piece's expert (up to 256 experts and more), one, two and several column blocks (whose order changes), and more pieces than one grid
+dimension holds.  All numbers are small integers, so every sum is exact."""
 import pytest
 
 from paper_2103_13262_amd import binding as B
@@ -11,7 +12,7 @@ EDGES = [0, 1, 2, 3, 8, 9, 10, 11, 0, 63, 64, 65, 66, 67, 128, 130]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("E,d,h", [(16, 32, 1056), (256, 256, 32), (257, 288, 544), (700, 704, 32)])
+@pytest.mark.parametrize("E,d,h", [(16, 32, 1056), (256, 256, 32), (257, 288, 544), (700, 704, 32), (16, 2080, 640), (4, 32, 32)])
 def test_sums_over_segments(E, d, h, dtype):
     import torch
 
@@ -20,7 +21,7 @@ def test_sums_over_segments(E, d, h, dtype):
     act = torch.bfloat16 if dtype == "bf16" else torch.float32
     g = torch.Generator(device=dev)
     g.manual_seed(E + h)
-    rows = EDGES if E == 16 else [(0, 1, 0, 2, 11, 1, 0, 3)[e % 8] + (130 if e == E - 1 else 0) for e in range(E)]
+    rows = EDGES if E == 16 else [2100000, 0, 130, 7] if E == 4 else [(0, 1, 0, 2, 11, 1, 0, 3)[e % 8] + (130 if e == E - 1 else 0) for e in range(E)]
     N = sum(rows)
     expert = torch.repeat_interleave(torch.arange(E, device=dev), torch.tensor(rows, device=dev))[torch.randperm(N, generator=g, device=dev)]
     X, Wg = torch.zeros((N, d), dtype=act, device=dev), torch.zeros((d, E), dtype=act, device=dev)
