@@ -12,8 +12,8 @@
 //            the matrix instructions' registers (a wavefront shares nothing, so LDS would buy nothing and a loop without
 //            barriers keeps 16 wavefronts' loads in flight); the slices' sums meet in LDS, added in ascending order.
 // Measured (training step; before: one 64 x 64 x 16 vector-FMA kernel per product, its loads not pipelined): N 256, d 64,
-// h 128, 4 experts top-2: 172 -> 48 us, a product 17-31 -> 5-6 us; N 4000, d = h = 64, 2 experts: 1672 -> 123 us; N 4096,
-// d 512, h 1024, 16 experts: 1436 -> 600 us, 92 TFLOP/s in the products (the tiled form; 558 us in a kernel trace).  The line between the forms: N 500,
+// h 128, 4 experts top-2: 172 -> 48 us (42 with the plan in one launch), a product 17-31 -> 5-6 us; N 4000, d = h = 64, 2 experts: 1672 -> 123 us; N 4096,
+// d 512, h 1024, 16 experts: 1436 -> 600 us, 93 TFLOP/s in the products (the tiled form; 552 us in a kernel trace).  The line between the forms: N 500,
 // d 96, h 992, 5 experts (20 tiles), second layer: 24 us with its tiles cut over four groups of a tiled workgroup, 12 us
 // sliced; N 2048, d 256, h 512, 8 experts (288 tiles): 31 against 29 us; above 512 tiles every compute unit has two
 // tiled workgroups to overlap and the sliced form only moves more data per product.
