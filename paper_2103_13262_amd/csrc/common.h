@@ -233,6 +233,10 @@ struct GemmArgs {
     int out_f32;      // kColsT: C holds float (else the activation type)
     int accumulate;   // kColsT
 };
+// bf16 products: whether a lane's place in a block of an operand fits 32 bits (setup_offsets): a block spans at most 256 rows of the operand, so
+// it does for all but rows of millions of values (2^22: 256 of them are 2 GB).  (Gathered rows lie anywhere in X: moe_forward
+// gathers only from less than 4 GB.)
+inline bool offsets_fit(const GemmArgs& a) { return a.K < (1 << 22) && a.Nout < (1 << 22); }
 // Points the control-block fields of a GemmArgs at a workspace's control block.
 inline void set_control(GemmArgs& a, char* ws, const WsLayout& L)
 {

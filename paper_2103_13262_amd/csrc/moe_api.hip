@@ -319,6 +319,10 @@ moe_status_t moe_forward(const moe_desc_t* desc, const moe_plan_t* plan, const v
 
     a.kind = kRowsNN_GeLU;  // Z = Xs W1[e],  H = GeLU(Z)
     a.A = X; a.a_gather = plan->perm; a.a_gather_div = D.k;
+    if (D.dtype == MOE_BF16 && ((size_t)D.N * D.d * 2) >> 32) {   // X of 4 GB and more: the loads' 32-bit offsets do not reach all rows
+        launch_scatter(D, X, plan->pos, ws + L.Xs, st);
+        a.A = ws + L.Xs; a.a_gather = nullptr;
+    }
     a.B = W1; a.C = ws + L.Z; a.C2 = ws + L.H; a.K = D.d; a.Nout = D.h; a.bias = b1;
     { ScopedTimer tm(S_FC1, st); run_gemm(D, a, st); }
     if ((s = check_launch("expert layer 1")) != MOE_OK) return s;
