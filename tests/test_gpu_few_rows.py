@@ -1,0 +1,78 @@
+"""Forward products with few rows per expert (tiles of 32, 64 and 128 rows by 128 columns, reductions cut into slices): the products at the
+edges of their tiles, against torch in fp32."""
+import pytest
+
+from paper_2103_13262_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # d, h, rows per expert, top-1, biases, seed
+    (256, 512, [1], True, False),                      # one row: 16 slices of nothing but a row
+    (2048, 160, [3, 0, 8, 1], True, True),             # the second layer's reduction is 160 deep, its columns 2048; a width of 128 + 32
+    (4128, 32, [5, 9], False, False),                  # 64 blocks and a half: uneven slices
+    (96, 1120, [31, 32, 33, 0, 64, 65], True, True),   # edges of the tile heights
+    (512, 4096, [60, 52, 64, 56, 57], False, True),    # tiles of 64 rows
+    (1056, 1376, [128, 127, 1, 129, 97] * 3, True, False),   # tiles of 128 rows, second row blocks
+    (64, 352, [2, 0, 1, 5] * 20, False, True),         # more than 64 experts
+    (768, 2016, [250, 300], True, True),               # few tiles although there are many rows
+]
+
+
+@pytest.mark.parametrize("d,h,rows,top1,biases", CASES, ids=lambda v: str(v)[:24].replace(" ", ""))
+def test_forward(d, h, rows, top1, biases):
+    import torch
+
+    print(f"[case] d {d} h {h} rows {rows[:8]} x {len(rows)}", flush=True)
+    E, N, dev = len(rows), sum(rows), torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(d + h + E)
+    normal = lambda shape, std=1.0: torch.empty(shape, dtype=torch.bfloat16, device=dev).normal_(0.0, std, generator=g)
+    expert = torch.repeat_interleave(torch.arange(E, device=dev), torch.tensor(rows, device=dev))[torch.randperm(N, generator=g, device=dev)]
+    k = 1 if top1 or E == 1 else 2
+    X, Wg = normal((N, d)), torch.zeros((d, E), dtype=torch.bfloat16, device=dev)
+    if E <= d:
+        X[:, :E] = 0                               # one feature per expert decides: the experts' row counts are exact (top-1)
+        X[torch.arange(N, device=dev), expert] = 1
+        Wg[torch.arange(E), torch.arange(E)] = 1
+    else:
+        Wg = normal((d, E))
+    W1, W2 = normal((E, d, h), 0.1), normal((E, h, d), 0.1)
+    b1, b2 = (normal((E, h)), normal((E, d))) if biases else (None, None)
+    desc = B.make_desc(N, d, h, E, k)
+    buf = B.MoeLayerBuffers(desc, dev)
+    Y = torch.empty_like(X)
+    ws, st = (buf.workspace, buf.ws_bytes), buf.stream()
+    B.moe_plan(desc, X, Wg, None, buf.plan, *ws, st)
+    for _ in range(2):                             # (the arrival counters are as the next launch expects them)
+        Y.fill_(float("nan"))
+        B.moe_forward(desc, buf.plan, X, W1, W2, b1, b2, Y, *ws, st)
+    first = Y.clone()
+    B.moe_forward(desc, buf.plan, X, W1, W2, b1, b2, Y, *ws, st)
+    assert torch.equal(first, Y)                   # sums in the same order whatever the timing
+    M = N * k
+
+    def region(name, width):
+        off, n = B.moe_workspace_region(desc, name)
+        return buf.workspace[off:off + n].view(torch.bfloat16).view(M, width)
+
+    Z, H, perm = region("Z", h), region("H", h), buf.perm[:M].long()
+    out = Y[perm // k] if k == 1 else region("Ys", d)
+    r0 = 0
+    for e, n in enumerate(buf.counts[:E].tolist()):
+        seg = slice(r0, r0 + n)
+        r0 += n
+        x, z, hh = X[perm[seg] // k].float(), Z[seg].float(), H[seg].float()
+        for name, got, a, w, bias in (("Z", z, x, W1[e].float(), b1), ("Ys", out[seg].float(), hh, W2[e].float(), b2)):
+            ref, size = a @ w, a.abs() @ w.abs()
+            if biases:
+                ref, size = ref + bias[e].float(), size + bias[e].float().abs()
+            # exact products; both sums round by at most depth * 2^-24 of the terms' size each, the result to bf16 by 2^-8 of itself
+            bound = 2 * (a.shape[1] + 1) * 2.0 ** -24 * size + 2.0 ** -8 * ref.abs() + 1e-30
+            over = float(((got - ref).abs() - bound).max()) if n else 0.0
+            assert over <= 0, (name, e, over)
+        # H = z Phi(z) of the sum before its rounding to Z: off by Z's rounding (8 significant bits: 2^-8 of z, with a slope below
+        # 1.13), H's own and Phi's error
+        ref = z.double() * 0.5 * torch.erfc(-z.double() / 2 ** 0.5)
+        bound = 2.0 ** -8 * (1.13 * z.abs().double() + 1.01 * ref.abs()) + z.abs().double() * 2e-7 + 1e-30
+        over = float(((hh.double() - ref).abs() - bound).max()) if n else 0.0
+        assert over <= 0, ("H", e, over)
