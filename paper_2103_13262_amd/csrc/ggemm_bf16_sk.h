@@ -1076,15 +1076,18 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
     // and for FC2, even for FC1 and dXs, and 10 % slower for dH, so each kind gets its better one.
     // (Two workgroups of 4 waves per compute unit, each on a 256 x 128 tile with 32-deep blocks, so that one computes
     // while the other waits or writes its tile, are 15-20 % slower: they move half as much again into LDS per flop.)
-    // Many small experts (fewer than 96 rows on average): the forward products in the small tiles of ggemm_bf16_tile.h, the
-    // backward ones in 64 x 256 tiles, 8 waves of 64 x 32, 3 ring slots, so that a tile is not mostly rows that do not exist.  (The
+    // Many small experts (fewer than 96 rows on average): the forward products and some of the backward ones in the small tiles of
+    // ggemm_bf16_tile.h, the others in 64 x 256 tiles, 8 waves of 64 x 32, 3 ring slots, so that a tile is not mostly rows that do not exist.  (The
     // weight gradients keep the large tile: their tile spans the weight matrix, not the expert's rows.)
     // Otherwise the rows kinds run in two size classes (launch_cls): an expert's last few rows in 128 x 512 tiles.
     if constexpr (KIND != kColsT) {
         if (!offsets_fit(a)) { launch_cfg<KIND, 1, 8, 2, 1, 3, 64, true>(a, st); return; }
         if constexpr (KIND == kRowsNN || KIND == kRowsNN_GeLU) {
             if (tile_pays(a)) { launch_tile<KIND>(a, st); return; }
-        } else if (a.M < 96L * a.E) { launch_cfg<KIND, 1, 8, 2, 1, 3, 64>(a, st); return; }
+        } else {
+            if (tile_beats_pair(a)) { launch_tile<KIND>(a, st); return; }
+            if (a.M < 96L * a.E) { launch_cfg<KIND, 1, 8, 2, 1, 3, 64>(a, st); return; }
+        }
         if (!a.cls) { fail_launch("grouped GEMM: the plan step's size-class tables are missing"); return; }
         if constexpr (KIND == kRowsNN) launch_cls<KIND, 4, 32>(a, st);
         else launch_cls<KIND, 2, 64>(a, st);

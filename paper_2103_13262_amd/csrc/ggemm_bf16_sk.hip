@@ -52,6 +52,7 @@ bool ggemm_pair_pays(const GemmArgs& rows)
     const int wgs = sk::persistent_wgs();
     if (wgs < 8) return false;
     if (!offsets_fit(rows)) return false;
+    if (tile_beats_pair(rows)) return false;
     const long row_tiles = rows.M / 256 + rows.E / 2, col_tiles = (rows.Nout + 255) / 256;
     return row_tiles * col_tiles <= 8L * wgs;
 }

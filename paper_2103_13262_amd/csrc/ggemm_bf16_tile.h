@@ -28,7 +28,8 @@ template <int KIND, int BM_, int STAGES_> struct TileCfg {
     static constexpr bool B_TRANS = KIND == kRowsNN || KIND == kRowsNN_GeLU;
     static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int LA = A_BYTES / 1024 / NW, LB = B_BYTES / 1024 / NW, PER = LA + LB;
-    static constexpr int PITCH = BN * 2 + 16;          // bytes of a row of results in LDS
+    static constexpr bool DGELU = KIND == kRowsNT_dGeLU;  // results wait in LDS in fp32 for the saved pre-activations
+    static constexpr int PITCH = BN * (DGELU ? 4 : 2) + 16;   // bytes of a row of results in LDS
     static constexpr int RESULTS = BM * PITCH * (KIND == kRowsNN_GeLU ? 2 : 1);
     static constexpr int SMEM = std::max(STAGES * STAGE_BYTES, RESULTS);
 };
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
     // together in LDS so that memory sees whole rows of it: 256 bytes in a row (in pieces of 32 bytes, straight from the registers,
     // the stores of 67 MB took 52 us longer than none).
     const int half = lane >> 5;
-    char* const out1 = smem + (r0 + (lane & 31)) * C::PITCH + (c0 + half * 8) * 2;
+    char* const out1 = smem + (r0 + (lane & 31)) * C::PITCH + (C::DGELU ? (c0 + half * 4) * 4 : (c0 + half * 8) * 2);
     auto put = [&](char* at, const unsigned (&w)[4][2]) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
@@ -277,6 +278,13 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             if (i >= tm_act) break;
+            if constexpr (C::DGELU) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *(float4*)(out1 + i * 32 * C::PITCH + j * 128 + q * 32) =
+                        make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+                continue;
+            }
             unsigned w[4][2], w2[4][2];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -305,7 +313,24 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
         const int m = r + prow;
         if (m < Mt && pok) {
             size_t row = (size_t)row0 + m;
-            const char* const from = smem + m * C::PITCH + piece * 16;
+            const char* const from = smem + m * C::PITCH + piece * (C::DGELU ? 32 : 16);
+            if constexpr (C::DGELU) {                       // dZ = dH (Phi(z) + z phi(z))
+                const size_t o = row * g.Nout + n0 + piece * 8;
+                const uint4 zw = *(const uint4*)((const u16*)g.Zin + o);
+                const float4 lo = *(const float4*)from, hi = *(const float4*)(from + 16);
+                const unsigned w[4] = {zw.x, zw.y, zw.z, zw.w};
+                float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const float zf = __uint_as_float(t & 1 ? w[t / 2] & 0xffff0000u : w[t / 2] << 16);
+                    const float zc = fminf(fmaxf(zf, -16.f), 16.f);   // (the factor is 0 or 1 there; an infinite z must not meet a zero)
+                    float ex;
+                    const float cdf = normal_cdf(zc, ex);
+                    x[t] *= fmaf(zc * 0.39894228040143268f, ex, cdf);
+                }
+                store_out((uint4*)((u16*)g.C + o), make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])), streaming);
+                continue;
+            }
             if constexpr (KIND == kRowsNN_GeLU)
                 store_out((uint4*)((u16*)g.C2 + row * g.Nout + n0 + piece * 8), *(const uint4*)(from + BM * C::PITCH), streaming);
             if constexpr (KIND == kRowsNN) {                // top-1: the row goes straight to its token's place in Y

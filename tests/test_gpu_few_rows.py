@@ -1,4 +1,4 @@
-"""Forward products with few rows per expert (tiles of 32, 64 and 128 rows by 128 columns, reductions cut into slices): the products at the
+"""Products with few rows per expert (tiles of 32, 64 and 128 rows by 128 columns, reductions cut into slices): the products at the
 edges of their tiles, against torch in fp32."""
 import pytest
 
@@ -76,3 +76,59 @@ def test_forward(d, h, rows, top1, biases):
         bound = 2.0 ** -8 * (1.13 * z.abs().double() + 1.01 * ref.abs()) + z.abs().double() * 2e-7 + 1e-30
         over = float(((hh.double() - ref).abs() - bound).max()) if n else 0.0
         assert over <= 0, ("H", e, over)
+
+
+BACKWARD = [  # d, h, rows per expert
+    (2048, 96, [5, 1, 0, 40]),                 # dZ 2048 deep with 96 columns
+    (160, 2144, [33, 64, 65, 1, 129, 0, 31]),  # dXs 33 blocks and a half deep, 128 + 32 columns
+    (1024, 1056, [63, 64, 65, 60, 57, 90, 31] * 4),   # as many rows as a tile has, 60 MB of weights
+    (992, 544, [3, 33, 16, 20] * 12),          # columns that fill 256-wide tiles badly
+]
+
+
+@pytest.mark.parametrize("d,h,rows", BACKWARD, ids=lambda v: str(v)[:24].replace(" ", ""))
+def test_backward(d, h, rows):
+    import torch
+
+    print(f"[case] d {d} h {h} rows {rows[:8]} x {len(rows)}", flush=True)
+    E, N, dev = len(rows), sum(rows), torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(d + h + E)
+    normal = lambda shape, std=1.0: torch.empty(shape, dtype=torch.bfloat16, device=dev).normal_(0.0, std, generator=g)
+    expert = torch.repeat_interleave(torch.arange(E, device=dev), torch.tensor(rows, device=dev))[torch.randperm(N, generator=g, device=dev)]
+    X, Wg = normal((N, d)), torch.zeros((d, E), dtype=torch.bfloat16, device=dev)
+    X[:, :E] = 0                                   # one feature per expert decides: the experts' row counts are exact
+    X[torch.arange(N, device=dev), expert] = 1
+    Wg[torch.arange(E), torch.arange(E)] = 1
+    W1, W2, dY = normal((E, d, h), 0.1), normal((E, h, d), 0.1), normal((N, d))
+    desc = B.make_desc(N, d, h, E, 1)
+    buf = B.MoeLayerBuffers(desc, dev)
+    ws, st = (buf.workspace, buf.ws_bytes), buf.stream()
+    Y, dX, dWg, dW1, dW2 = (torch.empty_like(t) for t in (dY, X, Wg, W1, W2))
+    B.moe_plan(desc, X, Wg, None, buf.plan, *ws, st)
+    B.moe_forward(desc, buf.plan, X, W1, W2, None, None, Y, *ws, st)
+    B.moe_backward(desc, buf.plan, X, Wg, W1, W2, dY, dX, dWg, torch.empty(max(E, 4), device=dev), dW1, dW2, *ws, st)
+    assert buf.counts[:E].tolist() == rows
+
+    def region(name, width):
+        off, n = B.moe_workspace_region(desc, name)
+        return buf.workspace[off:off + n].view(torch.bfloat16).view(N, width)
+
+    Z, H, dYs, dZ, dXs, Xs = (region(n, w).float() for n, w in (("Z", h), ("H", h), ("dYs", d), ("dZ", h), ("dXs", d), ("Xs", d)))
+    r0 = 0
+    for e, n in enumerate(rows):
+        seg = slice(r0, r0 + n)
+        r0 += n
+        z = Z[seg].double()
+        slope = (0.5 * torch.erfc(-z / 2 ** 0.5) + z * torch.exp(-0.5 * z * z) / (2 * torch.pi) ** 0.5).float()
+        one = torch.ones((), device=dev)
+        for name, got, a, w, f in (("dZ", dZ[seg], dYs[seg], W2[e].float().T, slope), ("dXs", dXs[seg], dZ[seg], W1[e].float().T, one),
+                                   ("dW1", dW1[e].float(), Xs[seg].T, dZ[seg], one), ("dW2", dW2[e].float(), H[seg].T, dYs[seg], one)):
+            if not got.numel():
+                continue
+            ref, size = a @ w, a.abs() @ w.abs()
+            # exact products; both sums round by at most depth * 2^-24 of the terms' size each, the result to bf16 by 2^-8 of itself;
+            # dZ's factor is off by less than 4e-4 where a table's nearest entry stands for it (the products that share a launch)
+            bound = 2 * (a.shape[1] + 1) * 2.0 ** -24 * size * f.abs() + ref.abs() * (2.0 ** -8 * f.abs() * 1.01 + (4e-4 if name == "dZ" else 0)) + 1e-30
+            over = float(((got - ref * f).abs() - bound).max())
+            assert over <= 0, (name, e, over)
