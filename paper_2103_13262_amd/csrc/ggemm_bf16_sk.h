@@ -1021,7 +1021,7 @@ template <int KIND, bool CLASSES, bool DEEP>
 __global__ __launch_bounds__(512, 1) void ggemm_pair_kernel(GemmArgs g1, int ntn1, int ntn1_small, GemmArgs g2, int ntm2, int ntn2)
 {
     if constexpr (CLASSES) ggemm_classes<KIND, 2, 64, DEEP>(g1, ntn1, ntn1_small);
-    else ggemm_sk_body<KIND, 1, 8, 2, 1, 3, 64>(g1, 0, ntn1);
+    else ggemm_sk_body<KIND, 2, 4, 1, 2, 3, 64>(g1, 0, ntn1);
     __syncthreads();
     ggemm_sk_body<kColsT, 2, 4, 4, 2, 4, 32>(g2, ntm2, ntn2);
 }
@@ -1077,16 +1077,18 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
     // (Two workgroups of 4 waves per compute unit, each on a 256 x 128 tile with 32-deep blocks, so that one computes
     // while the other waits or writes its tile, are 15-20 % slower: they move half as much again into LDS per flop.)
     // Many small experts (fewer than 96 rows on average): the forward products and some of the backward ones in the small tiles of
-    // ggemm_bf16_tile.h, the others in 64 x 256 tiles, 8 waves of 64 x 32, 3 ring slots, so that a tile is not mostly rows that do not exist.  (The
-    // weight gradients keep the large tile: their tile spans the weight matrix, not the expert's rows.)
+    // ggemm_bf16_tile.h, the others in 64 x 256 tiles, 8 waves of 32 x 64, 3 ring slots, so that a tile is not mostly rows that do
+    // not exist.  (Waves of 64 x 32 store a row in pieces of 64 bytes, which streaming stores write at 3.5 TB/s instead of 5.6: dZ
+    // with dW2 of 256 experts with 64 rows, d 512, h 1024: 156 us, in waves of 32 x 64 149.)  (The weight gradients keep the large
+    // tile: their tile spans the weight matrix, not the expert's rows.)
     // Otherwise the rows kinds run in two size classes (launch_cls): an expert's last few rows in 128 x 512 tiles.
     if constexpr (KIND != kColsT) {
-        if (!offsets_fit(a)) { launch_cfg<KIND, 1, 8, 2, 1, 3, 64, true>(a, st); return; }
+        if (!offsets_fit(a)) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64, true>(a, st); return; }
         if constexpr (KIND == kRowsNN || KIND == kRowsNN_GeLU) {
             if (tile_pays(a)) { launch_tile<KIND>(a, st); return; }
         } else {
             if (tile_beats_pair(a)) { launch_tile<KIND>(a, st); return; }
-            if (a.M < 96L * a.E) { launch_cfg<KIND, 1, 8, 2, 1, 3, 64>(a, st); return; }
+            if (a.M < 96L * a.E) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64>(a, st); return; }
         }
         if (!a.cls) { fail_launch("grouped GEMM: the plan step's size-class tables are missing"); return; }
         if constexpr (KIND == kRowsNN) launch_cls<KIND, 4, 32>(a, st);
@@ -1099,7 +1101,7 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
 template <int KIND, bool CLASSES, bool DEEP>
 void launch_pair_cfg(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
 {
-    using C1 = std::conditional_t<CLASSES, Cfg<KIND, 2, 4, 4, 2, 2, 64>, Cfg<KIND, 1, 8, 2, 1, 3, 64>>;
+    using C1 = std::conditional_t<CLASSES, Cfg<KIND, 2, 4, 4, 2, 2, 64>, Cfg<KIND, 2, 4, 1, 2, 3, 64>>;
     using C1s = CfgWide<KIND>;
     using C2 = Cfg<kColsT, 2, 4, 4, 2, 4, 32>;
     constexpr int SMEM = std::max({C1::SMEM, CLASSES ? C1s::SMEM : 0, CLASSES && DEEP ? CfgDeep<KIND>::SMEM : 0, C2::SMEM});
