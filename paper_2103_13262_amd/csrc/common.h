@@ -266,8 +266,8 @@ inline void set_control(GemmArgs& a, char* ws, const WsLayout& L)
     a.skewed = ctl + kCtlSkewed;
     a.dyn_counters = ctl + kCtlDyn;
 }
-void launch_segment_sums(const moe_desc_t& D, const WsLayout& L, const void* src, int width, const int32_t* counts,
-                         const int32_t* offsets, float* out, char* ws, hipStream_t st);
+void launch_bias_sums(const moe_desc_t& D, const WsLayout& L, const int32_t* counts, const int32_t* offsets, float* db1, float* db2, char* ws,
+                      hipStream_t st);
 void launch_ggemm_f32(const GemmArgs& a, hipStream_t st);
 void launch_ggemm_pair_f32(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st);   // as launch_ggemm_pair_bf16_sk
 void launch_ggemm_bf16_sk(const GemmArgs& a, hipStream_t st);

@@ -484,8 +484,7 @@ moe_status_t moe_bias_backward(const moe_desc_t* desc, const moe_plan_t* plan, f
     char* ws = (char*)workspace;
     // z = xs W1 + b1 and ys = h W2 + b2 per row: the bias gradients are the column sums, over the expert's rows,
     // of dZ and of dYs, which moe_backward left in the workspace.  (With N == 0 every sum is empty.)
-    if (db1) launch_segment_sums(D, L, ws + L.dZ, D.h, plan->counts, plan->offsets, db1, ws, st);
-    if (db2) launch_segment_sums(D, L, ws + L.dYs, D.d, plan->counts, plan->offsets, db2, ws, st);
+    launch_bias_sums(D, L, plan->counts, plan->offsets, db1, db2, ws, st);
     return check_launch("expert bias gradients");
 }
 

@@ -256,32 +256,16 @@ __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const 
 // owns one 16-byte column piece and walks the rows of its piece; a second kernel adds an expert's pieces
 // in ascending order.
 template <typename T>
-__global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, const float* __restrict__ dl,
-                                                   const int32_t* __restrict__ perm, const int32_t* __restrict__ counts,
-                                                   const int32_t* __restrict__ offsets, const int32_t* __restrict__ P64,
-                                                   float* __restrict__ part, float* __restrict__ bpart, int E, int d,
-                                                   int cpr, const T* __restrict__ Wg, T* __restrict__ WgT)
+__device__ __forceinline__ void segment_partial(const void* __restrict__ Xs, const float* __restrict__ dl, const int32_t* __restrict__ perm,
+                                                const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
+                                                const int32_t* __restrict__ P64, float* __restrict__ part, float* __restrict__ bpart, int E,
+                                                int d, int cpr, int piece, int col)
 {
-    // Rides along (WgT != nullptr): WgT[e][i] = Wg[i][e], which lets the kernel that follows the reduction read a
-    // gate column as contiguous 16-byte pieces; spread over all workgroups of the launch.
-    if (WgT) {
-        const long nel = (long)d * E, nthr = (long)gridDim.x * gridDim.y * gridDim.z * 512;
-        const long block = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        for (long i = block * 512 + threadIdx.x; i < nel; i += nthr) {
-            const int ee = (int)(i / d), row = (int)(i - (long)ee * d);
-            WgT[i] = Wg[(size_t)row * E + ee];
-        }
-    }
     // 64 column threads x 8 row groups: group q walks rows 8q .. 8q+7 of the piece (all eight loads in flight); the
     // groups' sums are added in the order (((0 + 1) + 2) + ...) + 7, so the result does not depend on timing.
     constexpr int V = Vec<T>::N;
     __shared__ float s_g[64];
     __shared__ float s_acc[7][64][V];
-    // The column blocks of a piece are neighbours, so that rows of several KB are read while their pages of memory are open (gate
-    // backward of 32768 tokens, d 2048, 32 experts, top-2, bf16: 149 us with a launch's pieces of the first column block in front
-    // of those of the second, 137 so).  Two of them change places every four pieces: otherwise every other XCD (workgroup number
-    // modulo 8) would get all the second ones, which may be mostly empty.
-    const int piece = (int)(blockIdx.z * gridDim.y + blockIdx.y), col = gridDim.x == 2 ? (int)blockIdx.x ^ (piece >> 2 & 1) : (int)blockIdx.x;
     const int pieces = P64[E];
     Segment sg;
     if (E <= 256) {
@@ -357,6 +341,45 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
     }
 }
 
+template <typename T>
+__global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, const float* __restrict__ dl,
+                                                   const int32_t* __restrict__ perm, const int32_t* __restrict__ counts,
+                                                   const int32_t* __restrict__ offsets, const int32_t* __restrict__ P64,
+                                                   float* __restrict__ part, float* __restrict__ bpart, int E, int d,
+                                                   int cpr, const T* __restrict__ Wg, T* __restrict__ WgT)
+{
+    // Rides along (WgT != nullptr): WgT[e][i] = Wg[i][e], which lets the kernel that follows the reduction read a
+    // gate column as contiguous 16-byte pieces; spread over all workgroups of the launch.
+    if (WgT) {
+        const long nel = (long)d * E, nthr = (long)gridDim.x * gridDim.y * gridDim.z * 512;
+        const long block = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        for (long i = block * 512 + threadIdx.x; i < nel; i += nthr) {
+            const int ee = (int)(i / d), row = (int)(i - (long)ee * d);
+            WgT[i] = Wg[(size_t)row * E + ee];
+        }
+    }
+    // The column blocks of a piece are neighbours, so that rows of several KB are read while their pages of memory are open (gate
+    // backward of 32768 tokens, d 2048, 32 experts, top-2, bf16: 149 us with a launch's pieces of the first column block in front
+    // of those of the second, 137 so).  Two of them change places every four pieces: otherwise every other XCD (workgroup number
+    // modulo 8) would get all the second ones, which may be mostly empty.
+    const int piece = (int)(blockIdx.z * gridDim.y + blockIdx.y), col = gridDim.x == 2 ? (int)blockIdx.x ^ (piece >> 2 & 1) : (int)blockIdx.x;
+    segment_partial<T>(Xs, dl, perm, counts, offsets, P64, part, bpart, E, d, cpr, piece, col);
+}
+
+// Plain column sums of two row matrices over the same segments (the gradients of both layers' biases), side by side in one launch:
+// the column blocks of the first, then those of the second, going round from piece to piece so that an XCD (workgroup number
+// modulo 8) does not get the same ones of all pieces.
+struct ColumnSums { const void* src; float* part; float* out; int width, cpr; };
+template <typename T>
+__global__ __launch_bounds__(512) void segsum_partial(ColumnSums a, ColumnSums b, const int32_t* __restrict__ counts,
+                                                      const int32_t* __restrict__ offsets, const int32_t* __restrict__ P64, int E)
+{
+    const int piece = (int)(blockIdx.z * gridDim.y + blockIdx.y), first = (a.cpr + 63) / 64;
+    const int x = (int)((blockIdx.x + (unsigned)piece) % gridDim.x);
+    const ColumnSums s = x < first ? a : b;
+    segment_partial<T>(s.src, nullptr, nullptr, counts, offsets, P64, s.part, nullptr, E, s.width, s.cpr, piece, x < first ? x : x - first);
+}
+
 // grid (ceil(d / 256), E): a thread owns one row of one expert's column, so that the threads of a wavefront read
 // consecutive floats of every piece; the pieces are added in ascending order (loads four at a time, sums in order).
 template <typename G>
@@ -409,15 +432,16 @@ __global__ __launch_bounds__(256) void gate_bwd_tail(int fgx, const float* __res
 }
 
 // out[e][c] = sum of the pieces of expert e, in ascending order (the column sums of its segment).
-__global__ __launch_bounds__(256) void segsum_final(const float* __restrict__ part, const int32_t* __restrict__ P64,
-                                                    float* __restrict__ out, int width, int accumulate)
+__global__ __launch_bounds__(256) void segsum_final(ColumnSums a, ColumnSums b, const int32_t* __restrict__ P64, int accumulate)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x, e = blockIdx.y;
-    if (c >= width) return;
+    const int first = (a.width + 255) / 256, x = (int)blockIdx.x, e = blockIdx.y;
+    const ColumnSums m = x < first ? a : b;
+    const int c = (x < first ? x : x - first) * 256 + threadIdx.x;
+    if (c >= m.width) return;
     float s = 0.f;
-    for (int q = P64[e]; q < P64[e + 1]; ++q) s += part[(size_t)q * width + c];
-    const size_t o = (size_t)e * width + c;
-    out[o] = accumulate ? out[o] + s : s;
+    for (int q = P64[e]; q < P64[e + 1]; ++q) s += m.part[(size_t)q * m.width + c];
+    const size_t o = (size_t)e * m.width + c;
+    m.out[o] = accumulate ? m.out[o] + s : s;
 }
 
 // ---- launchers -----------------------------------------------------------------------------------
@@ -480,10 +504,10 @@ void launch_dcombine(const moe_desc_t& D, const void* dY, const void* Ys, const 
 }
 
 // grid of dwg_partial: column blocks, then pieces (over two dimensions: one holds 65535 workgroups)
-static dim3 piece_grid(long pieces, int cpr)
+static dim3 piece_grid(long pieces, int col_blocks)
 {
     const unsigned y = (unsigned)(pieces < 32768 ? pieces : 32768);
-    return dim3((unsigned)((cpr + 63) / 64), y, (unsigned)((pieces + y - 1) / y));
+    return dim3((unsigned)col_blocks, y, (unsigned)((pieces + y - 1) / y));
 }
 
 void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
@@ -494,7 +518,7 @@ void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, con
     float* part = (float*)(ws + L.dwg_part);
     float* bpart = (float*)(ws + L.dbg_part);
     const int32_t* P64 = (const int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
-    const dim3 pg = piece_grid(L.dwg_pieces, cpr);
+    const dim3 pg = piece_grid(L.dwg_pieces, (cpr + 63) / 64);
     const unsigned xg = grid_for((long)D.N * cpr);
     void* WgT = ws + L.WgT;
     const int fgx = (D.d + 255) / 256;
@@ -515,23 +539,22 @@ void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, con
     else launch((unsigned short)0, float{});
 }
 
-// out[E][width] (float) = column sums of src[M][width] over every expert's segment (fixed order).
-void launch_segment_sums(const moe_desc_t& D, const WsLayout& L, const void* src, int width, const int32_t* counts,
-                         const int32_t* offsets, float* out, char* ws, hipStream_t st)
+// Column sums over every expert's segment (fixed order): db1[E][h] of dZ[M][h] and db2[E][d] of dYs[M][d], either NULL for none.
+void launch_bias_sums(const moe_desc_t& D, const WsLayout& L, const int32_t* counts, const int32_t* offsets, float* db1, float* db2, char* ws,
+                      hipStream_t st)
 {
-    const int cpr = (int)((size_t)width * dtype_size(D.dtype) / 16);
-    float* part = (float*)(ws + L.bias_part);
+    auto sums = [&](size_t src, size_t part, float* out, int width) {
+        return ColumnSums{ws + src, (float*)(ws + part), out, out ? width : 0, out ? (int)((size_t)width * dtype_size(D.dtype) / 16) : 0};
+    };
+    const ColumnSums a = sums(L.dZ, L.bias_part, db1, D.h), b = sums(L.dYs, L.dwg_part, db2, D.d);
+    const int cols = (a.cpr + 63) / 64 + (b.cpr + 63) / 64;
+    if (!cols) return;
     const int32_t* P64 = (const int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
-    const dim3 pg = piece_grid(L.dwg_pieces, cpr);
-    if (D.dtype == MOE_BF16)
-        hipLaunchKernelGGL(dwg_partial<unsigned short>, pg, dim3(512), 0, st, src, (const float*)nullptr,
-                           (const int32_t*)nullptr, counts, offsets, P64, part, (float*)nullptr, D.E, width, cpr,
-                           (const unsigned short*)nullptr, (unsigned short*)nullptr);
-    else
-        hipLaunchKernelGGL(dwg_partial<float>, pg, dim3(512), 0, st, src, (const float*)nullptr, (const int32_t*)nullptr,
-                           counts, offsets, P64, part, (float*)nullptr, D.E, width, cpr, (const float*)nullptr, (float*)nullptr);
-    hipLaunchKernelGGL(segsum_final, dim3((unsigned)((width + 255) / 256), (unsigned)D.E), dim3(256), 0, st,
-                       (const float*)part, P64, out, width, D.accumulate);
+    const dim3 pg = piece_grid(L.dwg_pieces, cols);
+    if (D.dtype == MOE_BF16) hipLaunchKernelGGL(segsum_partial<unsigned short>, pg, dim3(512), 0, st, a, b, counts, offsets, P64, D.E);
+    else hipLaunchKernelGGL(segsum_partial<float>, pg, dim3(512), 0, st, a, b, counts, offsets, P64, D.E);
+    hipLaunchKernelGGL(segsum_final, dim3((unsigned)((a.width + 255) / 256 + (b.width + 255) / 256), (unsigned)D.E), dim3(256), 0, st, a, b, P64,
+                       D.accumulate);
 }
 
 }  // namespace moe
