@@ -323,7 +323,8 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     const float zf = __uint_as_float(t & 1 ? w[t / 2] & 0xffff0000u : w[t / 2] << 16);
-                    const float zc = fminf(fmaxf(zf, -16.f), 16.f);   // (the factor is 0 or 1 there; an infinite z must not meet a zero)
+                    // (beyond 16 the factor is 0 or 1, and an infinite z must not meet a zero; a NaN stays one)
+                    const float zc = fabsf(zf) > 16.f ? copysignf(16.f, zf) : zf;
                     float ex;
                     const float cdf = normal_cdf(zc, ex);
                     x[t] *= fmaf(zc * 0.39894228040143268f, ex, cdf);
