@@ -35,9 +35,6 @@ int persistent_wgs()
 
 }  // namespace sk
 
-// With few tiles per workgroup the ragged end of a rows-kind launch (a quarter to half a tile per workgroup) and the
-// launch gap are worth more than the counter's round trips; measured, the pair wins up to about 8 tiles per
-// workgroup (C1: -3 % per step, C2: -1.4 %) and loses 0.5 % at 34 (C4).
 // How often a workgroup polls for its predecessor's partial sum before it gives up and sets the workspace's status
 // word.  MOE355_SPIN_LIMIT overrides the default (about a second); a negative value makes every wait give up at once,
 // which is how the tests reach the status word without making anything hang.
@@ -47,6 +44,9 @@ static int spin_limit()
     return s && *s ? atoi(s) : sk::kSpinLimit;
 }
 
+// With few tiles per workgroup the ragged end of a rows-kind launch (a quarter to half a tile per workgroup) and the
+// launch gap are worth more than the counter's round trips; measured, the pair wins up to about 8 tiles per
+// workgroup (C1: -3 % per step, C2: -1.4 %) and loses 0.5 % at 34 (C4).
 bool ggemm_pair_pays(const GemmArgs& rows)
 {
     const int wgs = sk::persistent_wgs();
