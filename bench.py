@@ -232,7 +232,7 @@ def run(a, torch, B, WORKLOADS, make_inputs):
         clock_mhz = 100.0 * cyc / ticks if ticks > 0 else None
     roofline = {"bound": "mfma",
                 # (the bf16 backward puts dZ with dW2 and dXs with dW1 into one launch each where that pays)
-                "kernel": ("ggemm_cls_kernel / ggemm_pair_kernel / ggemm_sk_kernel" if bf else
+                "kernel": ("ggemm_cls_kernel / ggemm_pair_kernel / ggemm_sk_kernel / ggemm_tile_kernel" if bf else
                            "ggemm_f32_sliced / ggemm_f32_tiled and their pairs")
                 + " (%d launches of 6 products per step)" % round(g_launches / a.steps),
                 "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
