@@ -124,8 +124,9 @@ moe_status_t moe_plan(const moe_desc_t *desc, const void *X, const void *Wg, con
  *   layers (the paper's expert is an FFN, Section 5.1): E_e(x) = GeLU(x W1[e] + b1[e]) W2[e] + b2[e].
  *   Y device [N,d] dtype, written.
  * Leaves Z (pre-activation), H and Ys in the workspace for moe_backward.  bf16: Z is the
- * rounded accumulator, H = z * Phi(Z) with z the fp32 accumulator and Phi the normal CDF taken at
- * the stored Z (the erf GeLU up to that rounding inside Phi, which moves H by less than 6e-4).
+ * rounded accumulator, H = z * Phi(z) with z the fp32 accumulator and Phi the normal CDF, evaluated
+ * in fp32 (products with few rows per expert) or looked up at the stored Z and carried to z along the
+ * slope (up to 6e-3 of itself off at z = -7; outside 2^-11 <= |Z| < 8 Phi is off by less than 4e-4).
  * The two data movements of Section 4 are done on the fly where that saves a pass over memory: the
  * first layer reads row perm[r] / k of X as row r of its input (no scattered copy is written in the
  * forward pass; moe_backward writes Xs for the weight gradients), and with k = 1 and score_all = 0,

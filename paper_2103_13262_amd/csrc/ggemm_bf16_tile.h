@@ -16,6 +16,7 @@
 #include <algorithm>
 
 #include "bf16_tiles.h"
+#include "gauss.h"
 
 namespace moe {
 namespace sk {
@@ -33,20 +34,6 @@ template <int KIND, int BM_, int STAGES_> struct TileCfg {
     static constexpr int RESULTS = BM * PITCH * (KIND == kRowsNN_GeLU ? 2 : 1);
     static constexpr int SMEM = std::max(STAGES * STAGE_BYTES, RESULTS);
 };
-
-// Phi(z) = (1 + erf(z / sqrt 2)) / 2 from formula 7.1.26 of Abramowitz and Stegun, "Handbook of Mathematical Functions" (error
-// below 1.5e-7), in its form for the complement, so that small values at negative z keep their leading digits; e = exp(-z^2 / 2).
-__device__ __forceinline__ float normal_cdf(float z, float& e)
-{
-    const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(z), 0.2316418882f, 1.0f));
-    e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
-    float p = fmaf(t, 0.5307027145f, -0.7265760135f);
-    p = fmaf(t, p, 0.7107068705f);
-    p = fmaf(t, p, -0.142248368f);
-    p = fmaf(t, p, 0.127414796f);
-    const float q = p * t * e;
-    return z < 0.f ? q : 1.0f - q;
-}
 
 template <int KIND, int BM, int STAGES, int OCC>
 __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int ntn, int slices)
@@ -294,9 +281,9 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
                 w[q][0] = pack_bf16x2(x[0], x[1]);
                 w[q][1] = pack_bf16x2(x[2], x[3]);
                 if constexpr (KIND == kRowsNN_GeLU) {
-                    float h[4], ex;
+                    float h[4];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) h[t] = x[t] * normal_cdf(x[t], ex);
+                    for (int t = 0; t < 4; ++t) h[t] = x[t] * normal_cdf(x[t]);
                     w2[q][0] = pack_bf16x2(h[0], h[1]);
                     w2[q][1] = pack_bf16x2(h[2], h[3]);
                 }
@@ -323,11 +310,7 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     const float zf = __uint_as_float(t & 1 ? w[t / 2] & 0xffff0000u : w[t / 2] << 16);
-                    // (beyond 16 the factor is 0 or 1, and an infinite z must not meet a zero; a NaN stays one)
-                    const float zc = fabsf(zf) > 16.f ? copysignf(16.f, zf) : zf;
-                    float ex;
-                    const float cdf = normal_cdf(zc, ex);
-                    x[t] *= fmaf(zc * 0.39894228040143268f, ex, cdf);
+                    x[t] *= gelu_slope(zf);
                 }
                 store_out((uint4*)((u16*)g.C + o), make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])), streaming);
                 continue;
