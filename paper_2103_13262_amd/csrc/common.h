@@ -226,7 +226,6 @@ struct GemmArgs {
     long long* clock_probe;    // [2]: shader cycles and 100 MHz ticks of workgroup 0 of the last launch
     const int32_t* skewed;     // 1: the experts' sizes are strongly skewed (decided by the plan step)
     int32_t* dyn_counters;     // [9]: next tile of every XCD's list and the number of workgroups that have finished; zero between launches
-    int whole_tiles;           // rows kinds: never cut a tile (another product in the same launch fills the idle workgroups)
     int on_demand;             // weight gradients: hand the tiles out from the counters whatever the sizes
     int stream_out;            // bf16 products: results leave as streaming stores (set by the host when the experts' weights exceed the L2 caches)
     int spin_limit;            // polls of a "partial sum ready" flag before the wait is given up and the status word set (negative: at once)

@@ -125,7 +125,8 @@ struct Fin {              // what finishing an item needs once the streams have 
 // Of every XCD's workgroups, those numbered wj_base .. wj_base + wj_count - 1 take part and the others return at once;
 // wj_count <= 0: all take part, counted round from wj_base (which only a launch of whole tiles may set then: a split
 // tile's partial sums go from one workgroup to the one numbered next).
-template <int KIND, int WM, int WN, int TM, int TN, int STAGES, int BK, int CLS = 0, bool WIDE = false>
+// WHOLE (rows kinds): never cut a tile (another product in the same launch fills the workgroups that have nothing left to do here).
+template <int KIND, int WM, int WN, int TM, int TN, int STAGES, int BK, int CLS = 0, bool WIDE = false, bool WHOLE = false>
 __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int ntn, int wj_base = 0, int wj_count = 0)
 {
     using C = Cfg<KIND, WM, WN, TM, TN, STAGES, BK>;
@@ -133,6 +134,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
     const int32_t* const counts_ = CLS == 0 ? g.counts : g.cls + (CLS == 1 ? kClsCountsBig : kClsCountsSmall) * (g.E + 1);
     const int32_t* const offsets_ = CLS == 2 ? g.cls + kClsOffsetsSmall * (g.E + 1) : g.offsets;
     constexpr int BM = C::BM, BN = C::BN, NT = C::NT, PITCH = C::PITCH;
+    constexpr bool CUTS = KIND != kColsT && !WHOLE;   // tiles may be cut along their reduction
     extern __shared__ __align__(1024) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -241,10 +243,9 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
         it.Mt = min(rows_per, counts_[e] - mt * BM - row_off);  it.Nt = min(BN, g.Nout - n0);  it.Kt = g.K;
     };
     if constexpr (KIND != kColsT) {
-        if (rem && g.whole_tiles) {
+        if constexpr (WHOLE) {
             // another product follows in this launch and takes up the workgroups that have nothing left to do here:
             // the left-over tiles are computed whole, one per workgroup (no partial sums, no slices)
-            row_f = 1;
             row_item = wj < rem;
         } else if (rem) {
             constexpr int kMinSplitBlocks = kMinSplitDepth / BK;
@@ -271,7 +272,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
                 it.kb0 = 0;  it.kb1 = nkT;  it.owner = 1;
                 if (it.Mt > 0) return true;      // (a slice past the tile's last row holds nothing)
             }
-            if (sk_cur > sk_a) {       // stream-K pieces, last one first
+            if (CUTS && sk_cur > sk_a) {       // stream-K pieces, last one first
                 const int tt = (sk_cur - 1) / nkT;
                 const int seg0 = max(sk_a, tt * nkT);
                 it.kb0 = seg0 - tt * nkT;  it.kb1 = sk_cur - tt * nkT;
@@ -906,10 +907,12 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
             __builtin_amdgcn_s_barrier();              // every wave is done reading the ring
         }
         const Fin fin{cur.c_off, cur.b_off, cur.Mt, cur.Nt, cur.owner, cur.row0};
-        if (cur.kb0 > 0) add_predecessor();   // the blocks before kb0 were summed by the workgroup just below
+        if constexpr (CUTS) {
+            if (cur.kb0 > 0) add_predecessor();   // the blocks before kb0 were summed by the workgroup just below
+        }
         have = __builtin_amdgcn_readfirstlane(next_item(cur));
         if (have) start_item(cur);
-        if (fin.owner) {
+        if (!CUTS || fin.owner) {
             constexpr std::true_type yes;
             constexpr std::false_type no;
             bool done = false;
@@ -925,8 +928,10 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
                 else epilogue(fin, no, no);
             }
         }
-        else store_partial();
-        stores_behind = fin.owner && fin.Mt == BM && fin.Nt == BN && !(KIND == kColsT && (g.out_f32 || g.accumulate));
+        if constexpr (CUTS) {
+            if (!fin.owner) store_partial();
+        }
+        stores_behind = (!CUTS || fin.owner) && fin.Mt == BM && fin.Nt == BN && !(KIND == kColsT && (g.out_f32 || g.accumulate));
     }
     if constexpr (KIND == kColsT) {
         if (dynamic && tid == 0) {       // the last workgroup to finish leaves the counters at zero for the next launch
@@ -954,37 +959,40 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void ggemm_sk_kernel(GemmArgs g, i
 // last pieces in 128 x 128 tiles with 128-deep blocks instead.  A tile's time is its number of blocks times the
 // time a block takes to arrive, so the few last pieces, which get a phase of their own behind the big tiles, are
 // done in a quarter of the blocks, by four times as many workgroups.
-template <int KIND, int STAGES, int BK, bool DEEP>
+// WHOLE: followed by another product in the same launch, so that no tile is cut.  (Known at compile time: with the code that cuts tiles
+// compiled in, a pair kernel needs 24 vector registers more than there are, and 12.6 MB of them pass through memory per launch.  A training
+// step of 4096 tokens, 16 experts, d 1024, h 4096: 623 us so, now 617; 8192 tokens, 64 experts, Zipf 1.2: 1446, 1431.)
+template <int KIND, int STAGES, int BK, bool DEEP, bool WHOLE>
 __device__ __forceinline__ void ggemm_classes(const GemmArgs& g, int ntn_big, int ntn_small)
 {
     if constexpr (DEEP) {
-        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big);
+        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, false, WHOLE>(g, 0, ntn_big);
         __syncthreads();   // the first class's last epilogue is done with the LDS before the second lays it out anew
         // (only while the narrow tiles are at most one round: beyond that their number counts, not their length, and
         // the wide ones are fewer - measured on a skewed load with 44 last pieces: 7 % slower with the narrow ones)
         const int ntn_deep = (g.Nout + 127) / 128;
         if ((long)g.cls[kClsPSmall * (g.E + 1) + g.E] * ntn_deep <= (long)gridDim.x)
-            ggemm_sk_body<KIND, 2, 4, 2, 1, 2, 128, 2>(g, 0, ntn_deep);
+            ggemm_sk_body<KIND, 2, 4, 2, 1, 2, 128, 2, false, WHOLE>(g, 0, ntn_deep);
         else
-            ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2>(g, 0, ntn_small);
+            ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2, false, WHOLE>(g, 0, ntn_small);
         return;
     }
     const int W = gridDim.x >> 3;
     const long Tb = (long)g.cls[kClsPBig * (g.E + 1) + g.E] * ntn_big, Ts = (long)g.cls[kClsPSmall * (g.E + 1) + g.E] * ntn_small;
-    if (g.whole_tiles) {
-        // Followed by another product in the same launch: whole tiles only.  The big tiles go round the workgroups
+    if constexpr (WHOLE) {
+        // The big tiles go round the workgroups
         // from the first on; the last pieces, in 128 x 256 tiles (a 128 x 512 tile of a deep reduction would be the
         // longest item of the launch), start behind the big tiles' last round: few of them stay with the workgroups that
         // got no tile of that round, more go round all workgroups from there on (last_pieces.h).  (Left to those
         // workgroups alone, whatever their number, a load whose big tiles nearly filled the last round gave two workgroups
         // of 32 all last pieces: dXs and dW1 of 16384 rows in 64 experts, Zipf 1.2, d 1024, h 4096, took 1123 us with one
         // seed and 415 with others.)
-        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big);
+        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, false, true>(g, 0, ntn_big);
         if (Ts == 0) return;
         __syncthreads();
         const int after = first_free_workgroup(Tb, W);
         const bool stay = last_pieces_stay((long)g.cls[kClsPSmall * (g.E + 1) + g.E] * ntn_big, after, W);   // (both kinds of tile are 256 wide)
-        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2>(g, 0, ntn_big, after, stay ? W - after : 0);
+        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2, false, true>(g, 0, ntn_big, after, stay ? W - after : 0);
         return;
     }
     if (Ts == 0) { ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big); return; }
@@ -1010,7 +1018,7 @@ __device__ __forceinline__ void ggemm_classes(const GemmArgs& g, int ntn_big, in
 template <int KIND, int STAGES, int BK, bool DEEP>
 __global__ __launch_bounds__(512, 1) void ggemm_cls_kernel(GemmArgs g, int ntn_big, int ntn_small)
 {
-    ggemm_classes<KIND, STAGES, BK, DEEP>(g, ntn_big, ntn_small);
+    ggemm_classes<KIND, STAGES, BK, DEEP, false>(g, ntn_big, ntn_small);
 }
 
 // Two products that do not depend on each other in one launch: a rows kind, then the weight gradients with their
@@ -1020,8 +1028,8 @@ __global__ __launch_bounds__(512, 1) void ggemm_cls_kernel(GemmArgs g, int ntn_b
 template <int KIND, bool CLASSES, bool DEEP>
 __global__ __launch_bounds__(512, 1) void ggemm_pair_kernel(GemmArgs g1, int ntn1, int ntn1_small, GemmArgs g2, int ntm2, int ntn2)
 {
-    if constexpr (CLASSES) ggemm_classes<KIND, 2, 64, DEEP>(g1, ntn1, ntn1_small);
-    else ggemm_sk_body<KIND, 2, 4, 1, 2, 3, 64>(g1, 0, ntn1);
+    if constexpr (CLASSES) ggemm_classes<KIND, 2, 64, DEEP, true>(g1, ntn1, ntn1_small);
+    else ggemm_sk_body<KIND, 2, 4, 1, 2, 3, 64, 0, false, true>(g1, 0, ntn1);
     __syncthreads();
     ggemm_sk_body<kColsT, 2, 4, 4, 2, 4, 32>(g2, ntm2, ntn2);
 }
@@ -1111,7 +1119,6 @@ void launch_pair_cfg(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
     if (wgs < 8) return;
     GemmArgs r = rows, c = cols;
     c.on_demand = 1;
-    r.whole_tiles = 1;
     const int ntn1 = (r.Nout + C1::BN - 1) / C1::BN, ntn1s = (r.Nout + C1s::BN - 1) / C1s::BN;
     const int ntn2 = (c.Nout + C2::BN - 1) / C2::BN, ntm2 = (c.K + C2::BM - 1) / C2::BM;
     hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(512), SMEM, st, r, ntn1, ntn1s, c, ntm2, ntn2);
