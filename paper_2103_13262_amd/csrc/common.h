@@ -9,6 +9,7 @@
 
 #include "../../include/moe355.h"
 #include "dynamic_lds.h"
+#include "routes.h"
 
 namespace moe {
 
@@ -232,26 +233,6 @@ struct GemmArgs {
     int out_f32;      // kColsT: C holds float (else the activation type)
     int accumulate;   // kColsT
 };
-// bf16 products: whether a lane's place in a block of an operand fits 32 bits (setup_offsets): a block spans at most 256 rows of the operand, so
-// it does for all but rows of millions of values (2^22: 256 of them are 2 GB).  (Gathered rows lie anywhere in X: moe_forward
-// gathers only from less than 4 GB.)
-inline bool offsets_fit(const GemmArgs& a) { return a.K < (1 << 22) && a.Nout < (1 << 22); }
-// bf16 backward products: whether a rows kind in small tiles (ggemm_bf16_tile.h), with the weight gradient in a launch of its own, beats
-// the launch that holds both.  The shared launch keeps all compute units busy to its end and hides the fp32 gradients' reads; the
-// small tiles read every expert's weights once where 64-row tiles read them twice, do not compute columns that do not exist, and
-// have a deep reduction done by many workgroups instead of few.  Both sides' times of 26 drawn layers:
-//   * 56 to 96 rows per expert, K above 1024: 61 rows, 111 experts, d 1408, h 2144: 372 -> 330 (dZ with dW2) and 441 -> 345 us (dXs with
-//     dW1); 64 rows, 64 experts, d 1024, h 2048: 157 -> 139; K 1024, 256 experts, d 512: 137 -> 140.  Accumulating in fp32: 198 -> 213.
-//   * widths that fill 256-wide tiles badly: 34 rows, 97 experts, 544 columns: 81 -> 67; 16 rows, 65 experts, 800 columns: 115 -> 92.
-//   * a quarter of a round of big tiles with a deep reduction: 250 rows, 8 experts, d 768, h 3072: 105 -> 95; 90 rows, 7 experts, d 320,
-//     h 2432: 39 -> 29; a whole round and more: 174 -> 239 (512 rows, 16 experts, d 1024, h 4096).
-inline bool tile_beats_pair(const GemmArgs& a)
-{
-    const long cols = (a.Nout + 255) / 256, big = (a.M / 256 + a.E / 2) * cols;
-    if (a.M > 0 && big <= 64 && a.K >= 2048) return true;
-    if (a.M <= 0 || a.M >= 96L * a.E || !a.stream_out || (a.accumulate && a.out_f32)) return false;   // (up to 48 MB of weights a launch more costs what it saves)
-    return (a.M > 56L * a.E && a.K > 1024) || cols * 256 * 4 >= (long)a.Nout * 5;
-}
 // Points the control-block fields of a GemmArgs at a workspace's control block.
 inline void set_control(GemmArgs& a, char* ws, const WsLayout& L)
 {

@@ -58,8 +58,6 @@
 namespace moe {
 namespace sk {
 
-constexpr int kMinSplitDepth = 16 * 64;         // a stream-K piece is at least this deep (16 blocks of 64): handing a partial sum on costs
-                                                // about as much time as 6 such blocks, and the hand-overs of one tile form a chain
 constexpr int kActLo = (127 - 11) << 7;         // bf16 bit pattern of 2^-11
 constexpr int kActHi = (127 + 3) << 7;          // bf16 bit pattern of 2^3
 constexpr int kActEntries = kActHi - kActLo;    // table entries per sign
@@ -83,6 +81,7 @@ struct Cfg {
     static constexpr int SMEM = RING + PATCH_BYTES + TABLE_BYTES + NEXT_BYTES;
     static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "tile must split evenly over waves");
     static_assert(SMEM <= 160 * 1024, "LDS budget");
+    static_assert(BM <= kMaxTileRows && BN <= kMaxTileRows, "reach of the loads' 32-bit offsets");
 };
 
 // Entry i of the activation table: Phi(z) (forward) or Phi(z) + z phi(z) (backward) at the bf16 value whose
@@ -1072,7 +1071,7 @@ void launch_cls_cfg(const GemmArgs& a, hipStream_t st)
 template <int KIND, int STAGES, int BK>
 void launch_cls(const GemmArgs& a, hipStream_t st)
 {
-    if (a.K < 2 * kMinSplitDepth) launch_cls_cfg<KIND, STAGES, BK, true>(a, st);
+    if (shallow(a)) launch_cls_cfg<KIND, STAGES, BK, true>(a, st);
     else launch_cls_cfg<KIND, STAGES, BK, false>(a, st);
 }
 
@@ -1091,12 +1090,12 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
     // tile: their tile spans the weight matrix, not the expert's rows.)
     // Otherwise the rows kinds run in two size classes (launch_cls): an expert's last few rows in 128 x 512 tiles.
     if constexpr (KIND != kColsT) {
-        if (!offsets_fit(a)) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64, true>(a, st); return; }
-        if constexpr (KIND == kRowsNN || KIND == kRowsNN_GeLU) {
-            if (tile_pays(a)) { launch_tile<KIND>(a, st); return; }
-        } else {
-            if (tile_beats_pair(a)) { launch_tile<KIND>(a, st); return; }
-            if (a.M < 96L * a.E) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64>(a, st); return; }
+        constexpr bool FORWARD = KIND == kRowsNN || KIND == kRowsNN_GeLU;
+        const Route to = route(a, FORWARD);
+        if (to == Route::kWide) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64, true>(a, st); return; }
+        if (to == Route::kSmallTiles) { launch_tile<KIND>(a, st); return; }
+        if constexpr (!FORWARD) {
+            if (to == Route::kTiles64) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64>(a, st); return; }
         }
         if (!a.cls) { fail_launch("grouped GEMM: the plan step's size-class tables are missing"); return; }
         if constexpr (KIND == kRowsNN) launch_cls<KIND, 4, 32>(a, st);
@@ -1126,8 +1125,8 @@ void launch_pair_cfg(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
 
 template <int KIND> void launch_pair_kind(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
 {
-    if (rows.M < 96L * rows.E) launch_pair_cfg<KIND, false, false>(rows, cols, st);   // as in launch_kind
-    else if (rows.K < 2 * kMinSplitDepth) launch_pair_cfg<KIND, true, true>(rows, cols, st);
+    if (few_rows(rows)) launch_pair_cfg<KIND, false, false>(rows, cols, st);
+    else if (shallow(rows)) launch_pair_cfg<KIND, true, true>(rows, cols, st);
     else launch_pair_cfg<KIND, true, false>(rows, cols, st);
 }
 }  // namespace sk

@@ -44,17 +44,10 @@ static int spin_limit()
     return s && *s ? atoi(s) : sk::kSpinLimit;
 }
 
-// With few tiles per workgroup the ragged end of a rows-kind launch (a quarter to half a tile per workgroup) and the
-// launch gap are worth more than the counter's round trips; measured, the pair wins up to about 8 tiles per
-// workgroup (C1: -3 % per step, C2: -1.4 %) and loses 0.5 % at 34 (C4).
 bool ggemm_pair_pays(const GemmArgs& rows)
 {
     const int wgs = sk::persistent_wgs();
-    if (wgs < 8) return false;
-    if (!offsets_fit(rows)) return false;
-    if (tile_beats_pair(rows)) return false;
-    const long row_tiles = rows.M / 256 + rows.E / 2, col_tiles = (rows.Nout + 255) / 256;
-    return row_tiles * col_tiles <= 8L * wgs;
+    return wgs >= 8 && pair_pays(rows, wgs);
 }
 
 void launch_ggemm_pair_bf16_sk(const GemmArgs& rows_, const GemmArgs& cols_, hipStream_t st)

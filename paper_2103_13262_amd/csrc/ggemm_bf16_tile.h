@@ -21,7 +21,7 @@
 namespace moe {
 namespace sk {
 
-constexpr int kTileCols = 128, kTileDepth = 64;    // columns of a tile; reduction indices of a block
+constexpr int kTileDepth = 64;    // reduction indices of a block
 
 template <int KIND, int BM_, int STAGES_> struct TileCfg {
     static constexpr int BM = BM_, BN = kTileCols, BK = kTileDepth, NW = 4, NT = 256, STAGES = STAGES_;
@@ -325,13 +325,6 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
     }
 }
 
-// At most so many tiles of BM rows.
-inline long most_tiles(const GemmArgs& a, int BM)
-{
-    const long touched = std::min<long>(a.E, a.M);
-    return (a.M + touched * (BM - 1)) / BM * ((a.Nout + kTileCols - 1) / kTileCols);
-}
-
 template <int KIND, int BM, int STAGES, int OCC>
 void launch_tile_cfg(const GemmArgs& a, hipStream_t st)
 {
@@ -352,33 +345,9 @@ void launch_tile_cfg(const GemmArgs& a, hipStream_t st)
     hipLaunchKernelGGL(kern, dim3((unsigned)((units + 7) / 8 * 8)), dim3(C::NT), C::SMEM, st, a, (a.Nout + C::BN - 1) / C::BN, (int)slices);
 }
 
-// Whether a forward product is better off in these tiles than in the persistent kernels'.  The lines come from both sides' times of FC1
-// and FC2 of 130 drawn layers (1 to 32000 tokens, 2 to 254 experts, d 256 to 2048, h 512 to 8192, launch included):
-//   * up to 96 rows per expert: 1.1 to 2 times as fast (64 rows, 256 experts, d 512, h 1024: FC1 96 -> 83, FC2 74 -> 68 us; 64 experts,
-//     d 1024, h 2048: 80 -> 66 and 72 -> 55; 8 tokens, 16 experts, d 1024, h 4096: 25 -> 23 and 33 -> 24; 7 tokens: 26 -> 13);
-//   * more rows, but less than half a round of 256 x 256 tiles, or less than a whole one with a shallow reduction, where the big
-//     tiles leave compute units idle and the last pieces' phase is as long as the tiles' (250 rows, 8 experts, d 768, h 3072: 55 -> 33
-//     and 59 -> 42 us; beyond: 430 rows, 5 experts, d 800, h 2112, a whole round with K 1024: 49 -> 64);
-//   * widths that fill 256-wide tiles badly (a fifth more columns computed than there are), up to three rounds of them (290 rows,
-//     222 experts, K 1088, 384 columns: 125 -> 107 us).
-inline bool tile_pays(const GemmArgs& a)
-{
-    if (a.M < 96L * a.E) return true;
-    const long cols = (a.Nout + 255) / 256, big = (a.M / 256 + a.E / 2) * cols;
-    if (a.spin_limit < 0) return false;      // (waits that are given up at once, the tests' way through that path: nothing waits in these tiles)
-    return big <= 128 || (big <= 192 && a.K <= 1536) || (big <= 256 && a.K <= 512) || (big <= 768 && cols * 256 * 5 >= (long)a.Nout * 6);
-}
-
-// The tile's height: an expert's rows in one tile, or its weights are read once more for each (with a mean of 56 rows a tile of 64 still
-// holds most experts'); 32 rows only for a handful, where more workgroups fit a compute unit (3 rows, 96 experts, d 480, h 2080: 42 and
-// 41 us against 46 and 42 in tiles of 64; 34 rows: 33 and 31 against 28 and 26; 82 rows, 13 experts, d 1984, h 3392: 82 and 68 in
-// tiles of 32, 65 and 63 of 64, 55 and 60 of 128).  Fewer tiles than compute units: smaller ones as well, since a slice of a
-// reduction costs its sums' way through memory (63 rows, 4 experts, d 1728, h 2016: 24 and 22 us in tiles of 64, 16 and 15 of 32).
 template <int KIND> void launch_tile(const GemmArgs& a, hipStream_t st)
 {
-    const long avg = a.M / std::min<long>(a.E, a.M);
-    int BM = avg <= 8 ? 32 : avg <= 56 ? 64 : 128;
-    while (BM > 32 && most_tiles(a, BM) < 200) BM /= 2;
+    const int BM = small_tile_height(a);
     if (BM == 32) launch_tile_cfg<KIND, 32, 2, 4>(a, st);
     else if (BM == 64) launch_tile_cfg<KIND, 64, 2, 3>(a, st);
     else launch_tile_cfg<KIND, 128, 2, 2>(a, st);

@@ -1,0 +1,101 @@
+// Which kernels a bf16 product runs in (internal; compiled for the host as well).  The host decides from sizes alone, since it does not know
+// the experts' row counts; a "round" below is one 256 x 256 tile for each of 256 workgroups.
+// Product: anything with the fields M (rows), E (experts), K (reduction), Nout (columns), stream_out, accumulate and out_f32 of GemmArgs.
+#pragma once
+#include <algorithm>
+
+namespace moe {
+
+// Whether a lane's place in a block of an operand fits 32 bits (setup_offsets): a block spans at most kMaxTileRows rows of the operand, so
+// it does for all but rows of millions of values (512 rows of 2^22 values are 4 GB).  (Gathered rows lie anywhere in X: moe_forward gathers only
+// from less than 4 GB.)
+constexpr int kMaxTileRows = 512;
+template <class Product> constexpr bool offsets_fit(const Product& a) { return a.K < (1 << 22) && a.Nout < (1 << 22); }
+
+// Many small experts: the rows kinds that are not in the small tiles run in 64 x 256 tiles, otherwise in two size classes (GemmArgs::cls).
+template <class Product> constexpr bool few_rows(const Product& a) { return a.M < 96L * a.E; }
+
+// Columns of 256, and about how many 256 x 256 tiles the rows make.
+template <class Product> constexpr long wide_columns(const Product& a) { return (a.Nout + 255) / 256; }
+template <class Product> constexpr long wide_tiles(const Product& a) { return (a.M / 256 + a.E / 2) * wide_columns(a); }
+
+constexpr int kMinSplitDepth = 16 * 64;         // a stream-K piece is at least this deep (16 blocks of 64): handing a partial sum on costs
+                                                // about as much time as 6 such blocks, and the hand-overs of one tile form a chain
+// Reductions that are never cut into pieces: few last pieces in 128 x 128 tiles with 128-deep blocks (ggemm_classes).
+template <class Product> constexpr bool shallow(const Product& a) { return a.K < 2 * kMinSplitDepth; }
+
+// Whether a forward product is better off in the small tiles (ggemm_bf16_tile.h) than in the persistent kernels'.  The lines come from both
+// sides' times of FC1 and FC2 of 130 drawn layers (1 to 32000 tokens, 2 to 254 experts, d 256 to 2048, h 512 to 8192, launch included):
+//   * up to 96 rows per expert: 1.1 to 2 times as fast (64 rows, 256 experts, d 512, h 1024: FC1 96 -> 83, FC2 74 -> 68 us; 64 experts,
+//     d 1024, h 2048: 80 -> 66 and 72 -> 55; 8 tokens, 16 experts, d 1024, h 4096: 25 -> 23 and 33 -> 24; 7 tokens: 26 -> 13);
+//   * more rows, but less than half a round of 256 x 256 tiles, or less than a whole one with a shallow reduction, where the big
+//     tiles leave compute units idle and the last pieces' phase is as long as the tiles' (250 rows, 8 experts, d 768, h 3072: 55 -> 33
+//     and 59 -> 42 us; beyond: 430 rows, 5 experts, d 800, h 2112, a whole round with K 1024: 49 -> 64);
+//   * widths that fill 256-wide tiles badly (a fifth more columns computed than there are), up to three rounds of them (290 rows,
+//     222 experts, K 1088, 384 columns: 125 -> 107 us).
+template <class Product> constexpr bool tile_pays(const Product& a)
+{
+    if (few_rows(a)) return true;
+    if (a.spin_limit < 0) return false;      // (waits that are given up at once, the tests' way through that path: nothing waits in these tiles)
+    const long big = wide_tiles(a);
+    return big <= 128 || (big <= 192 && a.K <= 1536) || (big <= 256 && a.K <= 512) || (big <= 768 && wide_columns(a) * 256 * 5 >= (long)a.Nout * 6);
+}
+
+// Backward products: whether a rows kind in small tiles, with the weight gradient in a launch of its own, beats
+// the launch that holds both.  The shared launch keeps all compute units busy to its end and hides the fp32 gradients' reads; the
+// small tiles read every expert's weights once where 64-row tiles read them twice, do not compute columns that do not exist, and
+// have a deep reduction done by many workgroups instead of few.  Both sides' times of 26 drawn layers:
+//   * 56 to 96 rows per expert, K above 1024: 61 rows, 111 experts, d 1408, h 2144: 372 -> 330 (dZ with dW2) and 441 -> 345 us (dXs with
+//     dW1); 64 rows, 64 experts, d 1024, h 2048: 157 -> 139; K 1024, 256 experts, d 512: 137 -> 140.  Accumulating in fp32: 198 -> 213.
+//   * widths that fill 256-wide tiles badly: 34 rows, 97 experts, 544 columns: 81 -> 67; 16 rows, 65 experts, 800 columns: 115 -> 92.
+//   * a quarter of a round of big tiles with a deep reduction: 250 rows, 8 experts, d 768, h 3072: 105 -> 95; 90 rows, 7 experts, d 320,
+//     h 2432: 39 -> 29; a whole round and more: 174 -> 239 (512 rows, 16 experts, d 1024, h 4096).
+template <class Product> constexpr bool tile_beats_pair(const Product& a)
+{
+    if (a.M <= 0) return false;
+    if (wide_tiles(a) <= 64 && a.K >= 2048) return true;
+    if (!few_rows(a) || !a.stream_out || (a.accumulate && a.out_f32)) return false;   // (up to 48 MB of weights a launch more costs what it saves)
+    return (a.M > 56L * a.E && a.K > 1024) || wide_columns(a) * 256 * 4 >= (long)a.Nout * 5;
+}
+
+// Backward products: whether a rows kind and a weight gradient share a launch.  With few tiles per workgroup the ragged end of a rows-kind launch
+// (a quarter to half a tile per workgroup) and the launch gap are worth more than the counter's round trips; measured, the pair wins up to
+// about 8 tiles per workgroup (4096 tokens, 16 experts, d 1024, h 4096: -3 % per step, 8192 tokens, 64 experts: -1.4 %) and loses 0.5 % at
+// 34 (32768 tokens, 32 experts, d 2048, h 8192).
+template <class Product> constexpr bool pair_pays(const Product& rows, int workgroups)
+{
+    return offsets_fit(rows) && !tile_beats_pair(rows) && wide_tiles(rows) <= 8L * workgroups;
+}
+
+// The kernel of a product that has a launch of its own, and of the first one of a pair (which never is kSmallTiles or kWide).
+enum class Route { kWide, kSmallTiles, kTiles64, kClasses };
+template <class Product> constexpr Route route(const Product& a, bool forward)
+{
+    if (!offsets_fit(a)) return Route::kWide;
+    if (forward ? tile_pays(a) : tile_beats_pair(a)) return Route::kSmallTiles;
+    return few_rows(a) ? Route::kTiles64 : Route::kClasses;      // (forward products never run in 64 x 256 tiles: tile_pays)
+}
+
+constexpr int kTileCols = 128;                  // columns of a small tile
+
+// At most so many small tiles of BM rows.
+template <class Product> constexpr long most_tiles(const Product& a, int BM)
+{
+    const long touched = std::min<long>(a.E, a.M);
+    return (a.M + touched * (BM - 1)) / BM * ((a.Nout + kTileCols - 1) / kTileCols);
+}
+
+// The small tile's height: an expert's rows in one tile, or its weights are read once more for each (with a mean of 56 rows a tile of 64 still
+// holds most experts'); 32 rows only for a handful, where more workgroups fit a compute unit (3 rows, 96 experts, d 480, h 2080: 42 and
+// 41 us against 46 and 42 in tiles of 64; 34 rows: 33 and 31 against 28 and 26; 82 rows, 13 experts, d 1984, h 3392: 82 and 68 in
+// tiles of 32, 65 and 63 of 64, 55 and 60 of 128).  Fewer tiles than compute units: smaller ones as well, since a slice of a
+// reduction costs its sums' way through memory (63 rows, 4 experts, d 1728, h 2016: 24 and 22 us in tiles of 64, 16 and 15 of 32).
+template <class Product> constexpr int small_tile_height(const Product& a)
+{
+    const long avg = a.M / std::min<long>(a.E, a.M);
+    int BM = avg <= 8 ? 32 : avg <= 56 ? 64 : 128;
+    while (BM > 32 && most_tiles(a, BM) < 200) BM /= 2;
+    return BM;
+}
+
+}  // namespace moe

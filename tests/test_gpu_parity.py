@@ -282,8 +282,8 @@ def _routed_inputs(w, counts):
 
 @pytest.mark.parametrize("d,h", [(64, 128), (512, 1024)])
 def test_row_counts_at_the_size_class_boundaries(d, h):
-    """The row products compute an expert's whole blocks of 256 rows and its last piece of at most 128 rows in
-    different tile shapes: experts with 0, 1, 128, 129, 256, 257, 384 and 385 rows sit on every side of those
+    """The backward row products compute an expert's whole blocks of 256 rows and its last piece of at most 128 rows in
+    different tile shapes (few tiles: the forward ones run in tiles of 32 to 128 rows; test_gpu_class_products.py has more): experts with 0, 1, 128, 129, 256, 257, 384 and 385 rows sit on every side of those
     limits (one narrow shape, where a wide tile is mostly columns that do not exist, and one with several tiles)."""
     counts = [0, 1, 128, 129, 256, 257, 384, 385]
     w = Workload(f"class_boundaries_{d}x{h}", sum(counts), d, h, len(counts), 1, "bf16", 0.0, 44)

@@ -8,9 +8,10 @@ pytestmark = pytest.mark.gpu
 
 
 # widths that end a 64-deep block in its middle, a 32-deep one at its end, a 128-deep one at each quarter; rows that end a 32-deep block at
-# every kind of place (the weight gradients' reductions), in small tiles (many experts), size classes and pairs
+# every kind of place (the weight gradients' reductions), in small tiles and pairs; the last case's forward products run in size classes
 @pytest.mark.parametrize("d,h,rows", [(96, 160, [33, 1, 300, 70, 0, 130]), (32, 96, [16, 17, 40, 15, 31, 2]), (224, 2144, [257, 129, 600, 383, 8, 24]),
-                                      (288, 64, [5, 6, 7, 9, 10, 11]), (2080, 96, [500, 270, 260, 390])])
+                                      (288, 64, [5, 6, 7, 9, 10, 11]), (2080, 96, [500, 270, 260, 390]),
+                                      (1120, 2080, [1025, 1407, 896, 1409, 1536, 799])])
 def test_the_next_experts_values_stay_out(d, h, rows):
     import torch
 
