@@ -36,7 +36,6 @@ template <class Product> constexpr bool shallow(const Product& a) { return a.K <
 template <class Product> constexpr bool tile_pays(const Product& a)
 {
     if (few_rows(a)) return true;
-    if (a.spin_limit < 0) return false;      // (waits that are given up at once, the tests' way through that path: nothing waits in these tiles)
     const long big = wide_tiles(a);
     return big <= 128 || (big <= 192 && a.K <= 1536) || (big <= 256 && a.K <= 512) || (big <= 768 && wide_columns(a) * 256 * 5 >= (long)a.Nout * 6);
 }
