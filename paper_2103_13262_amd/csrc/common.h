@@ -57,9 +57,9 @@ struct WsLayout {
     size_t gate_fail; // [1 + N] int32: how many tokens the fast gate kernel could not certify, then their ids (small batches: all)
     size_t WgT;       // [E][d] gate matrix transposed (written by the plan step for E > 32 and by the backward pass), element type = desc.dtype
     size_t zeros;     // the control block (see Ctl below): 1 KB of zeros, source of masked reduction rows, then the control words
-    size_t sk_flags;  // [kSkPhases][kMaxPersistentWgs] int32 "partial sum ready", zeroed with the zero page
+    size_t sk_flags;  // [kSkPhases][kMaxPersistentWgs] int32 "partial sum ready" or arrivals of slices, zeroed with the zero page
     size_t sk_error;  // int32: set if a wait for a partial sum ran out
-    size_t sk_part;   // [kSkPhases][kMaxPersistentWgs] fp32 tiles: partial sums of split output tiles (bf16 only)
+    size_t sk_part;   // [kSkPhases][kMaxPersistentWgs] fp32 tiles: partial sums of split output tiles, or of the small tiles' slices (bf16 only)
     size_t total;
     int nb;           // plan chunks = ceil(M / plan_chunk(M))
     long dwg_pieces;  // upper bound of 64-row pieces over all experts: floor(M/64) + E
@@ -69,11 +69,14 @@ struct WsLayout {
 // kinds): each phase has partial-sum buffers and flags of its own, so a workgroup that is already in the second
 // phase never overwrites a partial sum of the first that its successor has not read yet.
 constexpr int kSkPhases = 2;
+// A word of sk_flags is zero between launches, unless a wait was given up: then a "partial sum ready" that came too late stays set until the
+// next moe_plan.  The small tiles count their slices' arrivals in the bits below it, so that one left behind does not count as an arrival.
+constexpr int kPartialReady = 1 << 16;
 // The control block of a workspace, in int32 words from its start.  The plan step zeroes all of it and then sets
 // by_expert and skewed; the grouped products read and update the rest.
 enum Ctl {
     kCtlZeroPage = 0,                                          // 256 words of zeros
-    kCtlFlags = 256,                                           // [kSkPhases][kMaxPersistentWgs] "partial sum ready"
+    kCtlFlags = 256,                                           // [kSkPhases][kMaxPersistentWgs] kPartialReady, or arrivals of slices
     kCtlError = kCtlFlags + kSkPhases * kMaxPersistentWgs,     // status word: 1 if a bounded wait ran out
     kCtlByExpert = kCtlError + 1,                              // 1: the weight gradients give every XCD whole experts
     kCtlClock = kCtlError + 2,                                 // two int64: shader cycles, 100 MHz ticks (8-byte aligned)
@@ -220,8 +223,8 @@ struct GemmArgs {
     const int32_t* order;  // [E]
     const int32_t* cls;    // [kClsTables][E+1] size-class tables of the plan step, or NULL (bf16 row products only)
     const void* zeros;     // 1 KB of zeros
-    void* sk_part;         // partial-sum tiles, one per phase and persistent workgroup
-    int32_t* sk_flags;     // one flag per phase and persistent workgroup, all zero between launches
+    void* sk_part;         // partial sums: of the persistent kernels one tile per phase and workgroup; of the small tiles one per tile and slice
+    int32_t* sk_flags;     // one word per phase and persistent workgroup (kPartialReady) or per small tile (arrivals), see kPartialReady
     int32_t* sk_error;
     const int32_t* by_expert;  // 1: the weight-gradient products give every XCD whole experts (decided by the plan step)
     long long* clock_probe;    // [2]: shader cycles and 100 MHz ticks of workgroup 0 of the last launch

@@ -623,7 +623,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
                 }
         wait_vmcnt<0>();                       // this wave's partial sums have arrived ...
         __syncthreads();                       // ... and so have those of the other waves
-        if (tid == 0) __hip_atomic_store(g.sk_flags + sk_slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(g.sk_flags + sk_slot, kPartialReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     // Adds the partial sum of the workgroup just below (same XCD slot, one position lower).  The ring must be idle.
     auto add_predecessor = [&]() {
@@ -631,7 +631,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
         if (tid == 0) {
             int spins = 0;
             // (a negative limit gives every wait up at once, flag or no flag: the tests' way to walk through this path)
-            while (g.spin_limit < 0 || __hip_atomic_load(g.sk_flags + id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 1) {
+            while (g.spin_limit < 0 || __hip_atomic_load(g.sk_flags + id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kPartialReady) {
                 if (++spins > g.spin_limit) {   // cannot happen (see the header); kept so that every wave ends
                     __hip_atomic_store(g.sk_error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;

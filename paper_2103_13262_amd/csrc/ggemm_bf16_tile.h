@@ -200,7 +200,8 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // arrived where the XCDs' caches meet ...
         int* const s_last = (int*)smem;
         __syncthreads();                                   // ... for every wavefront (and the ring is idle)
-        if (tid == 0) *s_last = __hip_atomic_fetch_add(g.sk_flags + id, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == slices - 1;
+        if (tid == 0)
+            *s_last = (__hip_atomic_fetch_add(g.sk_flags + id, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kPartialReady - 1)) == slices - 1;
         __syncthreads();
         if (!*s_last) return;
         if (tid == 0) __hip_atomic_store(g.sk_flags + id, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // as the next launch expects
@@ -337,7 +338,7 @@ void launch_tile_cfg(const GemmArgs& a, hipStream_t st)
     // As many slices as keep all workgroups on the chip at once, and no more than 640 of them: every slice leaves its sums in memory (8
     // tokens, 16 experts, d 1024, h 4096, tiles of 32: FC1 and FC2 26 and 27 us cut for 1024 workgroups, 23.5 and 24 for 640).
     if (tiles <= kSkPhases * kMaxPersistentWgs) {       // (one arrival counter per tile)
-        slices = std::min<long>({std::min(256L * OCC, 640L) / tiles, 16, nk / 4});
+        slices = std::min<long>({std::min(256L * OCC, 640L) / tiles, 16, nk / 4});   // (far below kPartialReady arrivals)
         const long room = (long)(kSkPhases * kMaxPersistentWgs * kPartialBytesPerWg) / (tiles * BM * C::BN * 4);
         slices = std::max<long>(1, std::min(slices, room));
     }

@@ -136,3 +136,41 @@ def test_backward(d, h, rows):
             bound = 2 * (a.shape[1] + 1) * 2.0 ** -24 * size * f.abs() + ref.abs() * (2.0 ** -8 * f.abs() * 1.01 + (4e-4 if name == "dZ" else 0)) + 1e-30
             over = float(((got - ref * f).abs() - bound).max())
             assert over <= 0, (name, e, over)
+
+
+def test_slices_behind_waits_that_were_given_up(monkeypatch):
+    """FC2 is cut along its reduction; made to give its waits up, it leaves "partial sum ready" words behind (the step is reported invalid).  dZ of the
+    same step runs in small tiles of two slices whose arrivals are counted in the same words: its sums are whole all the same."""
+    import torch
+
+    N, d, h, E, dev = 768, 8192, 2048, 2, torch.device("cuda:0")
+    print(f"[case] N {N} d {d} h {h} E {E}", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(9)
+    normal = lambda shape, std=1.0: torch.empty(shape, dtype=torch.bfloat16, device=dev).normal_(0.0, std, generator=g)
+    X, Wg, W1, W2, dY = normal((N, d)), normal((d, E), 0.02), normal((E, d, h), 0.02), normal((E, h, d), 0.02), normal((N, d))
+    desc = B.make_desc(N, d, h, E, 2)
+    buf = B.MoeLayerBuffers(desc, dev)
+    ws, st = (buf.workspace, buf.ws_bytes), buf.stream()
+    Y, dX, dWg, dW1, dW2 = (torch.empty_like(t) for t in (dY, X, Wg, W1, W2))
+
+    def region(name, width):
+        off, n = B.moe_workspace_region(desc, name)
+        return buf.workspace[off:off + n].view(torch.bfloat16).view(2 * N, width)
+
+    B.moe_plan(desc, X, Wg, None, buf.plan, *ws, st)
+    monkeypatch.setenv("MOE355_SPIN_LIMIT", "-1")
+    B.moe_forward(desc, buf.plan, X, W1, W2, None, None, Y, *ws, st)
+    monkeypatch.delenv("MOE355_SPIN_LIMIT")
+    assert B.moe_check_status(desc, *ws, st) != 0
+    B.moe_backward(desc, buf.plan, X, Wg, W1, W2, dY, dX, dWg, torch.empty(4, device=dev), dW1, dW2, *ws, st)
+    Z, dYs, dZ = region("Z", h), region("dYs", d).float(), region("dZ", h)
+    z, ref = Z.double(), torch.empty((2 * N, h), device=dev)
+    size = torch.empty_like(ref)
+    for e in range(E):
+        seg = slice(int(buf.offsets[e]), int(buf.offsets[e + 1]))
+        ref[seg], size[seg] = dYs[seg] @ W2[e].float().T, dYs[seg].abs() @ W2[e].float().T.abs()
+    slope = (0.5 * torch.erfc(-z / 2 ** 0.5) + z * torch.exp(-0.5 * z * z) / (2 * torch.pi) ** 0.5).float()
+    # exact products; both sums round by at most depth * 2^-24 of the terms' size each, the result to bf16 by 2^-8 of itself
+    bound = 2 * (d + 1) * 2.0 ** -24 * size * slope.abs() + ref.abs() * (2.0 ** -8 * slope.abs() * 1.01 + 1.3e-7) + 1e-30
+    assert bool(((dZ.float() - ref * slope).abs() <= bound).all())
