@@ -916,7 +916,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
             constexpr std::false_type no;
             bool done = false;
             if constexpr (KIND == kColsT) {
-                done = true;
+                done = true;                     // (streaming stores whatever stream_out says: see store_out)
                 if (g.out_f32 && g.accumulate) epilogue_f32(fin, yes, yes);
                 else if (g.out_f32) epilogue_f32(fin, yes, no);
                 else if (g.accumulate) epilogue(fin, yes, yes);
