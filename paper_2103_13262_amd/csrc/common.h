@@ -212,6 +212,7 @@ struct GemmArgs {
     const void* bias; // kRowsNN_GeLU, kRowsNN: [E,Nout] added to the product (activation type), or NULL
     const int32_t* a_gather;  // kRows*: row r of the A operand is A[a_gather[r] / a_gather_div, :] (the scatter done on the fly), or NULL
     int a_gather_div;
+    int wide_gather;          // the gathered rows lie in 4 GB or more
     const int32_t* c_scatter; // kRowsNN: row r of the product is written to C[c_scatter[r], :] (the gather done on the fly; top-1 only), or NULL
     int K;            // kRows*: reduction width;  kColsT: K1 (rows of C[e])
     int Nout;         // kRows*: columns of C;     kColsT: K2 (columns of C[e])

@@ -961,19 +961,19 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void ggemm_sk_kernel(GemmArgs g, i
 // WHOLE: followed by another product in the same launch, so that no tile is cut.  (Known at compile time: with the code that cuts tiles
 // compiled in, a pair kernel needs 24 vector registers more than there are, and 12.6 MB of them pass through memory per launch.  A training
 // step of 4096 tokens, 16 experts, d 1024, h 4096: 623 us so, now 617; 8192 tokens, 64 experts, Zipf 1.2: 1446, 1431.)
-template <int KIND, int STAGES, int BK, bool DEEP, bool WHOLE>
+template <int KIND, int STAGES, int BK, bool DEEP, bool WHOLE, bool WIDE = false>
 __device__ __forceinline__ void ggemm_classes(const GemmArgs& g, int ntn_big, int ntn_small)
 {
     if constexpr (DEEP) {
-        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, false, WHOLE>(g, 0, ntn_big);
+        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, WIDE, WHOLE>(g, 0, ntn_big);
         __syncthreads();   // the first class's last epilogue is done with the LDS before the second lays it out anew
         // (only while the narrow tiles are at most one round: beyond that their number counts, not their length, and
         // the wide ones are fewer - measured on a skewed load with 44 last pieces: 7 % slower with the narrow ones)
         const int ntn_deep = (g.Nout + 127) / 128;
         if ((long)g.cls[kClsPSmall * (g.E + 1) + g.E] * ntn_deep <= (long)gridDim.x)
-            ggemm_sk_body<KIND, 2, 4, 2, 1, 2, 128, 2, false, WHOLE>(g, 0, ntn_deep);
+            ggemm_sk_body<KIND, 2, 4, 2, 1, 2, 128, 2, WIDE, WHOLE>(g, 0, ntn_deep);
         else
-            ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2, false, WHOLE>(g, 0, ntn_small);
+            ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2, WIDE, WHOLE>(g, 0, ntn_small);
         return;
     }
     const int W = gridDim.x >> 3;
@@ -986,16 +986,16 @@ __device__ __forceinline__ void ggemm_classes(const GemmArgs& g, int ntn_big, in
         // workgroups alone, whatever their number, a load whose big tiles nearly filled the last round gave two workgroups
         // of 32 all last pieces: dXs and dW1 of 16384 rows in 64 experts, Zipf 1.2, d 1024, h 4096, took 1123 us with one
         // seed and 415 with others.)
-        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, false, true>(g, 0, ntn_big);
+        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, WIDE, true>(g, 0, ntn_big);
         if (Ts == 0) return;
         __syncthreads();
         const int after = first_free_workgroup(Tb, W);
         const bool stay = last_pieces_stay((long)g.cls[kClsPSmall * (g.E + 1) + g.E] * ntn_big, after, W);   // (both kinds of tile are 256 wide)
-        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2, false, true>(g, 0, ntn_big, after, stay ? W - after : 0);
+        ggemm_sk_body<KIND, 2, 4, 2, 2, 2, 64, 2, WIDE, true>(g, 0, ntn_big, after, stay ? W - after : 0);
         return;
     }
-    if (Ts == 0) { ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big); return; }
-    if (Tb == 0) { ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2>(g, 0, ntn_small); return; }
+    if (Ts == 0) { ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, WIDE>(g, 0, ntn_big); return; }
+    if (Tb == 0) { ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2, WIDE>(g, 0, ntn_small); return; }
     if (g.K >= 2 * kMinSplitDepth && W >= 2 && Tb < 8L * W) {
         // Deep reductions with less than a round of tiles are cut into equal pieces over the workgroups, so a second
         // phase for the last pieces would leave most workgroups idle: the two classes run side by side instead, on
@@ -1005,19 +1005,19 @@ __device__ __forceinline__ void ggemm_classes(const GemmArgs& g, int ntn_big, in
         const long cs = Ts * 5, cb = Tb * 4;
         int ws = (int)((W * cs + (cs + cb) / 2) / (cs + cb));
         ws = ws < 1 ? 1 : ws > W - 1 ? W - 1 : ws;
-        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big, 0, W - ws);
-        ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2>(g, 0, ntn_small, W - ws, ws);   // (a workgroup runs one of the two)
+        ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, WIDE>(g, 0, ntn_big, 0, W - ws);
+        ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2, WIDE>(g, 0, ntn_small, W - ws, ws);   // (a workgroup runs one of the two)
         return;
     }
-    ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1>(g, 0, ntn_big);
+    ggemm_sk_body<KIND, 2, 4, 4, 2, STAGES, BK, 1, WIDE>(g, 0, ntn_big);
     __syncthreads();   // the first class's last epilogue is done with the LDS before the second lays it out anew
-    ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2>(g, 0, ntn_small);
+    ggemm_sk_body<KIND, 1, 8, 4, 2, 3, 32, 2, WIDE>(g, 0, ntn_small);
 }
 
-template <int KIND, int STAGES, int BK, bool DEEP>
+template <int KIND, int STAGES, int BK, bool DEEP, bool WIDE>
 __global__ __launch_bounds__(512, 1) void ggemm_cls_kernel(GemmArgs g, int ntn_big, int ntn_small)
 {
-    ggemm_classes<KIND, STAGES, BK, DEEP, false>(g, ntn_big, ntn_small);
+    ggemm_classes<KIND, STAGES, BK, DEEP, false, WIDE>(g, ntn_big, ntn_small);
 }
 
 // Two products that do not depend on each other in one launch: a rows kind, then the weight gradients with their
@@ -1053,14 +1053,14 @@ void launch_cfg(const GemmArgs& a, hipStream_t st)
 template <int KIND> using CfgWide = Cfg<KIND, 1, 8, 4, 2, 3, 32>;
 template <int KIND> using CfgDeep = Cfg<KIND, 2, 4, 2, 1, 2, 128>;
 
-template <int KIND, int STAGES, int BK, bool DEEP>
+template <int KIND, int STAGES, int BK, bool DEEP, bool WIDE>
 void launch_cls_cfg(const GemmArgs& a, hipStream_t st)
 {
     using C1 = Cfg<KIND, 2, 4, 4, 2, STAGES, BK>;
     using C2 = CfgWide<KIND>;
     static_assert((size_t)C2::BM * C2::BN * 4 <= kPartialBytesPerWg, "partial-sum buffer");
     constexpr int SMEM = std::max({C1::SMEM, C2::SMEM, DEEP ? CfgDeep<KIND>::SMEM : 0});
-    constexpr auto kern = ggemm_cls_kernel<KIND, STAGES, BK, DEEP>;
+    constexpr auto kern = ggemm_cls_kernel<KIND, STAGES, BK, DEEP, WIDE>;
     if (!allow_dynamic_lds<kern>(SMEM)) return;
     const int wgs = persistent_wgs();
     if (wgs < 8) return;
@@ -1071,8 +1071,9 @@ void launch_cls_cfg(const GemmArgs& a, hipStream_t st)
 template <int KIND, int STAGES, int BK>
 void launch_cls(const GemmArgs& a, hipStream_t st)
 {
-    if (shallow(a)) launch_cls_cfg<KIND, STAGES, BK, true>(a, st);
-    else launch_cls_cfg<KIND, STAGES, BK, false>(a, st);
+    if (!offsets_fit(a)) launch_cls_cfg<KIND, STAGES, BK, false, true>(a, st);   // (huge: few last pieces are not worth a kernel of their own)
+    else if (shallow(a)) launch_cls_cfg<KIND, STAGES, BK, true, false>(a, st);
+    else launch_cls_cfg<KIND, STAGES, BK, false, false>(a, st);
 }
 
 template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
@@ -1092,7 +1093,7 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
     if constexpr (KIND != kColsT) {
         constexpr bool FORWARD = KIND == kRowsNN || KIND == kRowsNN_GeLU;
         const Route to = route(a, FORWARD);
-        if (to == Route::kWide) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64, true>(a, st); return; }
+        if (to == Route::kWideTiles64) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64, true>(a, st); return; }
         if (to == Route::kSmallTiles) { launch_tile<KIND>(a, st); return; }
         if constexpr (!FORWARD) {
             if (to == Route::kTiles64) { launch_cfg<KIND, 2, 4, 1, 2, 3, 64>(a, st); return; }

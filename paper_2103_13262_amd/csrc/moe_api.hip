@@ -319,16 +319,13 @@ moe_status_t moe_forward(const moe_desc_t* desc, const moe_plan_t* plan, const v
 
     a.kind = kRowsNN_GeLU;  // Z = Xs W1[e],  H = GeLU(Z)
     a.A = X; a.a_gather = plan->perm; a.a_gather_div = D.k;
-    if (D.dtype == MOE_BF16 && ((size_t)D.N * D.d * 2) >> 32) {   // X of 4 GB and more: the loads' 32-bit offsets do not reach all rows
-        launch_scatter(D, X, plan->pos, ws + L.Xs, st);
-        a.A = ws + L.Xs; a.a_gather = nullptr;
-    }
+    a.wide_gather = ((size_t)D.N * D.d * 2) >> 32 != 0;
     a.B = W1; a.C = ws + L.Z; a.C2 = ws + L.H; a.K = D.d; a.Nout = D.h; a.bias = b1;
     { ScopedTimer tm(S_FC1, st); run_gemm(D, a, st); }
     if ((s = check_launch("expert layer 1")) != MOE_OK) return s;
 
     a.kind = kRowsNN;       // Ys = H W2[e]
-    a.A = ws + L.H; a.a_gather = nullptr; a.B = W2; a.C = ws + L.Ys; a.C2 = nullptr; a.K = D.h; a.Nout = D.d; a.bias = b2;
+    a.A = ws + L.H; a.a_gather = nullptr; a.wide_gather = 0; a.B = W2; a.C = ws + L.Ys; a.C2 = nullptr; a.K = D.h; a.Nout = D.d; a.bias = b2;
     // Top-1 with the score fixed at 1 (softmax over one logit): y is the one expert's output, so the second layer
     // writes row r straight to Y[perm[r]] - the gather of Section 4 done on the fly; Ys is not written.
     const bool direct = direct_top1(D);

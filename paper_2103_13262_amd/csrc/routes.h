@@ -1,16 +1,16 @@
 // Which kernels a bf16 product runs in (internal; compiled for the host as well).  The host decides from sizes alone, since it does not know
 // the experts' row counts; a "round" below is one 256 x 256 tile for each of 256 workgroups.
-// Product: anything with the fields M (rows), E (experts), K (reduction), Nout (columns), stream_out, accumulate and out_f32 of GemmArgs.
+// Product: anything with the fields M (rows), E (experts), K (reduction), Nout (columns), stream_out, accumulate, out_f32 and wide_gather of
+// GemmArgs.
 #pragma once
 #include <algorithm>
 
 namespace moe {
 
 // Whether a lane's place in a block of an operand fits 32 bits (setup_offsets): a block spans at most kMaxTileRows rows of the operand, so
-// it does for all but rows of millions of values (512 rows of 2^22 values are 4 GB).  (Gathered rows lie anywhere in X: moe_forward gathers only
-// from less than 4 GB.)
+// it does for all but rows of millions of values (512 rows of 2^22 values are 4 GB).  Gathered rows lie anywhere in X.
 constexpr int kMaxTileRows = 512;
-template <class Product> constexpr bool offsets_fit(const Product& a) { return a.K < (1 << 22) && a.Nout < (1 << 22); }
+template <class Product> constexpr bool offsets_fit(const Product& a) { return a.K < (1 << 22) && a.Nout < (1 << 22) && !a.wide_gather; }
 
 // Many small experts: the rows kinds that are not in the small tiles run in 64 x 256 tiles, otherwise in two size classes (GemmArgs::cls).
 template <class Product> constexpr bool few_rows(const Product& a) { return a.M < 96L * a.E; }
@@ -60,17 +60,24 @@ template <class Product> constexpr bool tile_beats_pair(const Product& a)
 // Backward products: whether a rows kind and a weight gradient share a launch.  With few tiles per workgroup the ragged end of a rows-kind launch
 // (a quarter to half a tile per workgroup) and the launch gap are worth more than the counter's round trips; measured, the pair wins up to
 // about 8 tiles per workgroup (4096 tokens, 16 experts, d 1024, h 4096: -3 % per step, 8192 tokens, 64 experts: -1.4 %) and loses 0.5 % at
-// 34 (32768 tokens, 32 experts, d 2048, h 8192).
+// 34 (32768 tokens, 32 experts, d 2048, h 8192).  (64-bit offsets: no pairs, whose tiles are never cut; a reduction over 2^22 and more has to be,
+// and that many columns are more than 8 tiles per workgroup.)
 template <class Product> constexpr bool pair_pays(const Product& rows, int workgroups)
 {
     return offsets_fit(rows) && !tile_beats_pair(rows) && wide_tiles(rows) <= 8L * workgroups;
 }
 
-// The kernel of a product that has a launch of its own, and of the first one of a pair (which never is kSmallTiles or kWide).
-enum class Route { kWide, kSmallTiles, kTiles64, kClasses };
+// 64-bit offsets, 96 rows per expert and more: whether the two size classes beat 64 x 256 tiles.  Millions of columns: always (one expert, 100 to
+// 3000 rows, 32 to 512 deep: 0.57 to 0.87 of the time).  A reduction over millions with few big tiles: no, since a tile is cut among the workgroups of one XCD only and
+// 64-row tiles are more (300 rows, 128 columns: FC2 1.8 ms against 14, dXs 2.4 against 13; 1000 rows, 256 columns, 3 tiles: 4.4 against 7.2 and
+// 6.8 against 7.2; 512 columns, 6 tiles: 8.7 against 7.1 and 12.5 against 7.4; 3000 rows, 256 columns: 13.2 against 13.9 and 20.7 against 13.7).
+template <class Product> constexpr bool wide_classes_pay(const Product& a) { return a.Nout >= (1 << 22) || wide_tiles(a) >= 6; }
+
+// The kernel of a product that has a launch of its own, and of the first one of a pair (kTiles64 or kClasses).
+enum class Route { kSmallTiles, kTiles64, kClasses, kWideTiles64, kWideClasses };
 template <class Product> constexpr Route route(const Product& a, bool forward)
 {
-    if (!offsets_fit(a)) return Route::kWide;
+    if (!offsets_fit(a)) return few_rows(a) || !wide_classes_pay(a) ? Route::kWideTiles64 : Route::kWideClasses;
     if (forward ? tile_pays(a) : tile_beats_pair(a)) return Route::kSmallTiles;
     return few_rows(a) ? Route::kTiles64 : Route::kClasses;      // (forward products never run in 64 x 256 tiles: tile_pays)
 }

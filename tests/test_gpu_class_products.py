@@ -26,7 +26,7 @@ ROUTES = r"""
 #include <cassert>
 #include "routes.h"
 using namespace moe;
-struct Product { long M; int E, K, Nout, stream_out, accumulate, out_f32; };
+struct Product { long M; int E, K, Nout, stream_out, accumulate, out_f32, wide_gather; };
 int main()
 {
     const Product cases[] = {%s};
@@ -35,6 +35,9 @@ int main()
         fc2.K = fc1.Nout; fc2.Nout = fc1.K;
         for (const Product& p : {fc1, fc2})
             for (bool forward : {true, false}) assert(route(p, forward) == Route::kClasses);
+        Product far = fc1;       // the same layer with its rows gathered from 4 GB and more
+        far.wide_gather = 1;
+        assert(route(far, true) == Route::kWideClasses);
         // dZ runs over d with h columns, dXs over h with d columns, each beside a weight gradient
         assert(pair_pays(fc1, 256) && pair_pays(fc2, 256));
     }
@@ -44,7 +47,7 @@ int main()
 
 
 def test_the_cases_reach_the_kernels_they_are_for(tmp_path):
-    sizes = ["{%d, %d, %d, %d, %d, 0, 0}" % (sum(rows), len(rows), d, h, len(rows) * d * h * 2 > 48 << 20) for d, h, rows, _, _ in CASES.values()]
+    sizes = ["{%d, %d, %d, %d, %d, 0, 0, 0}" % (sum(rows), len(rows), d, h, len(rows) * d * h * 2 > 48 << 20) for d, h, rows, _, _ in CASES.values()]
     (tmp_path / "routes.cpp").write_text(ROUTES % ", ".join(sizes))
     subprocess.run(["g++", "-std=c++20", "-I" + os.path.join(ROOT, "paper_2103_13262_amd", "csrc"), str(tmp_path / "routes.cpp"), "-o", str(tmp_path / "routes")], check=True)
     subprocess.run([str(tmp_path / "routes")], check=True)

@@ -1,5 +1,6 @@
 """bf16 products whose operands lie further apart than the main loop's 32-bit offsets reach: rows of 2^22 values and more (the
-kernels with 64-bit offsets), and an X of more than 4 GB (its rows are scattered first instead of being gathered on load)."""
+kernels with 64-bit offsets, in 64 x 256 tiles and in size classes), and rows gathered from an X of more than 4 GB (the same kernels: no scattered
+copy is written)."""
 import pytest
 
 from paper_2103_13262_amd import binding as B
@@ -14,10 +15,12 @@ def _close(got, a, b, what):
     assert bool(((got.float() - a @ b).abs() <= bound).all()), what
 
 
-def test_rows_of_millions_of_values():
+# 70: 64 x 256 tiles (below 96 rows per expert); 300: FC1 and dZ in size classes (a whole block and a last piece), FC2 and dXs, with few tiles, not
+@pytest.mark.parametrize("N", [70, 300])
+def test_rows_of_millions_of_values(N):
     import torch
 
-    N, d, h, E, dev = 70, 32, 1 << 22, 1, torch.device("cuda:0")
+    d, h, E, dev = 32, 1 << 22, 1, torch.device("cuda:0")
     print(f"[case] N {N} d {d} h {h}", flush=True)
     g = torch.Generator(device=dev)
     g.manual_seed(5)
@@ -49,6 +52,28 @@ def test_rows_of_millions_of_values():
     _close(dW2[0][at], H[:, at].T, dY, "dW2")
 
 
+def test_a_reduction_over_millions_in_size_classes():
+    import torch
+
+    N, d, h, E, dev = 1600, 32, 1 << 22, 1, torch.device("cuda:0")        # six whole blocks and a last piece of 64 rows
+    print(f"[case] N {N} d {d} h {h}", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(7)
+    normal = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device=dev).normal_(0.0, 0.3, generator=g)
+    at = torch.randint(0, h, (60,), generator=g, device=dev).unique()
+    X, Wg, W1 = normal(N, d), normal(d, E), torch.zeros((E, d, h), dtype=torch.bfloat16, device=dev)
+    W2 = torch.zeros((E, h, d), dtype=torch.bfloat16, device=dev)
+    W1[0][:, at], W2[0][at] = normal(d, len(at)), normal(len(at), d)
+    desc = B.make_desc(N, d, h, E, 1)
+    buf = B.MoeLayerBuffers(desc, dev)
+    ws, st = (buf.workspace, buf.ws_bytes), buf.stream()
+    Y = torch.full_like(X, 7)
+    B.moe_plan(desc, X, Wg, None, buf.plan, *ws, st)
+    B.moe_forward(desc, buf.plan, X, W1, W2, None, None, Y, *ws, st)
+    off, n = B.moe_workspace_region(desc, "H")
+    _close(Y, buf.workspace[off:off + n].view(torch.bfloat16).view(N, h)[:, at], W2[0][at], "Y")
+
+
 def test_x_of_more_than_4_gb():
     import torch
 
@@ -63,8 +88,12 @@ def test_x_of_more_than_4_gb():
     buf = B.MoeLayerBuffers(desc, dev)
     Y = torch.empty_like(X)
     ws, st = (buf.workspace, buf.ws_bytes), buf.stream()
+    off, n = B.moe_workspace_region(desc, "Xs")
+    Xs = buf.workspace[off:off + n].view(torch.int32)
+    Xs.fill_(0x5a5a5a5a)
     B.moe_plan(desc, X, Wg, None, buf.plan, *ws, st)
     B.moe_forward(desc, buf.plan, X, W1, W2, None, None, Y, *ws, st)
+    assert bool((Xs == 0x5a5a5a5a).all())
     at = torch.cat([torch.arange(40, device=dev), torch.arange(N - 40, N, device=dev), torch.randint(0, N, (400,), generator=g, device=dev)])
     row, expert = buf.pos[:N].long()[at], buf.topk_idx[:, 0].long()[at]
 
