@@ -45,7 +45,7 @@ struct WsLayout {
     size_t hist;      // [nb][E] int32: per plan-chunk histogram
     size_t dwg_part;  // [pieces][d] float: partial sums of dWg over pieces of 64 rows
     size_t dbg_part;  // [pieces] float
-    size_t bias_part; // [pieces][max(d,h)] float: partial column sums for the expert-bias gradients
+    size_t bias_part; // [pieces][h] float: partial column sums for the first layer's expert-bias gradients (the second's: dwg_part)
     // only with desc.score_all or desc.balance_stats:
     size_t logits;    // [N][E] double: the gate logits, then (same place) the gate probabilities
     size_t prob_part; // [ceil(N/kBalanceChunk)][E] double: sums of the gate probabilities by chunk of tokens
@@ -56,8 +56,8 @@ struct WsLayout {
     int dense_chunk, dense_chunks;
     size_t gate_fail; // [1 + N] int32: how many tokens the fast gate kernel could not certify, then their ids (small batches: all)
     size_t WgT;       // [E][d] gate matrix transposed (written by the plan step for E > 32 and by the backward pass), element type = desc.dtype
-    size_t zeros;     // the control block (see Ctl below): 1 KB of zeros, source of masked reduction rows, then the control words
-    size_t sk_flags;  // [kSkPhases][kMaxPersistentWgs] int32 "partial sum ready" or arrivals of slices, zeroed with the zero page
+    size_t control;   // the control block (see Ctl below)
+    size_t sk_flags;  // [kSkPhases][kMaxPersistentWgs] int32 "partial sum ready" or arrivals of slices
     size_t sk_error;  // int32: set if a wait for a partial sum ran out
     size_t sk_part;   // [kSkPhases][kMaxPersistentWgs] fp32 tiles: partial sums of split output tiles, or of the small tiles' slices (bf16 only)
     size_t total;
@@ -75,8 +75,7 @@ constexpr int kPartialReady = 1 << 16;
 // The control block of a workspace, in int32 words from its start.  The plan step zeroes all of it and then sets
 // by_expert and skewed; the grouped products read and update the rest.
 enum Ctl {
-    kCtlZeroPage = 0,                                          // 256 words of zeros
-    kCtlFlags = 256,                                           // [kSkPhases][kMaxPersistentWgs] kPartialReady, or arrivals of slices
+    kCtlFlags = 0,                                             // [kSkPhases][kMaxPersistentWgs] kPartialReady, or arrivals of slices
     kCtlError = kCtlFlags + kSkPhases * kMaxPersistentWgs,     // status word: 1 if a bounded wait ran out
     kCtlByExpert = kCtlError + 1,                              // 1: the weight gradients give every XCD whole experts
     kCtlClock = kCtlError + 2,                                 // two int64: shader cycles, 100 MHz ticks (8-byte aligned)
@@ -85,7 +84,7 @@ enum Ctl {
     kCtlWords = kCtlError + 32
 };
 static_assert(kCtlClock % 2 == 0 && kCtlWords <= 1024, "clock words 8-byte aligned; one 1024-thread workgroup zeroes the block");
-constexpr size_t kZeroedBytes = kCtlWords * sizeof(int32_t);
+constexpr size_t kControlBytes = kCtlWords * sizeof(int32_t);
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline size_t dtype_size(int dt) { return dt == MOE_BF16 ? 2 : 4; }
 
@@ -111,7 +110,7 @@ inline WsLayout ws_layout(const moe_desc_t& D)
     L.dwg_pieces = (long)(M / 64) + D.E;
     L.dwg_part = take((size_t)L.dwg_pieces * D.d * sizeof(float));
     L.dbg_part = take((size_t)L.dwg_pieces * sizeof(float));
-    L.bias_part = take((size_t)L.dwg_pieces * (D.d > D.h ? D.d : D.h) * sizeof(float));
+    L.bias_part = take((size_t)L.dwg_pieces * D.h * sizeof(float));
     L.gate_fail = take(((size_t)D.N + 1) * sizeof(int32_t));
     L.WgT = take((size_t)D.E * D.d * b);
     // chunks of the dense weight gradient: as long as it takes to give two compute-unit loads of 64 x 64 tiles, 64 to 512 tokens
@@ -134,9 +133,9 @@ inline WsLayout ws_layout(const moe_desc_t& D)
         const size_t least = before_scores + (size_t)D.N * (12 * (size_t)D.E + 4 * (size_t)D.d);
         if (o < least) o = (least + 255) / 256 * 256;
     }
-    L.zeros = take(kZeroedBytes);
-    L.sk_flags = L.zeros + kCtlFlags * sizeof(int32_t);
-    L.sk_error = L.zeros + kCtlError * sizeof(int32_t);
+    L.control = take(kControlBytes);
+    L.sk_flags = L.control + kCtlFlags * sizeof(int32_t);
+    L.sk_error = L.control + kCtlError * sizeof(int32_t);
     L.sk_part = take(D.dtype == MOE_BF16 ? (size_t)kSkPhases * kMaxPersistentWgs * kPartialBytesPerWg : 0);
     L.total = o;
     return L;
@@ -223,7 +222,6 @@ struct GemmArgs {
     const int32_t* tileP;  // [4][E+1]
     const int32_t* order;  // [E]
     const int32_t* cls;    // [kClsTables][E+1] size-class tables of the plan step, or NULL (bf16 row products only)
-    const void* zeros;     // 1 KB of zeros
     void* sk_part;         // partial sums: of the persistent kernels one tile per phase and workgroup; of the small tiles one per tile and slice
     int32_t* sk_flags;     // one word per phase and persistent workgroup (kPartialReady) or per small tile (arrivals), see kPartialReady
     int32_t* sk_error;
@@ -240,8 +238,7 @@ struct GemmArgs {
 // Points the control-block fields of a GemmArgs at a workspace's control block.
 inline void set_control(GemmArgs& a, char* ws, const WsLayout& L)
 {
-    int32_t* ctl = (int32_t*)(ws + L.zeros);
-    a.zeros = ctl + kCtlZeroPage;
+    int32_t* ctl = (int32_t*)(ws + L.control);
     a.sk_part = ws + L.sk_part;
     a.sk_flags = ctl + kCtlFlags;
     a.sk_error = ctl + kCtlError;

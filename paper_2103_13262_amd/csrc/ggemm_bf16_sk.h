@@ -12,7 +12,8 @@
 //     last block writes the tile.  Every workgroup handles the piece at the end of its range first, and a
 //     workgroup waits only for the one numbered just below it, so the waits cannot form a cycle.
 // The rows kinds compute an expert's whole blocks of 256 rows in 256 x 256 tiles and its last piece (at most 128 rows)
-// in 128 x 512 tiles, from the plan step's size-class tables (ggemm_cls_kernel); many small experts: 64 x 256 tiles.
+// in 128 x 512 tiles, from the plan step's size-class tables (ggemm_cls_kernel); many small experts: the backward ones that are not in
+// the small tiles of ggemm_bf16_tile.h in 64 x 256 tiles (routes.h says which product runs where).
 // The weight gradients (whole tiles only: their reduction runs over an expert's rows) take their tiles in fixed
 // rounds too, or - when the experts' sizes are strongly skewed, or when they follow another product inside one
 // launch (ggemm_pair_kernel) - from counters in memory, on demand.
@@ -232,7 +233,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
         const int rows_per = BM / f, row_off = slice * rows_per;
         const long r0 = (long)offsets_[e] + (long)mt * BM + row_off;
         const int n0 = nt * BN;
-        it.A = (const u16*)g.A + (g.a_gather ? 0 : r0 * g.K);  it.lda = g.K;   // (gathered rows: the base, see setup_ptrs)
+        it.A = (const u16*)g.A + (g.a_gather ? 0 : r0 * g.K);  it.lda = g.K;   // (gathered rows: the base, see setup_offsets)
         it.row0 = r0;
         const u16* Be = (const u16*)g.B + (size_t)e * g.K * g.Nout;
         if constexpr (C::B_TRANS) { it.B = Be + n0; it.ldb = g.Nout; }
@@ -553,11 +554,9 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
                 const int lslot = li % STAGES;
                 before_block(li + STAGES);
                 step(c1, std::true_type{}, (li + 1) % STAGES, 0, c0, cHalf, lslot);
-                if (li + 2 < nk) {                     // (always true here: STAGES is at least 2)
-                    first_steps((li + 1) % STAGES, std::true_type{}, lslot);
-                    qa += stepA_;  qb += stepB_;
-                    next_block(li + 1);
-                }
+                first_steps((li + 1) % STAGES, std::true_type{}, lslot);    // (li + 2 < nk: STAGES is at least 2)
+                qa += stepA_;  qb += stepB_;
+                next_block(li + 1);
             }
             for (; li + 2 < nk; ++li) {                // (rings of more than two slots: nothing left to request)
                 step(c1, std::true_type{}, (li + 1) % STAGES, 0, c0, c0, 0);

@@ -3,7 +3,7 @@
 //
 // With up to a hundred rows per expert a row product is a stream of weights: every expert's matrix is read once for a few
 // rows, and the time is the memory's as long as enough of it is on its way at any moment.  So the tiles are narrow (128 columns)
-// and the workgroups small (20 to 32 KB of ring): two to four of them on a compute unit hide each other's first loads, barriers and
+// and the workgroups small (rings of two slots, 40 to 64 KB): two to four of them on a compute unit hide each other's first loads, barriers and
 // epilogues, which cost a persistent workgroup with a 256-wide tile 8 to 10 us per launch, and the hardware hands the tiles out.
 //
 // A tile is BM rows x 128 columns; each wavefront computes 32 columns of all rows (BM 128: 64 of 64 rows) with

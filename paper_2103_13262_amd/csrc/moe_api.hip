@@ -230,7 +230,7 @@ moe_status_t moe_workspace_region(const moe_desc_t* desc, const char* name, size
         {"dXs", L.dXs, M * desc->d * b}, {"dl", L.dl, M * sizeof(float)},
         {"gate_uncertified", L.gate_fail, ((size_t)desc->N + 1) * sizeof(int32_t)},
         {"status", L.sk_error, sizeof(int32_t)},
-        {"clock", L.zeros + kCtlClock * sizeof(int32_t), 2 * sizeof(long long)},
+        {"clock", L.control + kCtlClock * sizeof(int32_t), 2 * sizeof(long long)},
     };
     for (const auto& r : regions)
         if (!strcmp(r.n, name)) { *offset = r.off; *bytes = r.len; return MOE_OK; }
