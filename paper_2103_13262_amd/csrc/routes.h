@@ -24,36 +24,70 @@ constexpr int kMinSplitDepth = 16 * 64;         // a stream-K piece is at least 
 // Reductions that are never cut into pieces: few last pieces in 128 x 128 tiles with 128-deep blocks (ggemm_classes).
 template <class Product> constexpr bool shallow(const Product& a) { return a.K < 2 * kMinSplitDepth; }
 
+constexpr int kTileCols = 128;                  // columns of a small tile
+
+// At most so many small tiles of BM rows.
+template <class Product> constexpr long most_tiles(const Product& a, int BM)
+{
+    const long touched = std::min<long>(a.E, a.M);
+    return (a.M + touched * (BM - 1)) / BM * ((a.Nout + kTileCols - 1) / kTileCols);
+}
+
+// One or two experts whose rows, at their mean, are whole blocks of 256 (or nearly: a last piece above 128 rows counts as a block): the big tiles have
+// no last pieces behind them then.
+template <class Product> constexpr bool whole_blocks(const Product& a)
+{
+    const long last = a.M / a.E % 256;
+    return a.E <= 2 && (last == 0 || last > 128);
+}
+// A fraction of the columns that 256-wide tiles compute is not there: a sixth, or nearly a quarter.
+template <class Product> constexpr bool sixth_missing(const Product& a) { return wide_columns(a) * 256 * 5 >= (long)a.Nout * 6; }
+template <class Product> constexpr bool quarter_missing(const Product& a) { return wide_columns(a) * 256 * 10 >= (long)a.Nout * 13; }
+
 // Whether a forward product is better off in the small tiles (ggemm_bf16_tile.h) than in the persistent kernels'.  The lines come from both
-// sides' times of FC1 and FC2 of 130 drawn layers (1 to 32000 tokens, 2 to 254 experts, d 256 to 2048, h 512 to 8192, launch included):
+// sides' times of FC1 and FC2 of 130 drawn layers (1 to 32000 tokens, 2 to 254 experts, d 256 to 2048, h 512 to 8192, launch included) and, above
+// 96 rows per expert, of 630 more (96 to 32000 tokens, 1 to 256 experts, d 256 to 4096):
 //   * up to 96 rows per expert: 1.1 to 2 times as fast (64 rows, 256 experts, d 512, h 1024: FC1 96 -> 83, FC2 74 -> 68 us; 64 experts,
 //     d 1024, h 2048: 80 -> 66 and 72 -> 55; 8 tokens, 16 experts, d 1024, h 4096: 25 -> 23 and 33 -> 24; 7 tokens: 26 -> 13);
 //   * more rows, but less than half a round of 256 x 256 tiles, or less than a whole one with a shallow reduction, where the big
 //     tiles leave compute units idle and the last pieces' phase is as long as the tiles' (250 rows, 8 experts, d 768, h 3072: 55 -> 33
-//     and 59 -> 42 us; beyond: 430 rows, 5 experts, d 800, h 2112, a whole round with K 1024: 49 -> 64);
-//   * widths that fill 256-wide tiles badly (a fifth more columns computed than there are), up to three rounds of them (290 rows,
-//     222 experts, K 1088, 384 columns: 125 -> 107 us).
+//     and 59 -> 42 us; beyond: 1024 rows, 4 experts, K 1024, 4096 columns: 72 -> 82);
+//   * widths that fill 256-wide tiles badly, up to three rounds of them: a sixth of the columns not there up to K 3000 (290 rows, 222 experts, K
+//     1088, 384 columns: 125 -> 107 us; 1498 rows, 9 experts, K 5056, 800 columns: 151 -> 187), nearly a quarter up to 6000 (476 rows, 64
+//     experts, K 4512, 288 columns: 223 -> 192; 1630 rows, 18 experts, K 7584, 352 columns: 214 -> 348).
+// Not so: reductions of 5000 and more with more than 250 small tiles, whose weights all row tiles read again (226 rows, 6 experts, K 7712, 3712 columns:
+// 127 -> 175 us), but for one expert with a last piece (5223 rows, K 7104, 896 columns: 163 -> 123); and one or two experts of whole blocks, where
+// the big tiles are at their best, from one round of small tiles on (512: 8192 rows, K 512, 2048 columns: 38 -> 48; K 4096, 1024 columns: 81 -> 93;
+// 2 experts, 1705 rows, K 896, 3488 columns: 35 -> 44).
+// Of those 630 layers' products 12 are slower by 5 to 21 % than in the kernels before the small tiles (without the last two rules 51, by up to
+// 67 %), and all of them take 0.76 of the time.
 template <class Product> constexpr bool tile_pays(const Product& a)
 {
     if (few_rows(a)) return true;
-    const long big = wide_tiles(a);
-    return big <= 128 || (big <= 192 && a.K <= 1536) || (big <= 256 && a.K <= 512) || (big <= 768 && wide_columns(a) * 256 * 5 >= (long)a.Nout * 6);
+    const long big = wide_tiles(a), small = most_tiles(a, 128);
+    if (whole_blocks(a) && !sixth_missing(a) && (small > 512 || (small >= 400 && a.K >= 4096))) return false;
+    const bool one_last_piece = a.E == 1 && !whole_blocks(a);
+    if (big <= 128 && (a.K < 5000 || small <= 250 || one_last_piece)) return true;
+    if ((big <= 192 && a.K <= 1536) || (big <= 256 && a.K <= 512)) return true;
+    return big <= 768 && ((sixth_missing(a) && a.K <= 3000 && a.M < 6000L * a.E) || (quarter_missing(a) && a.K <= 6000));
 }
 
 // Backward products: whether a rows kind in small tiles, with the weight gradient in a launch of its own, beats
 // the launch that holds both.  The shared launch keeps all compute units busy to its end and hides the fp32 gradients' reads; the
 // small tiles read every expert's weights once where 64-row tiles read them twice, do not compute columns that do not exist, and
-// have a deep reduction done by many workgroups instead of few.  Both sides' times of 26 drawn layers:
+// have a deep reduction done by many workgroups instead of few.  Both sides' times of 26 drawn layers and, for the last line, of 630 more:
 //   * 56 to 96 rows per expert, K above 1024: 61 rows, 111 experts, d 1408, h 2144: 372 -> 330 (dZ with dW2) and 441 -> 345 us (dXs with
 //     dW1); 64 rows, 64 experts, d 1024, h 2048: 157 -> 139; K 1024, 256 experts, d 512: 137 -> 140.  Accumulating in fp32: 198 -> 213.
 //   * widths that fill 256-wide tiles badly: 34 rows, 97 experts, 544 columns: 81 -> 67; 16 rows, 65 experts, 800 columns: 115 -> 92.
 //   * a quarter of a round of big tiles with a deep reduction: 250 rows, 8 experts, d 768, h 3072: 105 -> 95; 90 rows, 7 experts, d 320,
-//     h 2432: 39 -> 29; a whole round and more: 174 -> 239 (512 rows, 16 experts, d 1024, h 4096).
+//     h 2432: 39 -> 29; a whole round and more: 174 -> 239 (512 rows, 16 experts, d 1024, h 4096); 2500 rows per expert and more, or half a round
+//     of small tiles and K below 4096: 88 -> 135 (4096 rows, one expert, K 4096, 1024 columns), 60 -> 86 (2 experts, 2048 rows, K 2048, 1024 columns).
 template <class Product> constexpr bool tile_beats_pair(const Product& a)
 {
     if (a.M <= 0) return false;
+    if (!few_rows(a)) return wide_tiles(a) <= 64 && a.K >= 2048 && a.M < 2500L * a.E && (most_tiles(a, 128) < 256 || a.K >= 4096);
     if (wide_tiles(a) <= 64 && a.K >= 2048) return true;
-    if (!few_rows(a) || !a.stream_out || (a.accumulate && a.out_f32)) return false;   // (up to 48 MB of weights a launch more costs what it saves)
+    if (!a.stream_out || (a.accumulate && a.out_f32)) return false;   // (up to 48 MB of weights a launch more costs what it saves)
     return (a.M > 56L * a.E && a.K > 1024) || wide_columns(a) * 256 * 4 >= (long)a.Nout * 5;
 }
 
@@ -80,15 +114,6 @@ template <class Product> constexpr Route route(const Product& a, bool forward)
     if (!offsets_fit(a)) return few_rows(a) || !wide_classes_pay(a) ? Route::kWideTiles64 : Route::kWideClasses;
     if (forward ? tile_pays(a) : tile_beats_pair(a)) return Route::kSmallTiles;
     return few_rows(a) ? Route::kTiles64 : Route::kClasses;      // (forward products never run in 64 x 256 tiles: tile_pays)
-}
-
-constexpr int kTileCols = 128;                  // columns of a small tile
-
-// At most so many small tiles of BM rows.
-template <class Product> constexpr long most_tiles(const Product& a, int BM)
-{
-    const long touched = std::min<long>(a.E, a.M);
-    return (a.M + touched * (BM - 1)) / BM * ((a.Nout + kTileCols - 1) / kTileCols);
 }
 
 // The small tile's height: an expert's rows in one tile, or its weights are read once more for each (with a mean of 56 rows a tile of 64 still
