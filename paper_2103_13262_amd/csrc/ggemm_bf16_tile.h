@@ -89,7 +89,8 @@ __global__ __launch_bounds__(256, OCC) void ggemm_tile_kernel(GemmArgs g, int nt
     const u16* qa = scalar((const u16*)g.A + (g.a_gather ? 0 : row0 * g.K) + (long)kb0 * BK);
     const u16* qb = scalar((const u16*)g.B + (size_t)e * g.K * g.Nout + (C::B_TRANS ? (size_t)n0 : (size_t)n0 * g.K) + stepB * kb0);
     const unsigned lds_base = (unsigned)(uintptr_t)LDS_PTR(char, smem);
-    const bool once = mte == 1 && streaming;      // one tile alone reads these weights: streaming loads, which push nothing out of the caches
+    // one tile alone reads these weights: streaming loads, which push nothing out of the caches (forward: see stream_weights)
+    const bool once = mte == 1 && (C::B_TRANS ? g.stream_weights != 0 : streaming);
     auto issue = [&](int li) {                          // block li of this range into ring slot li % STAGES
         if (li == nk - 1 && rem < BK) {
             clamp_offsets<false, BM, 4, C::LA, BK>(rem, g.K, wave, lane, va);

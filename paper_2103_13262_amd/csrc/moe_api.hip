@@ -320,12 +320,14 @@ moe_status_t moe_forward(const moe_desc_t* desc, const moe_plan_t* plan, const v
     a.kind = kRowsNN_GeLU;  // Z = Xs W1[e],  H = GeLU(Z)
     a.A = X; a.a_gather = plan->perm; a.a_gather_div = D.k;
     a.wide_gather = ((size_t)D.N * D.d * 2) >> 32 != 0;
+    const double touched = touched_weights(D.N, D.k, D.E, 2.0 * D.E * D.d * D.h);
+    a.stream_weights = a.stream_out && stream_weights(false, touched);
     a.B = W1; a.C = ws + L.Z; a.C2 = ws + L.H; a.K = D.d; a.Nout = D.h; a.bias = b1;
     { ScopedTimer tm(S_FC1, st); run_gemm(D, a, st); }
     if ((s = check_launch("expert layer 1")) != MOE_OK) return s;
 
     a.kind = kRowsNN;       // Ys = H W2[e]
-    a.A = ws + L.H; a.a_gather = nullptr; a.wide_gather = 0; a.B = W2; a.C = ws + L.Ys; a.C2 = nullptr; a.K = D.h; a.Nout = D.d; a.bias = b2;
+    a.A = ws + L.H; a.a_gather = nullptr; a.wide_gather = 0; a.stream_weights = a.stream_out && stream_weights(true, touched); a.B = W2; a.C = ws + L.Ys; a.C2 = nullptr; a.K = D.h; a.Nout = D.d; a.bias = b2;
     // Top-1 with the score fixed at 1 (softmax over one logit): y is the one expert's output, so the second layer
     // writes row r straight to Y[perm[r]] - the gather of Section 4 done on the fly; Ys is not written.
     const bool direct = direct_top1(D);

@@ -4,6 +4,7 @@
 // GemmArgs.
 #pragma once
 #include <algorithm>
+#include <cmath>
 
 namespace moe {
 
@@ -115,6 +116,20 @@ template <class Product> constexpr Route route(const Product& a, bool forward)
     if (forward ? tile_pays(a) : tile_beats_pair(a)) return Route::kSmallTiles;
     return few_rows(a) ? Route::kTiles64 : Route::kClasses;      // (forward products never run in 64 x 256 tiles: tile_pays)
 }
+
+// Whether a forward product's small tiles request weights that one tile alone reads as streaming loads, which leave nothing of them in the
+// memory-side cache (256 MB).  Streaming is the faster way to read them (8 tokens, 16 experts, d 1024, h 4096: 53.8 us a pass, ordinary loads 58.9), but
+// what it leaves out is missing where it is read again soon: the second layer's weights first of all, with which the backward pass begins.  Few
+// enough to stay there beside those of other layers or steps, they come as ordinary loads.  Over 130 drawn layers below 96 rows per expert, three of
+// them in turn, against both streaming (us):
+//   * up to 40 MB touched per layer neither streams: a forward pass 0.90 to 1.0, a training step 0.86 to 1.04 (6 tokens, 13 experts, d 1600, h 1472,
+//     22 MB: 115 -> 99); one layer by itself: dXs with dW1 69 -> 49 (4 tokens, 31 experts, d 1248, h 2944, 27 MB);
+//   * up to 80 MB the first alone: 0.91 to 1.0 and 0.93 to 1.02 (32 tokens, 3 experts, d 1536, h 6208, 55 MB: 54 -> 51 and 143 -> 136);
+//   * beyond, the first alone makes a forward pass 1.0 to 1.11 times as long for a step of 0.94 to 1.04 (1024 tokens, 64 experts, d 1024, h 2048, 256
+//     MB: 142 -> 158 and 380 -> 395; 412 tokens, 32 experts, d 1312, h 1696, 136 MB: 78 -> 83 and 246 -> 236): both stream.
+// touched: bytes of one layer's experts that the tokens reach, if they choose evenly.
+inline double touched_weights(long tokens, int k, int E, double bytes) { return bytes * (1.0 - std::pow(1.0 - (double)k / E, (double)tokens)); }
+constexpr bool stream_weights(bool second_layer, double touched) { return touched > (second_layer ? 80.0 : 40.0) * (1 << 20); }
 
 // The small tile's height: an expert's rows in one tile, or its weights are read once more for each (with a mean of 56 rows a tile of 64 still
 // holds most experts'); 32 rows only for a handful, where more workgroups fit a compute unit (3 rows, 96 experts, d 480, h 2080: 42 and

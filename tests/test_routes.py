@@ -33,6 +33,11 @@ int main()
         p.Nout = 1 << 22;
         assert(!pair_pays(p, 256));
     }
+    // weights that one tile reads: few touched, neither layer's come as streaming loads, then the first's, then both
+    const double mb = 1 << 20;
+    assert(!stream_weights(false, 39 * mb) && stream_weights(false, 41 * mb) && !stream_weights(true, 79 * mb) && stream_weights(true, 81 * mb));
+    assert(touched_weights(1, 2, 16, 16.0) == 2.0 && touched_weights(100000, 1, 4, 100.0) == 100.0 && touched_weights(3, 4, 4, 8.0) == 8.0);
+    assert(std::abs(touched_weights(8, 2, 16, 16.0) - 16 * (1 - std::pow(0.875, 8))) < 1e-12);
     return 0;
 }
 """
