@@ -1079,8 +1079,10 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
 {
     // 256 x 256 tile, 8 waves of 128 x 64, and a 128 KB ring: two slots of 64-deep blocks, or four slots of 32-deep
     // blocks.  The finer ring keeps three quarters of itself in flight instead of half, which hides more of the
-    // operands' latency, at the price of twice as many barriers; measured, it is 5 % faster for the weight gradients
-    // and for FC2, even for FC1 and dXs, and 10 % slower for dH, so each kind gets its better one.
+    // operands' latency, at the price of twice as many barriers.  Four slots against two, us: FC2 1855 / 1960 (32768 tokens, 32 experts,
+    // d 2048, h 8192) and 101 / 104 (4096 tokens, 16 experts, d 1024, h 4096), weight gradients 1820 / 2100 and 1900 / 2210, dXs 2044 / 2006,
+    // dZ 2278 / 2275, FC1 2419 / 2485 and 113 / 115; so each kind has its better one but for FC1, whose two slots date from a main loop
+    // for which both were even.
     // (Two workgroups of 4 waves per compute unit, each on a 256 x 128 tile with 32-deep blocks, so that one computes
     // while the other waits or writes its tile, are 15-20 % slower: they move half as much again into LDS per flop.)
     // Many small experts (fewer than 96 rows on average): the forward products and some of the backward ones in the small tiles of
