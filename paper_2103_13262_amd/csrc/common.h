@@ -54,6 +54,8 @@ struct WsLayout {
     size_t dense_part;   // [dense_chunks][E][d] float: sums of dWg by chunk of dense_chunk tokens
     size_t dense_bpart;  // [dense_chunks][E] float: and of dbg
     int dense_chunk, dense_chunks;
+    size_t arrive;    // [E][arrive_cols] int32: how many pieces of an expert's sums have arrived, by column block (zeroed by the plan step; zero between launches)
+    int arrive_cols;
     size_t gate_fail; // [1 + N] int32: how many tokens the fast gate kernel could not certify, then their ids (small batches: all)
     size_t WgT;       // [E][d] gate matrix transposed (written by the plan step for E > 32 and by the backward pass), element type = desc.dtype
     size_t control;   // the control block (see Ctl below)
@@ -111,6 +113,8 @@ inline WsLayout ws_layout(const moe_desc_t& D)
     L.dwg_part = take((size_t)L.dwg_pieces * D.d * sizeof(float));
     L.dbg_part = take((size_t)L.dwg_pieces * sizeof(float));
     L.bias_part = take((size_t)L.dwg_pieces * D.h * sizeof(float));
+    L.arrive_cols = (int)((D.d * b / 16 + 63) / 64 + (D.h * b / 16 + 63) / 64);   // (both layers' bias sums side by side)
+    L.arrive = take((size_t)D.E * L.arrive_cols * sizeof(int32_t));
     L.gate_fail = take(((size_t)D.N + 1) * sizeof(int32_t));
     L.WgT = take((size_t)D.E * D.d * b);
     // chunks of the dense weight gradient: as long as it takes to give two compute-unit loads of 64 x 64 tiles, 64 to 512 tokens
@@ -180,11 +184,14 @@ struct GateDense {
     int E, stride;
 };
 void launch_dcombine(const moe_desc_t& D, const void* dY, const void* Ys, const float* topk_w,
-                     const int32_t* pos, void* dYs, float* dl, const GateDense& gate, const void* X, void* Xs, hipStream_t st);
-// (X, Xs: the scatter Xs[pos[a],:] = X[t,:] rides along, or NULL, NULL)
+                     const int32_t* pos, void* dYs, float* dl, const GateDense& gate, const void* X, void* Xs, const void* Wg, void* WgT, hipStream_t st);
+// (X, Xs: the scatter Xs[pos[a],:] = X[t,:] rides along, or NULL, NULL; Wg, WgT: the gate matrix transposed, likewise)
 void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
                      const float* dl, const int32_t* topk_idx, const int32_t* pos, const int32_t* perm,
                      const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws, hipStream_t st);
+void launch_gate_bwd_whole(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
+                           const float* dl, const int32_t* topk_idx, const int32_t* pos, const int32_t* perm,
+                           const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws, hipStream_t st);
 void launch_balance_stats(const moe_desc_t& D, const WsLayout& L, const int32_t* counts, float* fraction, float* mean_prob,
                           float* loss, char* ws, hipStream_t st);
 // launch_gate_bwd for scores over all experts: from the gradient of every logit (GateDense::R)

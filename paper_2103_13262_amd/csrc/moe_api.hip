@@ -374,7 +374,7 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
         if (D.score_all)
             gate = GateDense{(const double*)(ws + L.logits), plan->topk_idx, (float*)(ws + L.gate_R), D.E, gate_r_stride(D.E)};
         launch_dcombine(D, dY, direct_top1(D) ? nullptr : ws + L.Ys, plan->topk_w, plan->pos, ws + L.dYs, (float*)(ws + L.dl),
-                        gate, X, ws + L.Xs, st);
+                        gate, X, ws + L.Xs, Wg, D.score_all ? nullptr : ws + L.WgT, st);
         if ((s = check_launch("combine backward")) != MOE_OK) return s;
     }
 
@@ -442,8 +442,8 @@ moe_status_t moe_backward(const moe_desc_t* desc, const moe_plan_t* plan, const 
         ScopedTimer tm(S_GATEBWD, st);
         if (D.score_all) launch_gate_dense_bwd(D, L, X, Wg, ws + L.dXs, plan->pos, dX, dWg, dbg, ws, st);
         else
-            launch_gate_bwd(D, L, ws + L.Xs, ws + L.dXs, Wg, (const float*)(ws + L.dl), plan->topk_idx, plan->pos,
-                            plan->perm, plan->counts, plan->offsets, dX, dWg, dbg, ws, st);
+            launch_gate_bwd_whole(D, L, ws + L.Xs, ws + L.dXs, Wg, (const float*)(ws + L.dl), plan->topk_idx, plan->pos,
+                                  plan->perm, plan->counts, plan->offsets, dX, dWg, dbg, ws, st);
     }
     return check_launch("gate backward");
 }
@@ -526,7 +526,7 @@ moe_status_t moe_gather_backward(const moe_desc_t* desc, const moe_plan_t* plan,
     if (!dl || (reinterpret_cast<uintptr_t>(dl) & 3u)) { set_error("dl is NULL or not 4-byte aligned"); return MOE_ERR_INVALID_ARG; }
     if (desc->score_all) { set_error("moe_gather_backward / moe_scatter_backward carry the gradient of the selected experts only (score_all must be 0)"); return MOE_ERR_UNSUPPORTED; }
     if (desc->N == 0) return MOE_OK;
-    launch_dcombine(*desc, dY, Ys, plan->topk_w, plan->pos, dYs, dl, GateDense{}, nullptr, nullptr, (hipStream_t)stream);
+    launch_dcombine(*desc, dY, Ys, plan->topk_w, plan->pos, dYs, dl, GateDense{}, nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
     return check_launch("gather backward");
 }
 

@@ -79,7 +79,8 @@ __global__ __launch_bounds__(kThreads) void plan_place(const int32_t* __restrict
                                                        int E, int nbits, long M, int32_t* __restrict__ counts,
                                                        int32_t* __restrict__ offsets, int32_t* __restrict__ tileP,
                                                        int32_t* __restrict__ order, int32_t* __restrict__ cls,
-                                                       int32_t* __restrict__ control, int32_t* __restrict__ pos, int32_t* __restrict__ perm)
+                                                       int32_t* __restrict__ control, int32_t* __restrict__ arrive, int arrive_words, int32_t* __restrict__ pos,
+                                                       int32_t* __restrict__ perm)
 {
     extern __shared__ __align__(16) int smem_plan[];
     const int Ep = (E + 3) & ~3;
@@ -97,8 +98,11 @@ __global__ __launch_bounds__(kThreads) void plan_place(const int32_t* __restrict
         return e;
     };
     int ev = tables ? -1 : index(base + tid);       // first round, on its way while the counts are taken
-    // the control words of the grouped products
-    if (tables && tid < kCtlWords) control[tid] = 0;
+    // the control words of the grouped products, and the counters of the backward pass's sums
+    if (tables) {
+        if (tid < kCtlWords) control[tid] = 0;
+        for (int i = tid; i < arrive_words; i += kThreads) arrive[i] = 0;
+    }
     for (int e = tid; e < 2 * Ep; e += kThreads) s_total[e] = 0;
     __syncthreads();
     if (hist) {
@@ -290,7 +294,8 @@ void launch_plan(const moe_desc_t& D, const WsLayout& L, const int32_t* topk_idx
     if (!allow_dynamic_lds<plan_place>((2 + kWaves) * kMaxE * (int)sizeof(int))) return;
     hipLaunchKernelGGL(plan_place, dim3(L.nb + 1), dim3(kThreads), (2 + kWaves) * Ep * sizeof(int), st, topk_idx,
                        own ? (const int32_t*)nullptr : hist, L.nb, chunk, D.E, nbits, M, counts, offsets, (int32_t*)(ws + L.tileP),
-                       (int32_t*)(ws + L.order), (int32_t*)(ws + L.cls), (int32_t*)(ws + L.control), pos, perm);
+                       (int32_t*)(ws + L.order), (int32_t*)(ws + L.cls), (int32_t*)(ws + L.control), (int32_t*)(ws + L.arrive), D.E * L.arrive_cols,
+                       pos, perm);
 }
 
 }  // namespace moe

@@ -5,6 +5,8 @@
 // The four movements and the plan of 32768 tokens, d 2048, 32 experts, top-2, bf16: 597 -> 551 us since scatter goes by token,
 // rows are found with 32-bit divisions and the loads of a thread are issued together (2.9 TB/s of what has to move at least,
 // the gate's product included; a plain copy reaches 5.1).
+#include <algorithm>
+
 #include "common.h"
 
 namespace moe {
@@ -120,15 +122,27 @@ __global__ __launch_bounds__(256) void combine_rows(const void* __restrict__ Ys,
 //   (Ys == NULL: the expert outputs were not kept - top-1 with the score fixed at 1, where dl is exactly zero)
 //   Rides along (X != NULL): Xs[pos[a],:] = X[t,:], the scatter that the weight gradients of the first layer and of
 //   the gate read; the token's row is in hand anyway, and the backward pass saves a launch.
+//   Rides along as well (WgT != NULL): WgT[e][i] = Wg[i][e], which lets the gate's part of dX read a gate column as contiguous 16-byte
+//   pieces; spread over all workgroups (of which there are more than the tokens need where the matrix is large).
 //   KC = k where it is 1, 2 or 4, so that no branch stands between the slots' loads; 0: any k.
+template <typename T>
+__device__ __forceinline__ void transpose_gate(const T* __restrict__ Wg, T* __restrict__ WgT, int d, int E, long thread, long threads)
+{
+    for (long i = thread; i < (long)d * E; i += threads) {
+        const int e = (int)(i / d), row = (int)(i - (long)e * d);
+        WgT[i] = Wg[(size_t)row * E + e];
+    }
+}
 template <typename T, int KC>
 __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY, const void* __restrict__ Ys,
                                                      const float* __restrict__ topk_w,
                                                      const int32_t* __restrict__ pos, void* __restrict__ dYs,
                                                      float* __restrict__ dl, long N, int kArg, int cpr,
                                                      const GateDense gate,   // (R NULL: only the selected logits have a gradient)
-                                                     const uint4* __restrict__ X, uint4* __restrict__ Xs)
+                                                     const uint4* __restrict__ X, uint4* __restrict__ Xs,
+                                                     const T* __restrict__ Wg, T* __restrict__ WgT, int d, int E)
 {
+    if (WgT) transpose_gate(Wg, WgT, d, E, (long)blockIdx.x * 256 + threadIdx.x, (long)gridDim.x * 256);
     constexpr int V = Vec<T>::N, KM = KC > 0 ? KC : kMaxK;
     const int k = KC > 0 ? KC : kArg;
     const int lane = threadIdx.x & 63;
@@ -197,7 +211,7 @@ __global__ __launch_bounds__(256) void dcombine_rows(const void* __restrict__ dY
 
 // ---- dX[t,:] = sum_j dXs[pos[a],:] + sum_j dl[a] * Wg[:, idx[a]] ------------------------------
 // (K as for combine_rows)
-template <typename T, int K>
+template <typename T, int K, int NT>
 __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const void* __restrict__ dXs, const void* __restrict__ WgT,
                                                  const float* __restrict__ dl, const int32_t* __restrict__ topk_idx,
                                                  const int32_t* __restrict__ pos, void* __restrict__ dX, long N, int k,
@@ -205,7 +219,7 @@ __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const 
 {
     constexpr int V = Vec<T>::N;
     const long total = N * cpr;
-    for (long i = block * 256 + threadIdx.x; i < total; i += blocks * 256) {
+    for (long i = block * NT + threadIdx.x; i < total; i += blocks * NT) {
         long t;
         int c;
         split_piece(i, total, cpr, t, c);
@@ -255,8 +269,18 @@ __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const 
 // work per workgroup is the same however skewed the load is.  grid: piece_grid; each thread
 // owns one 16-byte column piece and walks the rows of its piece; a second kernel adds an expert's pieces
 // in ascending order.
-template <typename T>
-__device__ __forceinline__ void segment_partial(const void* __restrict__ Xs, const float* __restrict__ dl, const int32_t* __restrict__ perm,
+// 16 bytes to where the XCDs' caches meet.  (The wait states keep the next instruction from overwriting the data registers while the
+// store still reads them: the compiler sees to that for its own stores but cannot see into an assembly statement.)
+__device__ __forceinline__ void store_shared(float* p, const float4 v)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    const f32x4 w = {v.x, v.y, v.z, v.w};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 2" :: "v"(p), "v"(w) : "memory");
+}
+
+// SHARED: another workgroup of the launch reads the sums (segment_arrive).  Returns the piece's segment, e = -1 past the last piece.
+template <typename T, bool SHARED>
+__device__ __forceinline__ Segment segment_partial(const void* __restrict__ Xs, const float* __restrict__ dl, const int32_t* __restrict__ perm,
                                                 const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
                                                 const int32_t* __restrict__ P64, float* __restrict__ part, float* __restrict__ bpart, int E,
                                                 int d, int cpr, int piece, int col)
@@ -270,11 +294,11 @@ __device__ __forceinline__ void segment_partial(const void* __restrict__ Xs, con
     Segment sg;
     if (E <= 256) {
         sg = find_segment(P64, E, piece, counts, offsets);   // (a piece past the last finds the last expert)
-        if (piece >= pieces) return;      // uniform over the workgroup
+        if (piece >= pieces) return Segment{-1, 0, 0, 0, 0};      // uniform over the workgroup
     } else {
         // Beyond 256 experts find_segment takes several round trips, which the many pieces past the last would wait for too:
         // those leave first, and the search is one of halves over scalar loads.
-        if (piece >= pieces) return;
+        if (piece >= pieces) return Segment{-1, 0, 0, 0, 0};
         int lo = 0, hi = E;
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -331,14 +355,59 @@ __device__ __forceinline__ void segment_partial(const void* __restrict__ Xs, con
 #pragma unroll
             for (int u = 0; u < V; ++u) acc[u] += s_acc[g][ct][u];
         float* dst = part + (size_t)piece * d + (size_t)c * V;
+        if constexpr (SHARED) {
 #pragma unroll
-        for (int u = 0; u < V; ++u) dst[u] = acc[u];
+            for (int u = 0; u < V; u += 4) store_shared(dst + u, make_float4(acc[u], acc[u + 1], acc[u + 2], acc[u + 3]));
+        } else {
+#pragma unroll
+            for (int u = 0; u < V; ++u) dst[u] = acc[u];
+        }
         if (c == 0 && bpart) {
             float sdl = 0.f;
             for (int i = 0; i < 64; ++i) sdl += s_g[i];
-            bpart[piece] = sdl;
+            if constexpr (SHARED) __hip_atomic_store(bpart + piece, sdl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else bpart[piece] = sdl;
         }
     }
+    return sg;
+}
+
+// The pieces' sums of one launch added up in the same launch: the workgroup that arrives last of an expert's pieces (in one column
+// block) adds all of them, in ascending order whoever it is.  The sums are written and read at agent scope, where the XCDs'
+// caches meet.  arrive: a counter per expert and column block, zero between launches.
+__device__ __forceinline__ bool last_to_arrive(int32_t* __restrict__ arrive, int pieces)
+{
+    __shared__ int s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's sums have arrived ...
+    __syncthreads();                                   // ... and so have those of the others
+    if (threadIdx.x == 0) {
+        s_last = __hip_atomic_fetch_add(arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pieces - 1;
+        if (s_last) __hip_atomic_store(arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return s_last;
+}
+// Calls f for every expert without rows, on all threads.
+template <typename F> __device__ __forceinline__ void for_empty(const int32_t* __restrict__ counts, int E, F f)
+{
+    const int lane = threadIdx.x & 63;
+    for (int e0 = 0; e0 < E; e0 += 64)
+        for (unsigned long long m = __ballot(e0 + lane < E && counts[min(e0 + lane, E - 1)] == 0); m; m &= m - 1) f(e0 + __ffsll(m) - 1);
+}
+// Sum over pieces first .. next - 1 of part[q][c], in ascending order.
+__device__ __forceinline__ float sum_pieces(const float* __restrict__ part, int first, int next, int d, int c)
+{
+    constexpr int FLY = 8;
+    float s = 0.f;
+    for (int q = first; q < next; q += FLY) {
+        float f[FLY];
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) f[u] = __hip_atomic_load(part + (size_t)min(q + u, next - 1) * d + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < FLY; ++u)
+            if (q + u < next) s += f[u];
+    }
+    return s;
 }
 
 template <typename T>
@@ -348,36 +417,45 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
                                                    float* __restrict__ part, float* __restrict__ bpart, int E, int d,
                                                    int cpr, const T* __restrict__ Wg, T* __restrict__ WgT)
 {
-    // Rides along (WgT != nullptr): WgT[e][i] = Wg[i][e], which lets the kernel that follows the reduction read a
-    // gate column as contiguous 16-byte pieces; spread over all workgroups of the launch.
-    if (WgT) {
-        const long nel = (long)d * E, nthr = (long)gridDim.x * gridDim.y * gridDim.z * 512;
-        const long block = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        for (long i = block * 512 + threadIdx.x; i < nel; i += nthr) {
-            const int ee = (int)(i / d), row = (int)(i - (long)ee * d);
-            WgT[i] = Wg[(size_t)row * E + ee];
-        }
-    }
+    // The transposed gate matrix rides along: the kernel that follows the reduction reads it.
+    const long block = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    transpose_gate(Wg, WgT, d, E, block * 512 + threadIdx.x, (long)gridDim.x * gridDim.y * gridDim.z * 512);
     // The column blocks of a piece are neighbours, so that rows of several KB are read while their pages of memory are open (gate
     // backward of 32768 tokens, d 2048, 32 experts, top-2, bf16: 149 us with a launch's pieces of the first column block in front
     // of those of the second, 137 so).  Two of them change places every four pieces: otherwise every other XCD (workgroup number
     // modulo 8) would get all the second ones, which may be mostly empty.
     const int piece = (int)(blockIdx.z * gridDim.y + blockIdx.y), col = gridDim.x == 2 ? (int)blockIdx.x ^ (piece >> 2 & 1) : (int)blockIdx.x;
-    segment_partial<T>(Xs, dl, perm, counts, offsets, P64, part, bpart, E, d, cpr, piece, col);
+    segment_partial<T, false>(Xs, dl, perm, counts, offsets, P64, part, bpart, E, d, cpr, piece, col);
 }
 
 // Plain column sums of two row matrices over the same segments (the gradients of both layers' biases), side by side in one launch:
 // the column blocks of the first, then those of the second, going round from piece to piece so that an XCD (workgroup number
 // modulo 8) does not get the same ones of all pieces.
+// An expert's pieces are added up by the last of their workgroups; what has no rows is left to one more
+// workgroup per column block.  With the additions in a launch of their own, and the gate's (below)
+// likewise, a training step of 1000 tokens, 8 experts, d 768, h 3072, top-2 took 280 us, now 277.5.
 struct ColumnSums { const void* src; float* part; float* out; int width, cpr; };
+__device__ __forceinline__ void put_sum(float* out, float s, int accumulate) { *out = accumulate ? *out + s : s; }
 template <typename T>
-__global__ __launch_bounds__(512) void segsum_partial(ColumnSums a, ColumnSums b, const int32_t* __restrict__ counts,
-                                                      const int32_t* __restrict__ offsets, const int32_t* __restrict__ P64, int E)
+__global__ __launch_bounds__(512) void segment_sums(ColumnSums a, ColumnSums b, const int32_t* __restrict__ counts,
+                                                    const int32_t* __restrict__ offsets, const int32_t* __restrict__ P64, int E,
+                                                    int32_t* __restrict__ arrive, long pieces, int accumulate)
 {
-    const int piece = (int)(blockIdx.z * gridDim.y + blockIdx.y), first = (a.cpr + 63) / 64;
+    constexpr int V = Vec<T>::N;
+    const long piece = (long)blockIdx.z * gridDim.y + blockIdx.y;
+    const int first = (a.cpr + 63) / 64;
     const int x = (int)((blockIdx.x + (unsigned)piece) % gridDim.x);
     const ColumnSums s = x < first ? a : b;
-    segment_partial<T>(s.src, nullptr, nullptr, counts, offsets, P64, s.part, nullptr, E, s.width, s.cpr, piece, x < first ? x : x - first);
+    const int col = x < first ? x : x - first, c = col * 64 * V + (int)threadIdx.x;
+    const bool mine = (int)threadIdx.x < 64 * V && c < s.width;
+    if (piece >= pieces) {                          // experts without rows
+        if (piece > pieces || accumulate) return;
+        for_empty(counts, E, [&](int e) { if (mine) s.out[(size_t)e * s.width + c] = 0.f; });
+        return;
+    }
+    const Segment sg = segment_partial<T, true>(s.src, nullptr, nullptr, counts, offsets, P64, s.part, nullptr, E, s.width, s.cpr, (int)piece, col);
+    if (sg.e < 0 || !last_to_arrive(arrive + (size_t)sg.e * gridDim.x + x, sg.next - sg.first) || !mine) return;
+    put_sum(s.out + (size_t)sg.e * s.width + c, sum_pieces(s.part, sg.first, sg.next, s.width, c), accumulate);
 }
 
 // grid (ceil(d / 256), E): a thread owns one row of one expert's column, so that the threads of a wavefront read
@@ -428,20 +506,66 @@ __global__ __launch_bounds__(256) void gate_bwd_tail(int fgx, const float* __res
     if ((int)blockIdx.x < nfinal)
         dwg_final_body<G>((int)blockIdx.x % fgx, (int)blockIdx.x / fgx, part, bpart, P64, dWg, dbg, d, E, accumulate);
     else
-        gate_bwd_dx_body<T, K>((long)blockIdx.x - nfinal, (long)gridDim.x - nfinal, dXs, WgT, dl, topk_idx, pos, dX, N, k, cpr);
+        gate_bwd_dx_body<T, K, 256>((long)blockIdx.x - nfinal, (long)gridDim.x - nfinal, dXs, WgT, dl, topk_idx, pos, dX, N, k, cpr);
 }
 
-// out[e][c] = sum of the pieces of expert e, in ascending order (the column sums of its segment).
-__global__ __launch_bounds__(256) void segsum_final(ColumnSums a, ColumnSums b, const int32_t* __restrict__ P64, int accumulate)
+// Gate backward in one launch, for a call that has the transposed gate matrix already: workgroups of pieces first, each expert's sums added
+// up by the last of them; then a workgroup per column block for the experts without rows; then dX.  None of these reads
+// what another writes.  Bound by latency in small batches, by HBM in large ones.  A step against one whose sums are added up in a second
+// launch beside dX: 256 tokens, d 64, 4 experts, fp32 42.6 -> 41.1 us; 16384 tokens, d 512, 256 experts, top-1 507.6 -> 505.1; 8192, d 1024, 64
+// experts 1426 -> 1423.
+template <typename T, typename G, int K>
+__global__ __launch_bounds__(512) void gate_bwd_whole(const void* __restrict__ Xs, const float* __restrict__ dl, const int32_t* __restrict__ perm,
+                                                      const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
+                                                      const int32_t* __restrict__ P64, float* __restrict__ part, float* __restrict__ bpart,
+                                                      int32_t* __restrict__ arrive, int pieces, int cols, G* __restrict__ dWg, float* __restrict__ dbg,
+                                                      int d, int E, int accumulate, const void* __restrict__ dXs, const void* __restrict__ WgT,
+                                                      const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ pos, void* __restrict__ dX,
+                                                      long N, int k, int cpr)
 {
-    const int first = (a.width + 255) / 256, x = (int)blockIdx.x, e = blockIdx.y;
-    const ColumnSums m = x < first ? a : b;
-    const int c = (x < first ? x : x - first) * 256 + threadIdx.x;
-    if (c >= m.width) return;
-    float s = 0.f;
-    for (int q = P64[e]; q < P64[e + 1]; ++q) s += m.part[(size_t)q * m.width + c];
-    const size_t o = (size_t)e * m.width + c;
-    m.out[o] = accumulate ? m.out[o] + s : s;
+    constexpr int V = Vec<T>::N;
+    const int nsum = (pieces + 1) * cols;
+    if ((int)blockIdx.x >= nsum) {
+        gate_bwd_dx_body<T, K, 512>((long)blockIdx.x - nsum, (long)gridDim.x - nsum, dXs, WgT, dl, topk_idx, pos, dX, N, k, cpr);
+        return;
+    }
+    // (as in dwg_partial: the column blocks of a piece are neighbours, and two of them change places every four pieces)
+    const int piece = (int)blockIdx.x / cols, x = (int)blockIdx.x - piece * cols, col = cols == 2 ? x ^ (piece >> 2 & 1) : x;
+    const int c = col * 64 * V + (int)threadIdx.x;
+    const bool mine = (int)threadIdx.x < 64 * V && c < d;
+    auto put = [&](int e, float s) {
+        const size_t i = (size_t)c * E + e;
+        if constexpr (sizeof(G) == 2) {
+            if (accumulate) s += bf16_to_f32(dWg[i]);
+            dWg[i] = f32_to_bf16(s);
+        } else {
+            if (accumulate) s += dWg[i];
+            dWg[i] = s;
+        }
+    };
+    if (piece == pieces) {                              // experts without rows
+        if (accumulate) return;
+        for_empty(counts, E, [&](int e) {
+            if (mine) put(e, 0.f);
+            if (dbg && col == 0 && threadIdx.x == 0) dbg[e] = 0.f;
+        });
+        return;
+    }
+    const Segment sg = segment_partial<T, true>(Xs, dl, perm, counts, offsets, P64, part, bpart, E, d, cpr, piece, col);
+    if (sg.e < 0 || !last_to_arrive(arrive + sg.e * cols + col, sg.next - sg.first)) return;
+    if (mine) put(sg.e, sum_pieces(part, sg.first, sg.next, d, c));
+    if (dbg && col == 0) {                              // (uniform over the workgroup)
+        __shared__ float s_b[512];
+        float s = 0.f;
+        for (int q = sg.first; q < sg.next; q += 512) {
+            if (q + (int)threadIdx.x < sg.next) s_b[threadIdx.x] = __hip_atomic_load(bpart + q + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            if (threadIdx.x == 0)
+                for (int i = 0; i < min(512, sg.next - q); ++i) s += s_b[i];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) dbg[sg.e] = accumulate ? dbg[sg.e] + s : s;
+    }
 }
 
 // ---- launchers -----------------------------------------------------------------------------------
@@ -488,18 +612,20 @@ void launch_combine(const moe_desc_t& D, const void* Ys, const float* topk_w, co
 }
 
 void launch_dcombine(const moe_desc_t& D, const void* dY, const void* Ys, const float* topk_w,
-                     const int32_t* pos, void* dYs, float* dl, const GateDense& gate, const void* X, void* Xs, hipStream_t st)
+                     const int32_t* pos, void* dYs, float* dl, const GateDense& gate, const void* X, void* Xs, const void* Wg, void* WgT,
+                     hipStream_t st)
 {
     const int cpr = (int)((size_t)D.d * dtype_size(D.dtype) / 16);
-    const unsigned g = (unsigned)((D.N + 3) / 4);
+    unsigned g = (unsigned)((D.N + 3) / 4);
+    if (WgT) g = std::max(g, (unsigned)(((long)D.d * D.E + 2047) / 2048));   // (at most eight elements of the gate matrix a thread)
     with_k(D.k, [&](auto kc) {
         constexpr int K = decltype(kc)::value;
         if (D.dtype == MOE_BF16)
             hipLaunchKernelGGL((dcombine_rows<unsigned short, K>), dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl,
-                               (long)D.N, D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
+                               (long)D.N, D.k, cpr, gate, (const uint4*)X, (uint4*)Xs, (const unsigned short*)Wg, (unsigned short*)WgT, D.d, D.E);
         else
             hipLaunchKernelGGL((dcombine_rows<float, K>), dim3(g), dim3(256), 0, st, dY, Ys, topk_w, pos, dYs, dl, (long)D.N,
-                               D.k, cpr, gate, (const uint4*)X, (uint4*)Xs);
+                               D.k, cpr, gate, (const uint4*)X, (uint4*)Xs, (const float*)Wg, (float*)WgT, D.d, D.E);
     });
 }
 
@@ -539,6 +665,32 @@ void launch_gate_bwd(const moe_desc_t& D, const WsLayout& L, const void* Xs, con
     else launch((unsigned short)0, float{});
 }
 
+// launch_gate_bwd for a call whose combine backward wrote the transposed gate matrix (and whose workspace has the counters: moe_backward)
+void launch_gate_bwd_whole(const moe_desc_t& D, const WsLayout& L, const void* Xs, const void* dXs, const void* Wg,
+                           const float* dl, const int32_t* topk_idx, const int32_t* pos, const int32_t* perm,
+                           const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws, hipStream_t st)
+{
+    const int cpr = (int)((size_t)D.d * dtype_size(D.dtype) / 16), cols = (cpr + 63) / 64;
+    const long dx_blocks = std::min<long>(((long)D.N * cpr + 511) / 512, 256 * 16), blocks = (L.dwg_pieces + 1) * cols + dx_blocks;
+    if (blocks > 4 << 20) {                             // (a launch holds less than 2^32 threads)
+        launch_gate_bwd(D, L, Xs, dXs, Wg, dl, topk_idx, pos, perm, counts, offsets, dX, dWg, dbg, ws, st);
+        return;
+    }
+    const int32_t* P64 = (const int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
+    auto launch = [&](auto tv, auto gv) {
+        using T = decltype(tv);
+        using G = decltype(gv);
+        with_k(D.k, [&](auto kc) {
+            hipLaunchKernelGGL((gate_bwd_whole<T, G, decltype(kc)::value>), dim3((unsigned)blocks), dim3(512), 0, st, Xs, dl, perm, counts, offsets,
+                               P64, (float*)(ws + L.dwg_part), (float*)(ws + L.dbg_part), (int32_t*)(ws + L.arrive), (int)L.dwg_pieces, cols,
+                               (G*)dWg, dbg, D.d, D.E, D.accumulate, dXs, (const void*)(ws + L.WgT), topk_idx, pos, dX, (long)D.N, D.k, cpr);
+        });
+    };
+    if (D.dtype == MOE_F32) launch(float{}, float{});
+    else if (D.grad_dtype == MOE_BF16) launch((unsigned short)0, (unsigned short)0);
+    else launch((unsigned short)0, float{});
+}
+
 // Column sums over every expert's segment (fixed order): db1[E][h] of dZ[M][h] and db2[E][d] of dYs[M][d], either NULL for none.
 void launch_bias_sums(const moe_desc_t& D, const WsLayout& L, const int32_t* counts, const int32_t* offsets, float* db1, float* db2, char* ws,
                       hipStream_t st)
@@ -550,11 +702,12 @@ void launch_bias_sums(const moe_desc_t& D, const WsLayout& L, const int32_t* cou
     const int cols = (a.cpr + 63) / 64 + (b.cpr + 63) / 64;
     if (!cols) return;
     const int32_t* P64 = (const int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
-    const dim3 pg = piece_grid(L.dwg_pieces, cols);
-    if (D.dtype == MOE_BF16) hipLaunchKernelGGL(segsum_partial<unsigned short>, pg, dim3(512), 0, st, a, b, counts, offsets, P64, D.E);
-    else hipLaunchKernelGGL(segsum_partial<float>, pg, dim3(512), 0, st, a, b, counts, offsets, P64, D.E);
-    hipLaunchKernelGGL(segsum_final, dim3((unsigned)((a.width + 255) / 256 + (b.width + 255) / 256), (unsigned)D.E), dim3(256), 0, st, a, b, P64,
-                       D.accumulate);
+    const dim3 pg = piece_grid(L.dwg_pieces + 1, cols);
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, pg, dim3(512), 0, st, a, b, counts, offsets, P64, D.E, (int32_t*)(ws + L.arrive), L.dwg_pieces, D.accumulate);
+    };
+    if (D.dtype == MOE_BF16) launch(segment_sums<unsigned short>);
+    else launch(segment_sums<float>);
 }
 
 }  // namespace moe
