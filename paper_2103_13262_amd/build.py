@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoe355.so")
-SOURCES = ["moe_api.hip", "gate_topk.hip", "gate_bf16.hip", "gate_small.hip", "gate_dense.hip", "plan.hip", "rowmove.hip", "noalloc.hip", "ggemm_f32.hip", "ggemm_bf16_sk.hip",
+SOURCES = ["moe_api.hip", "gate_topk.hip", "gate_bf16.hip", "gate_rows.hip", "gate_small.hip", "gate_dense.hip", "plan.hip", "rowmove.hip", "noalloc.hip", "ggemm_f32.hip", "ggemm_bf16_sk.hip",
            *(f"ggemm_bf16_{p}.hip" for p in ("fc1", "fc2", "dz", "dxs", "dw", "dz_dw2", "dxs_dw1"))]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

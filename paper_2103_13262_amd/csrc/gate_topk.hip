@@ -580,7 +580,8 @@ static bool small_batch(const moe_desc_t& D, bool logits)
         small = 5.5 + w * round;
     }
     if (D.E <= 16) tiled = 6.4 + (bf16 ? 4.95 : 6.3) * d + (logits ? 3.0 : 0.0);
-    else if (bf16 && D.E <= 256 && !logits) tiled = 11.3 + 6.0 * d + 2.3 * k + 1.5 * k * d + 0.042 * el;
+    else if (bf16 && D.E <= 256 && !logits)                    // (gate_rows.hip from 256 features up)
+        tiled = D.d >= 256 ? 9.0 + 1.5 * k + 0.02 * D.E + 4.0 * d + 0.055 * el : 11.3 + 6.0 * d + 2.3 * k + 1.5 * k * d + 0.042 * el;
     else if (D.E <= 32) tiled = 6.0 + 40.0 * d + 2.4 * k;
     else tiled = 9.0 + (D.E + 63) / 64 * (2.2 + 13.0 * d + 1.9 * k);
     return small <= tiled;
