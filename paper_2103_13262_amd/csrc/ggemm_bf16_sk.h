@@ -1089,7 +1089,7 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
     // ggemm_bf16_tile.h, the others in 64 x 256 tiles, 8 waves of 32 x 64, 3 ring slots, so that a tile is not mostly rows that do
     // not exist.  (Waves of 64 x 32 store a row in pieces of 64 bytes, which streaming stores write at 3.5 TB/s instead of 5.6: dZ
     // with dW2 of 256 experts with 64 rows, d 512, h 1024: 156 us, in waves of 32 x 64 149.)  (The weight gradients keep the large
-    // tile: their tile spans the weight matrix, not the expert's rows.)
+    // tile, or half of it (half_tiles_pay): their tile spans the weight matrix, not the expert's rows.)
     // Otherwise the rows kinds run in two size classes (launch_cls): an expert's last few rows in 128 x 512 tiles.
     if constexpr (KIND != kColsT) {
         constexpr bool FORWARD = KIND == kRowsNN || KIND == kRowsNN_GeLU;
@@ -1104,6 +1104,7 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
         else launch_cls<KIND, 2, 64>(a, st);
     } else {
         if (!offsets_fit(a)) launch_cfg<KIND, 2, 4, 4, 2, 4, 32, true>(a, st);
+        else if (half_tiles_pay(a)) launch_cfg<KIND, 2, 4, 2, 2, 4, 32>(a, st);
         else launch_cfg<KIND, 2, 4, 4, 2, 4, 32>(a, st);
     }
 }

@@ -102,6 +102,19 @@ template <class Product> constexpr bool pair_pays(const Product& rows, int workg
     return offsets_fit(rows) && !tile_beats_pair(rows) && wide_tiles(rows) <= 8L * workgroups;
 }
 
+// A weight gradient in a launch of its own: whether tiles of 128 x 256 beat those of 256 x 256.  A tile's time is mostly that of its gradient's way to
+// memory, so what counts is how much of the last round of tiles (256 at a time) is empty; but a tile half as high reads nearly as much.
+// Both sides' times of 59 products (1 to 200 experts, 5 to 2500 rows each, K 256 to 5700, 500 to 5900 columns), rounds of either in brackets:
+//   * a single round of the smaller ones: 0.68 to 0.88 of the time (88 and 132 tiles, added up in fp32: 66 -> 45 us; 105 and 189: 17 -> 14);
+//   * a third more rounds of the smaller ones at most (3 and 4): 0.87 to 0.95 (88 -> 77, 28 -> 26);
+//   * half as many more (2 and 3, 4 and 6) where fp32 gradients are added to, which is read as well: 0.89 and 1.0; otherwise 0.95 to 1.13.
+// Beyond: 0.97 to 1.26.
+template <class Product> constexpr bool half_tiles_pay(const Product& a)
+{
+    const long columns = a.E * wide_columns(a), whole = (columns * ((a.K + 255) / 256) + 255) / 256, half = (columns * ((a.K + 127) / 128) + 255) / 256;
+    return half <= 1 || half * 3 <= whole * 4 || (a.accumulate && a.out_f32 && half * 2 <= whole * 3);
+}
+
 // 64-bit offsets, 96 rows per expert and more: whether the two size classes beat 64 x 256 tiles.  Millions of columns: always (one expert, 100 to
 // 3000 rows, 32 to 512 deep: 0.57 to 0.87 of the time).  A reduction over millions with few big tiles: no, since a tile is cut among the workgroups of one XCD only and
 // 64-row tiles are more (300 rows, 128 columns: FC2 1.8 ms against 14, dXs 2.4 against 13; 1000 rows, 256 columns, 3 tiles: 4.4 against 7.2 and
