@@ -1022,14 +1022,14 @@ __global__ __launch_bounds__(512, 1) void ggemm_cls_kernel(GemmArgs g, int ntn_b
 // Two products that do not depend on each other in one launch: a rows kind, then the weight gradients with their
 // tiles handed out on demand.  A workgroup that runs out of tiles of the first product goes on with the second
 // instead of idling until the launch ends, and one launch gap is saved.  CLASSES: the rows kind in size classes
-// (as ggemm_cls_kernel), else in 64 x 256 tiles (many small experts).
-template <int KIND, bool CLASSES, bool DEEP>
+// (as ggemm_cls_kernel), else in 64 x 256 tiles (many small experts).  HALF: the weight gradients in 128 x 256 tiles (half_round).
+template <int KIND, bool CLASSES, bool DEEP, bool HALF>
 __global__ __launch_bounds__(512, 1) void ggemm_pair_kernel(GemmArgs g1, int ntn1, int ntn1_small, GemmArgs g2, int ntm2, int ntn2)
 {
     if constexpr (CLASSES) ggemm_classes<KIND, 2, 64, DEEP, true>(g1, ntn1, ntn1_small);
     else ggemm_sk_body<KIND, 2, 4, 1, 2, 3, 64, 0, false, true>(g1, 0, ntn1);
     __syncthreads();
-    ggemm_sk_body<kColsT, 2, 4, 4, 2, 4, 32>(g2, ntm2, ntn2);
+    ggemm_sk_body<kColsT, 2, 4, HALF ? 2 : 4, 2, 4, 32>(g2, ntm2, ntn2);
 }
 
 // Persistent workgroups of one launch (a multiple of the 8 XCDs, at most kMaxPersistentWgs); 0 after fail_launch.
@@ -1108,14 +1108,14 @@ template <int KIND> void launch_kind(const GemmArgs& a, hipStream_t st)
         else launch_cfg<KIND, 2, 4, 4, 2, 4, 32>(a, st);
     }
 }
-template <int KIND, bool CLASSES, bool DEEP>
+template <int KIND, bool CLASSES, bool DEEP, bool HALF>
 void launch_pair_cfg(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
 {
     using C1 = std::conditional_t<CLASSES, Cfg<KIND, 2, 4, 4, 2, 2, 64>, Cfg<KIND, 2, 4, 1, 2, 3, 64>>;
     using C1s = CfgWide<KIND>;
-    using C2 = Cfg<kColsT, 2, 4, 4, 2, 4, 32>;
+    using C2 = Cfg<kColsT, 2, 4, HALF ? 2 : 4, 2, 4, 32>;
     constexpr int SMEM = std::max({C1::SMEM, CLASSES ? C1s::SMEM : 0, CLASSES && DEEP ? CfgDeep<KIND>::SMEM : 0, C2::SMEM});
-    constexpr auto kern = ggemm_pair_kernel<KIND, CLASSES, DEEP>;
+    constexpr auto kern = ggemm_pair_kernel<KIND, CLASSES, DEEP, HALF>;
     if (!allow_dynamic_lds<kern>(SMEM)) return;
     const int wgs = persistent_wgs();
     if (wgs < 8) return;
@@ -1128,9 +1128,14 @@ void launch_pair_cfg(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
 
 template <int KIND> void launch_pair_kind(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
 {
-    if (few_rows(rows)) launch_pair_cfg<KIND, false, false>(rows, cols, st);
-    else if (shallow(rows)) launch_pair_cfg<KIND, true, true>(rows, cols, st);
-    else launch_pair_cfg<KIND, true, false>(rows, cols, st);
+    auto go = [&](auto half) {
+        constexpr bool HALF = decltype(half)::value;
+        if (shallow(rows)) launch_pair_cfg<KIND, true, true, HALF>(rows, cols, st);
+        else launch_pair_cfg<KIND, true, false, HALF>(rows, cols, st);
+    };
+    if (few_rows(rows)) launch_pair_cfg<KIND, false, false, false>(rows, cols, st);
+    else if (half_round(cols)) go(std::true_type{});
+    else go(std::false_type{});
 }
 }  // namespace sk
 

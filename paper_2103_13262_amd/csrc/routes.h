@@ -102,6 +102,15 @@ template <class Product> constexpr bool pair_pays(const Product& rows, int workg
     return offsets_fit(rows) && !tile_beats_pair(rows) && wide_tiles(rows) <= 8L * workgroups;
 }
 
+// A weight gradient that follows a rows product in one launch: whether its tiles are so few that half as high ones still make a single round, over
+// reductions long enough to matter.  Both sides' times of the launch, 153 drawn products with at most 256 of the smaller tiles: 0.67 to 1.0 with 1024 rows
+// per expert and more and up to 224 of them, with a few up to 1.13 (0.84 on average; one expert, 9768 rows, K 1408, 384 columns: 178 -> 119 us; 10 experts,
+// 3079 rows, K 448, 960 columns: 118 -> 102); 0.93 to 1.06 with fewer rows; 0.89 to 1.18 with more tiles.
+template <class Product> constexpr bool half_round(const Product& a)
+{
+    return a.M >= 1024L * a.E && a.E * wide_columns(a) * ((a.K + 127) / 128) <= 224;
+}
+
 // A weight gradient in a launch of its own: whether tiles of 128 x 256 beat those of 256 x 256.  A tile's time is mostly that of its gradient's way to
 // memory, so what counts is how much of the last round of tiles (256 at a time) is empty; but a tile half as high reads nearly as much.
 // Both sides' times of 59 products (1 to 200 experts, 5 to 2500 rows each, K 256 to 5700, 500 to 5900 columns), rounds of either in brackets:

@@ -1,4 +1,4 @@
-"""Weight gradients in tiles of 128 x 256 (few tiles, or fp32 gradients that are added to): edges of a tile in both directions, experts without rows, with one, 31 to 33
+"""Weight gradients in tiles of 128 x 256 (few tiles, or fp32 gradients that are added to), in launches of their own and behind the rows products: edges of a tile in both directions, experts without rows, with one, 31 to 33
 and more rows, stored in bf16 or fp32, added to or not, against fp64 sums of the same bf16 operands.  The operands are small integers, so every product and
 every sum is exact in fp32; the only rounding is the result's to bf16 (2^-9 of its magnitude)."""
 import pytest
@@ -7,11 +7,11 @@ from paper_2103_13262_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
-ROWS = {5: [0, 1, 31, 33, 200], 3: [64, 65, 700], 1: [300]}
+ROWS = {5: [0, 1, 31, 33, 200], 3: [64, 65, 700], 1: [300], 2: [2100, 33], 4: [1, 4000, 0, 321]}
 
 
 @pytest.mark.parametrize("grad,accumulate", [("bf16", 0), ("f32", 0), ("f32", 1), ("bf16", 1)])
-@pytest.mark.parametrize("E,d,h", [(5, 128, 256), (5, 160, 288), (3, 384, 4096), (1, 1056, 2080), (3, 32, 64), (5, 96, 544)])
+@pytest.mark.parametrize("E,d,h", [(5, 128, 256), (5, 160, 288), (3, 384, 4096), (1, 1056, 2080), (3, 32, 64), (5, 96, 544), (2, 160, 1056), (4, 544, 288), (2, 1088, 2080)])
 def test_weight_gradients(E, d, h, grad, accumulate):
     import torch
 
@@ -27,7 +27,7 @@ def test_weight_gradients(E, d, h, grad, accumulate):
     X[torch.arange(N, device=dev), expert] = 1     # one feature per expert decides: the experts' row counts are exact
     Wg[torch.arange(E), torch.arange(E)] = 1
     gt = torch.float32 if grad == "f32" else torch.bfloat16
-    # weights in the place of their own gradients: every gradient gets a launch of its own
+    # weights in the place of their own gradients: every gradient gets a launch of its own (up to 1000 rows; with more, beside the weights)
     desc = B.make_desc(N, d, h, E, 1, B.MOE_BF16, B.MOE_F32 if grad == "f32" else B.MOE_BF16, accumulate)
     buf = B.MoeLayerBuffers(desc, dev)
     ws = (buf.workspace, buf.ws_bytes, buf.stream())
@@ -37,6 +37,8 @@ def test_weight_gradients(E, d, h, grad, accumulate):
         for m in (mem1, mem2):
             m.view(torch.bfloat16)[:size] = torch.randint(-2, 3, (size,), generator=g, device=dev).bfloat16() / 64
     W1, W2 = mem1.view(torch.bfloat16)[:size].view(E, d, h), mem2.view(torch.bfloat16)[:size].view(E, h, d)
+    if N > 1000:
+        W1, W2 = (torch.randint(-2, 3, w.shape, generator=g, device=dev).bfloat16() / 64 for w in (W1, W2))
     dY = torch.randint(-2, 3, (N, d), generator=g, device=dev).bfloat16()
     Y, dX, dWg, dbg = torch.empty_like(X), torch.empty_like(X), torch.zeros((d, E), dtype=gt, device=dev), torch.zeros(max(E, 4), device=dev)
     before = [m.clone().double() for m in (mem1, mem2)]
