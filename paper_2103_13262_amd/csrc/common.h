@@ -239,6 +239,7 @@ struct GemmArgs {
     long long* clock_probe;    // [2]: shader cycles and 100 MHz ticks of workgroup 0 of the last launch
     const int32_t* skewed;     // 1: the experts' sizes are strongly skewed (decided by the plan step)
     int32_t* dyn_counters;     // [9]: next tile of every XCD's list and the number of workgroups that have finished; zero between launches
+    int slices;                // weight gradients behind a rows product, in 128 x 256 tiles: ranges that an expert's rows are cut into
     int on_demand;             // weight gradients: hand the tiles out from the counters whatever the sizes
     int stream_out;            // bf16 products: results leave as streaming stores (set by the host when the experts' weights exceed the L2 caches; fp32 and accumulating gradients always do)
     int stream_weights;        // forward products in small tiles: weights that one tile reads come as streaming loads (routes.h)

@@ -112,6 +112,7 @@ struct Item {
     int owner;            // the range holds the tile's last block: this workgroup writes the tile
     size_t b_off;         // rows kinds: expert * Nout + first column (where the tile's bias values start)
     long row0;            // rows kinds: first row of the tile in the expert-contiguous order
+    int tile, slice;      // SLICES: the tile's number among all, and which of its ranges
 };
 
 struct Fin {              // what finishing an item needs once the streams have moved on to the next one
@@ -126,7 +127,9 @@ struct Fin {              // what finishing an item needs once the streams have 
 // wj_count <= 0: all take part, counted round from wj_base (which only a launch of whole tiles may set then: a split
 // tile's partial sums go from one workgroup to the one numbered next).
 // WHOLE (rows kinds): never cut a tile (another product in the same launch fills the workgroups that have nothing left to do here).
-template <int KIND, int WM, int WN, int TM, int TN, int STAGES, int BK, int CLS = 0, bool WIDE = false, bool WHOLE = false>
+// SLICES (weight gradients): an expert's rows may be cut into g.slices ranges; a range is an item of its own and leaves its sum in fp32, and the workgroup
+// that is the last of a tile's to arrive adds them up in ascending order (nobody waits).
+template <int KIND, int WM, int WN, int TM, int TN, int STAGES, int BK, int CLS = 0, bool WIDE = false, bool WHOLE = false, bool SLICES = false>
 __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int ntn, int wj_base = 0, int wj_count = 0)
 {
     using C = Cfg<KIND, WM, WN, TM, TN, STAGES, BK>;
@@ -181,7 +184,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
         n_dp = n_x - rem;
         dp_i = wj; dp_stride = W;
     } else {
-        tpe = ntm * ntn;
+        tpe = ntm * ntn * (SLICES ? g.slices : 1);   // (a tile's ranges as so many tiles: those of one range are neighbours and share panels)
         by_expert = *g.by_expert != 0;
         if (by_expert) { n_dp = (long)((g.E + 7) / 8) * tpe; dp_i = wj; dp_stride = W; }
         else if ((tpe & 7) == 0) { per = tpe >> 3; n_dp = (long)g.E * per; dp_i = wj; dp_stride = W; }
@@ -338,6 +341,8 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
                 break;
             }
             const int e = g.order[ord];
+            int slice = 0;
+            if constexpr (SLICES) { slice = q / (ntm * ntn); q -= slice * (ntm * ntn); }
             const int m0 = (q / ntn) * BM, n0 = (q % ntn) * BN;
             const long off = g.offsets[e];
             it.A = (const u16*)g.A + off * g.K + m0;     it.lda = g.K;
@@ -346,6 +351,11 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
             it.b_off = 0;
             it.Mt = min(BM, g.K - m0);  it.Nt = min(BN, g.Nout - n0);  it.Kt = g.counts[e];
             it.kb0 = 0;  it.kb1 = (it.Kt + BK - 1) / BK;  it.owner = 1;
+            if constexpr (SLICES) {
+                const int blocks = it.kb1;
+                it.kb0 = slice * blocks / g.slices;  it.kb1 = (slice + 1) * blocks / g.slices;  it.owner = g.slices == 1;
+                it.tile = e * (ntm * ntn) + q;  it.slice = slice;
+            }
             return true;
         }
     };
@@ -603,10 +613,10 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
     constexpr int PART_ROW_BYTES = NT * 16;                      // one piece of every thread
     constexpr int RING_ROWS = C::RING / PART_ROW_BYTES;          // pieces per thread that fit in the ring
     static_assert(RING_ROWS >= 1, "ring too small to land partial sums");
-    auto store_partial = [&]() {
+    auto store_sums = [&](size_t at) {
         int tid_ = tid;
         asm volatile("" : "+v"(tid_));   // keeps the address arithmetic of this cold path out of the main loop's registers
-        char* const dst = (char*)g.sk_part + (size_t)sk_slot * kPartialBytesPerWg + tid_ * 16;
+        char* const dst = (char*)g.sk_part + at + tid_ * 16;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -622,27 +632,16 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
                 }
         wait_vmcnt<0>();                       // this wave's partial sums have arrived ...
         __syncthreads();                       // ... and so have those of the other waves
+    };
+    auto store_partial = [&]() {
+        store_sums((size_t)sk_slot * kPartialBytesPerWg);
         if (tid == 0) __hip_atomic_store(g.sk_flags + sk_slot, kPartialReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    // Adds the partial sum of the workgroup just below (same XCD slot, one position lower).  The ring must be idle.
-    auto add_predecessor = [&]() {
-        const int id = sk_slot - 8;
-        if (tid == 0) {
-            int spins = 0;
-            // (a negative limit gives every wait up at once, flag or no flag: the tests' way to walk through this path)
-            while (g.spin_limit < 0 || __hip_atomic_load(g.sk_flags + id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kPartialReady) {
-                if (++spins > g.spin_limit) {   // cannot happen (see the header); kept so that every wave ends
-                    __hip_atomic_store(g.sk_error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(16);
-            }
-            __hip_atomic_store(g.sk_flags + id, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // as the next launch expects
-        }
-        __syncthreads();
+    // Adds the sums that lie at `at` to the accumulators, by way of the ring, which must be idle.
+    auto add_sums = [&](size_t at) {
         int tid_ = tid;
         asm volatile("" : "+v"(tid_));
-        const char* const src = (const char*)g.sk_part + (size_t)id * kPartialBytesPerWg + tid_ * 16;
+        const char* const src = (const char*)g.sk_part + at + tid_ * 16;
         const char* const mine = smem + tid_ * 16;   // every thread reads back exactly what its own wave requested
 #pragma unroll
         for (int r0 = 0; r0 < PART_ROWS; r0 += RING_ROWS) {
@@ -662,8 +661,49 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
                 acc[i][j][4 * q + 2] += pz.z;  acc[i][j][4 * q + 3] += pz.w;
             }
         }
+    };
+    // Adds the partial sum of the workgroup just below (same XCD slot, one position lower).  The ring must be idle.
+    auto add_predecessor = [&]() {
+        const int id = sk_slot - 8;
+        if (tid == 0) {
+            int spins = 0;
+            // (a negative limit gives every wait up at once, flag or no flag: the tests' way to walk through this path)
+            while (g.spin_limit < 0 || __hip_atomic_load(g.sk_flags + id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kPartialReady) {
+                if (++spins > g.spin_limit) {   // cannot happen (see the header); kept so that every wave ends
+                    __hip_atomic_store(g.sk_error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(16);
+            }
+            __hip_atomic_store(g.sk_flags + id, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // as the next launch expects
+        }
+        __syncthreads();
+        add_sums((size_t)id * kPartialBytesPerWg);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();              // every wave is done with the ring: the next item's blocks may land
+    };
+    // SLICES: leaves this range's sum; the last of the tile's to arrive comes out with the whole one (true).
+    auto add_slices = [&](const Item& it) -> bool {
+        constexpr size_t BYTES = (size_t)PART_ROWS * PART_ROW_BYTES;
+        store_sums((size_t)(it.tile * g.slices + it.slice) * BYTES);
+        if (tid == 0) {
+            s_next = (__hip_atomic_fetch_add(g.sk_flags + it.tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kPartialReady - 1)) == g.slices - 1;
+            if (s_next) __hip_atomic_store(g.sk_flags + it.tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // as the next launch expects
+        }
+        __syncthreads();
+        const bool last = __builtin_amdgcn_readfirstlane(s_next);
+        __syncthreads();                           // every wave has read it before the next index overwrites it
+        if (!last) return false;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int sl = 0; sl < g.slices; ++sl) add_sums((size_t)(it.tile * g.slices + sl) * BYTES);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();              // every wave is done with the ring: the next item's blocks may land
+        return true;
     };
     auto pack8 = [](const float* f) {
         return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]),
@@ -904,13 +944,16 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
             __builtin_amdgcn_s_waitcnt(0xc07f);
             __builtin_amdgcn_s_barrier();              // every wave is done reading the ring
         }
+        if constexpr (SLICES) {
+            if (!cur.owner) cur.owner = add_slices(cur);
+        }
         const Fin fin{cur.c_off, cur.b_off, cur.Mt, cur.Nt, cur.owner, cur.row0};
         if constexpr (CUTS) {
             if (cur.kb0 > 0) add_predecessor();   // the blocks before kb0 were summed by the workgroup just below
         }
         have = __builtin_amdgcn_readfirstlane(next_item(cur));
         if (have) start_item(cur);
-        if (!CUTS || fin.owner) {
+        if (!(CUTS || SLICES) || fin.owner) {
             constexpr std::true_type yes;
             constexpr std::false_type no;
             bool done = false;
@@ -929,7 +972,7 @@ __device__ __forceinline__ void ggemm_sk_body(const GemmArgs& g, int ntm, int nt
         if constexpr (CUTS) {
             if (!fin.owner) store_partial();
         }
-        stores_behind = (!CUTS || fin.owner) && fin.Mt == BM && fin.Nt == BN && !(KIND == kColsT && (g.out_f32 || g.accumulate));
+        stores_behind = (!(CUTS || SLICES) || fin.owner) && fin.Mt == BM && fin.Nt == BN && !(KIND == kColsT && (g.out_f32 || g.accumulate));
     }
     if constexpr (KIND == kColsT) {
         if (dynamic && tid == 0) {       // the last workgroup to finish leaves the counters at zero for the next launch
@@ -1022,14 +1065,15 @@ __global__ __launch_bounds__(512, 1) void ggemm_cls_kernel(GemmArgs g, int ntn_b
 // Two products that do not depend on each other in one launch: a rows kind, then the weight gradients with their
 // tiles handed out on demand.  A workgroup that runs out of tiles of the first product goes on with the second
 // instead of idling until the launch ends, and one launch gap is saved.  CLASSES: the rows kind in size classes
-// (as ggemm_cls_kernel), else in 64 x 256 tiles (many small experts).  HALF: the weight gradients in 128 x 256 tiles (half_round).
+// (as ggemm_cls_kernel), else in 64 x 256 tiles (many small experts).  HALF: the weight gradients in 128 x 256 tiles (half_round), their rows cut
+// into ranges.
 template <int KIND, bool CLASSES, bool DEEP, bool HALF>
 __global__ __launch_bounds__(512, 1) void ggemm_pair_kernel(GemmArgs g1, int ntn1, int ntn1_small, GemmArgs g2, int ntm2, int ntn2)
 {
     if constexpr (CLASSES) ggemm_classes<KIND, 2, 64, DEEP, true>(g1, ntn1, ntn1_small);
     else ggemm_sk_body<KIND, 2, 4, 1, 2, 3, 64, 0, false, true>(g1, 0, ntn1);
     __syncthreads();
-    ggemm_sk_body<kColsT, 2, 4, HALF ? 2 : 4, 2, 4, 32>(g2, ntm2, ntn2);
+    ggemm_sk_body<kColsT, 2, 4, HALF ? 2 : 4, 2, 4, 32, 0, false, false, HALF>(g2, ntm2, ntn2);
 }
 
 // Persistent workgroups of one launch (a multiple of the 8 XCDs, at most kMaxPersistentWgs); 0 after fail_launch.
@@ -1121,6 +1165,7 @@ void launch_pair_cfg(const GemmArgs& rows, const GemmArgs& cols, hipStream_t st)
     if (wgs < 8) return;
     GemmArgs r = rows, c = cols;
     c.on_demand = 1;
+    if constexpr (HALF) c.slices = half_round_slices(r, c);
     const int ntn1 = (r.Nout + C1::BN - 1) / C1::BN, ntn1s = (r.Nout + C1s::BN - 1) / C1s::BN;
     const int ntn2 = (c.Nout + C2::BN - 1) / C2::BN, ntm2 = (c.K + C2::BM - 1) / C2::BM;
     hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(512), SMEM, st, r, ntn1, ntn1s, c, ntm2, ntn2);

@@ -111,6 +111,39 @@ template <class Product> constexpr bool half_round(const Product& a)
     return a.M >= 1024L * a.E && a.E * wide_columns(a) * ((a.K + 127) / 128) <= 224;
 }
 
+// Into how many ranges those tiles' rows are cut (at most eight, and one range for each of 256 workgroups), from an estimate of the launch in
+// microseconds: the rows product's tiles (1.7 a block of 64, and 12) leave `free` workgroups of their last round to start on the ranges at
+// once (0.37 a block of 32 rows, and 8), the others come when it ends; a tile's last workgroup adds its ranges' sums up (3 each, and 6).  Cut only
+// where that is 5 % better.  Against no cuts, 65 drawn launches (1100 to 12600 rows per expert, 18 to 128 tiles) cut once into as many ranges as a rule without the
+// rows product gave: the 26 where this estimate is better took 0.44 to 0.98 of the time (one expert, 9768 rows, K 384, 1408 columns: 122 -> 54 us; 5948 rows, 3
+// experts: 110 -> 75), the others 0.82 to 1.25.  With the
+// ranges that it gives now the 88 launches of that sweep take 0.92 of the time on average, the slowest of them 1.05.
+template <class Product> inline int half_round_slices(const Product& rows, const Product& cols)
+{
+    const long tiles = cols.E * wide_columns(cols) * ((cols.K + 127) / 128), big = wide_tiles(rows), rounds = std::max(1L, (big + 255) / 256);
+    const long free = 256 * rounds - big;
+    const double blocks = cols.M / cols.E / 32.0, round = rows.K / 64 * 1.7 + 12, begin = (rounds - 1) * round, end = rounds * round;
+    auto estimate = [&](int s) {
+        const double each = blocks * 0.37 / s + 8;
+        auto done = [&](double t) {        // ranges that are through by then
+            return (t > begin ? free * (long)((t - begin) / each + 1e-9) : 0) + (t > end ? (256 - free) * (long)((t - end) / each + 1e-9) : 0);
+        };
+        double best = end + 256 * each;    // (one workgroup a range: always enough)
+        for (int n = 1; n <= 32; ++n) {
+            if (done(begin + n * each) >= tiles * s) best = std::min(best, begin + n * each);
+            if (done(end + n * each) >= tiles * s) best = std::min(best, end + n * each);
+        }
+        return std::max(best, end) + (s > 1 ? 6 + 3 * s : 0);
+    };
+    int slices = 1;
+    double least = 0.95 * estimate(1);
+    for (int s = 2; s <= 8 && tiles * s <= 256; ++s) {
+        const double t = estimate(s);
+        if (t < least) { least = t; slices = s; }
+    }
+    return slices;
+}
+
 // A weight gradient in a launch of its own: whether tiles of 128 x 256 beat those of 256 x 256.  A tile's time is mostly that of its gradient's way to
 // memory, so what counts is how much of the last round of tiles (256 at a time) is empty; but a tile half as high reads nearly as much.
 // Both sides' times of 59 products (1 to 200 experts, 5 to 2500 rows each, K 256 to 5700, 500 to 5900 columns), rounds of either in brackets:

@@ -1,4 +1,5 @@
-"""Weight gradients in tiles of 128 x 256 (few tiles, or fp32 gradients that are added to), in launches of their own and behind the rows products: edges of a tile in both directions, experts without rows, with one, 31 to 33
+"""Weight gradients in tiles of 128 x 256 (few tiles, or fp32 gradients that are added to), in launches of their own and behind the rows products, there with an expert's
+rows cut into ranges where the reduction is long (9000 rows in one expert, none or one in others): edges of a tile in both directions, experts without rows, with one, 31 to 33
 and more rows, stored in bf16 or fp32, added to or not, against fp64 sums of the same bf16 operands.  The operands are small integers, so every product and
 every sum is exact in fp32; the only rounding is the result's to bf16 (2^-9 of its magnitude)."""
 import pytest
@@ -7,11 +8,11 @@ from paper_2103_13262_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
-ROWS = {5: [0, 1, 31, 33, 200], 3: [64, 65, 700], 1: [300], 2: [2100, 33], 4: [1, 4000, 0, 321]}
+ROWS = {5: [0, 1, 31, 33, 200], 3: [64, 65, 700], 1: [300], 2: [2100, 33], 4: [1, 4000, 0, 321], 6: [9000, 0, 1, 33, 700, 1]}
 
 
 @pytest.mark.parametrize("grad,accumulate", [("bf16", 0), ("f32", 0), ("f32", 1), ("bf16", 1)])
-@pytest.mark.parametrize("E,d,h", [(5, 128, 256), (5, 160, 288), (3, 384, 4096), (1, 1056, 2080), (3, 32, 64), (5, 96, 544), (2, 160, 1056), (4, 544, 288), (2, 1088, 2080)])
+@pytest.mark.parametrize("E,d,h", [(5, 128, 256), (5, 160, 288), (3, 384, 4096), (1, 1056, 2080), (3, 32, 64), (5, 96, 544), (2, 160, 1056), (4, 544, 288), (2, 1088, 2080), (6, 128, 96)])
 def test_weight_gradients(E, d, h, grad, accumulate):
     import torch
 
