@@ -4,13 +4,15 @@
 //
 //   plan_hist  : per chunk of assignments, an LDS histogram over experts (batches of more than kOwnCounts assignments only).
 //   plan_place : workgroup 0 writes the tables - counts, offsets, tile prefix tables for four row-tile heights, size
-//                classes, experts ordered by descending count, the control block; every other workgroup places the
-//                assignments of one chunk.  All of them work out the counts and offsets they need for themselves (from the
+//                classes; workgroup 1 the experts in order of descending count and the control block; every other workgroup
+//                places the assignments of one chunk.  All of them work out the counts and offsets they need for themselves (from the
 //                chunk histograms, or from the indices where those are few), so that the placing does not wait for a
 //                launch of one workgroup in front of it.  Ranks inside a wavefront come from ballots (lanes that hold the same
 //                expert are found bit by bit), so rows keep assignment order.
 // Bound by latency.  With the tables in a launch of one workgroup and the placing behind it: 12.4 us at 8192 assignments and 16
-// experts, 17.2 us at 200 and 256, 21.5 us at 16384 and 256, 29.0 us at 65536 and 32; now 8.8, 8.4, 14.2 and 11.0 us.
+// experts, 17.2 us at 200 and 256, 21.5 us at 16384 and 256, 29.0 us at 65536 and 32; then
+// 8.8, 8.4, 14.2 and 11.0 us; with the order in a workgroup of its own beside the tables 0.6 us less for few experts, 1.8 less for 256 (gate and plan of 200 tokens
+// 17.4 -> 15.5) and 3.4 less for 600.
 #include "common.h"
 
 namespace moe {
@@ -89,8 +91,8 @@ __global__ __launch_bounds__(kThreads) void plan_place(const int32_t* __restrict
     int* const s_w = s_below + Ep;                  // [kWaves][Ep] (placing)
     __shared__ int s_wave[kWaves * (3 + kNumTileHeights)];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool tables = blockIdx.x == 0;
-    const int b = (int)blockIdx.x - 1;              // this workgroup's chunk
+    const bool tables = blockIdx.x < 2;             // workgroup 0: counts, offsets, tiles, size classes; 1: the experts in order
+    const int b = (int)blockIdx.x - 2;              // this workgroup's chunk
     const long base = (long)b * chunk;
     auto index = [&](long a) {                      // (an index out of range cannot come from the gate kernels)
         int e = -1;
@@ -98,11 +100,10 @@ __global__ __launch_bounds__(kThreads) void plan_place(const int32_t* __restrict
         return e;
     };
     int ev = tables ? -1 : index(base + tid);       // first round, on its way while the counts are taken
-    // the control words of the grouped products, and the counters of the backward pass's sums
-    if (tables) {
-        if (tid < kCtlWords) control[tid] = 0;
+    // the control words of the grouped products
+    if (blockIdx.x == 1 && tid < kCtlWords) control[tid] = 0;
+    if (blockIdx.x == gridDim.x - 1)                // the counters of the backward pass's sums
         for (int i = tid; i < arrive_words; i += kThreads) arrive[i] = 0;
-    }
     for (int e = tid; e < 2 * Ep; e += kThreads) s_total[e] = 0;
     __syncthreads();
     if (hist) {
@@ -181,35 +182,38 @@ __global__ __launch_bounds__(kThreads) void plan_place(const int32_t* __restrict
     // ---- the tables ----
     const int e = tid;
     const int cnt = e < E ? s_total[e] : 0;
-    if (e < E) counts[e] = cnt;
-    // one pass of scans: offsets, the tile prefix tables of every tile height, the two size classes of every expert's rows
-    int nbig = cnt / kClsBigRows, last = cnt - nbig * kClsBigRows;
-    if (last > kClsSmallRows) { ++nbig; last = 0; }
-    constexpr int NV = 3 + kNumTileHeights;
-    int sc[NV], total[NV];
-    sc[0] = cnt;
-    sc[1] = e < E ? nbig : 0;
-    sc[2] = e < E && last > 0 ? 1 : 0;
+    if (blockIdx.x == 0) {
+        if (e < E) counts[e] = cnt;
+        // one pass of scans: offsets, the tile prefix tables of every tile height, the two size classes of every expert's rows
+        int nbig = cnt / kClsBigRows, last = cnt - nbig * kClsBigRows;
+        if (last > kClsSmallRows) { ++nbig; last = 0; }
+        constexpr int NV = 3 + kNumTileHeights;
+        int sc[NV], total[NV];
+        sc[0] = cnt;
+        sc[1] = e < E ? nbig : 0;
+        sc[2] = e < E && last > 0 ? 1 : 0;
 #pragma unroll
-    for (int q = 0; q < kNumTileHeights; ++q) sc[3 + q] = e < E ? (cnt + tile_height(q) - 1) / tile_height(q) : 0;
-    block_excl_scan_1024<NV>(sc, (int (*)[NV])s_wave, total, E);
-    const int off = sc[0];
-    if (e < E) {
-        offsets[e] = off;
-        cls[kClsCountsBig * (E + 1) + e] = min(cnt, nbig * kClsBigRows);
-        cls[kClsCountsSmall * (E + 1) + e] = last;
-        cls[kClsOffsetsSmall * (E + 1) + e] = off + nbig * kClsBigRows;
-        cls[kClsPBig * (E + 1) + e] = sc[1];
-        cls[kClsPSmall * (E + 1) + e] = sc[2];
+        for (int q = 0; q < kNumTileHeights; ++q) sc[3 + q] = e < E ? (cnt + tile_height(q) - 1) / tile_height(q) : 0;
+        block_excl_scan_1024<NV>(sc, (int (*)[NV])s_wave, total, E);
+        const int off = sc[0];
+        if (e < E) {
+            offsets[e] = off;
+            cls[kClsCountsBig * (E + 1) + e] = min(cnt, nbig * kClsBigRows);
+            cls[kClsCountsSmall * (E + 1) + e] = last;
+            cls[kClsOffsetsSmall * (E + 1) + e] = off + nbig * kClsBigRows;
+            cls[kClsPBig * (E + 1) + e] = sc[1];
+            cls[kClsPSmall * (E + 1) + e] = sc[2];
 #pragma unroll
-        for (int q = 0; q < kNumTileHeights; ++q) tileP[q * (E + 1) + e] = sc[3 + q];
-    }
-    if (e == 0) {
-        offsets[E] = total[0];
-        cls[kClsPBig * (E + 1) + E] = total[1];
-        cls[kClsPSmall * (E + 1) + E] = total[2];
+            for (int q = 0; q < kNumTileHeights; ++q) tileP[q * (E + 1) + e] = sc[3 + q];
+        }
+        if (e == 0) {
+            offsets[E] = total[0];
+            cls[kClsPBig * (E + 1) + E] = total[1];
+            cls[kClsPSmall * (E + 1) + E] = total[2];
 #pragma unroll
-        for (int q = 0; q < kNumTileHeights; ++q) tileP[q * (E + 1) + E] = total[3 + q];
+            for (int q = 0; q < kNumTileHeights; ++q) tileP[q * (E + 1) + E] = total[3 + q];
+        }
+        return;
     }
     // Experts by descending count, ties by ascending id.  Up to 256: everybody's rank is counted, 1024 / (E rounded up to a
     // power of two) threads per expert sharing the comparisons.  More (the comparisons grow with E^2: 1000 experts
@@ -292,7 +296,7 @@ void launch_plan(const moe_desc_t& D, const WsLayout& L, const int32_t* topk_idx
     const bool own = M <= kOwnCounts;
     if (!own) hipLaunchKernelGGL(plan_hist, dim3(L.nb), dim3(kThreads), 0, st, topk_idx, M, D.E, chunk, hist);
     if (!allow_dynamic_lds<plan_place>((2 + kWaves) * kMaxE * (int)sizeof(int))) return;
-    hipLaunchKernelGGL(plan_place, dim3(L.nb + 1), dim3(kThreads), (2 + kWaves) * Ep * sizeof(int), st, topk_idx,
+    hipLaunchKernelGGL(plan_place, dim3(L.nb + 2), dim3(kThreads), (2 + kWaves) * Ep * sizeof(int), st, topk_idx,
                        own ? (const int32_t*)nullptr : hist, L.nb, chunk, D.E, nbits, M, counts, offsets, (int32_t*)(ws + L.tileP),
                        (int32_t*)(ws + L.order), (int32_t*)(ws + L.cls), (int32_t*)(ws + L.control), (int32_t*)(ws + L.arrive), D.E * L.arrive_cols,
                        pos, perm);
