@@ -164,8 +164,9 @@ void launch_gate_topk(const moe_desc_t& D, const void* X, const void* Wg, const 
 // margin, fp64 for the k selected logits and for the tokens that cannot be certified (gate_fail: [1 + N] int32 scratch)
 void launch_gate_bf16(const moe_desc_t& D, const void* X, const void* Wg, const float* bg, int32_t* topk_idx, float* topk_w,
                       void* WgT, int32_t* gate_fail, hipStream_t st);
-// few enough tokens: another kernel behind the transposition, or false
-bool launch_gate_rows(const moe_desc_t& D, const void* X, const void* WgT, const float* bg, int32_t* topk_idx, float* topk_w, int32_t* gate_fail,
+// few enough tokens (gate_rows_pays): another kernel behind the transposition
+bool gate_rows_pays(const moe_desc_t& D);
+void launch_gate_rows(const moe_desc_t& D, const void* X, const void* WgT, const float* bg, int32_t* topk_idx, float* topk_w, int32_t* gate_fail,
                       hipStream_t st);
 // (WgT: [E][d] scratch for the transposed gate matrix; logits [N][E]: only with desc.score_all or desc.balance_stats, else NULL; holds the
 // gate probabilities afterwards)

@@ -437,7 +437,10 @@ void launch_gate_bf16(const moe_desc_t& D, const void* X, const void* Wg, const 
     const long n = (long)D.d * D.E;
     hipLaunchKernelGGL(gate_prep<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const T*)Wg, (T*)WgT, D.d, D.E, fail);
     if (D.N == 0) return;
-    if (launch_gate_rows(D, X, WgT, bg, topk_idx, topk_w, fail, st)) return;
+    if (gate_rows_pays(D)) {
+        launch_gate_rows(D, X, WgT, bg, topk_idx, topk_w, fail, st);
+        return;
+    }
     if (D.E <= 64) launch_fast<64>(D, (const u16*)X, (const u16*)WgT, bg, topk_idx, topk_w, fail, st);
     else if (D.E <= 128) launch_fast<128>(D, (const u16*)X, (const u16*)WgT, bg, topk_idx, topk_w, fail, st);
     else launch_fast<256>(D, (const u16*)X, (const u16*)WgT, bg, topk_idx, topk_w, fail, st);

@@ -44,20 +44,6 @@ template <int CG, int NB> struct Lds {
 constexpr int kLdsBytes = 160 * 1024;
 inline int padded(int d) { return (d + 127) / 128 * 128; }
 
-// Whether this kernel beats that of gate_bf16.hip.  Both sides' times (gate and plan together, top-2) of d 256 to 4096, 20 to 256 experts, 1500
-// to 32768 tokens:
-//   * up to a workgroup per compute unit (4096 tokens) always: 0.47 to 0.95 of the time (1500 tokens, d 1024, 32 experts 27 -> 19 us; d 2048, 64
-//     experts 39 -> 28; d 256, 256 experts 27 -> 24);
-//   * up to two with at most 64 experts and d at least 1024: 0.68 to 0.97 (8192 tokens, d 2048, 32 experts 45 -> 36; d 1024, 64 experts 32 -> 31; beyond
-//     either line 0.91 to 1.5: d 512, 256 experts 35 -> 42; d 1024, 128 experts 35 -> 39);
-//   * up to three with at most 32: 0.79 to 0.94 (12000 tokens, d 1024, 32 experts 36 -> 34; with 64 experts 38 -> 39).  More tokens: 0.88 to 2.2.
-bool rows_pay(const moe_desc_t& D)
-{
-    if (padded(D.d) * kTok * 2 + Lds<8, 2>::kOther > kLdsBytes) return false;   // (d above 4480)
-    const int groups = (D.N + kTok - 1) / kTok;
-    return groups <= 256 || (D.d >= 1024 && ((groups <= 512 && D.E <= 64) || (groups <= 768 && D.E <= 32)));
-}
-
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
 __device__ __forceinline__ bool better(double v, int i, double bv, int bi) { return v > bv || (v == bv && i < bi); }
 
@@ -382,10 +368,24 @@ void launch_rows(const moe_desc_t& D, const u16* X, const u16* WgT, const float*
 
 }  // namespace
 
-bool launch_gate_rows(const moe_desc_t& D, const void* X, const void* WgT, const float* bg, int32_t* topk_idx, float* topk_w, int32_t* fail,
+// Whether this kernel beats that of gate_bf16.hip.  Both sides' times (gate and plan together, top-2) of d 256 to 4096, 20 to 256 experts, 1500
+// to 32768 tokens:
+//   * up to a workgroup per compute unit (4096 tokens) always: 0.47 to 0.95 of the time (1500 tokens, d 1024, 32 experts 27 -> 19 us; d 2048, 64
+//     experts 39 -> 28; d 256, 256 experts 27 -> 24), and the gate alone with d 32 to 224 0.67 to 1.04 (1024 to 4096 tokens, top-1, 2 and 8; above
+//     1 only with 256 experts: d 128, 1024 tokens 17.8 -> 18.6);
+//   * up to two with at most 64 experts and d at least 1024: 0.68 to 0.97 (8192 tokens, d 2048, 32 experts 45 -> 36; d 1024, 64 experts 32 -> 31; beyond
+//     either line 0.91 to 1.5: d 512, 256 experts 35 -> 42; d 1024, 128 experts 35 -> 39);
+//   * up to three with at most 32: 0.79 to 0.94 (12000 tokens, d 1024, 32 experts 36 -> 34; with 64 experts 38 -> 39).  More tokens: 0.88 to 2.2.
+bool gate_rows_pays(const moe_desc_t& D)
+{
+    if (padded(D.d) * kTok * 2 + Lds<8, 2>::kOther > kLdsBytes) return false;   // (d above 4480)
+    const int groups = (D.N + kTok - 1) / kTok;
+    return groups <= 256 || (D.d >= 1024 && ((groups <= 512 && D.E <= 64) || (groups <= 768 && D.E <= 32)));
+}
+
+void launch_gate_rows(const moe_desc_t& D, const void* X, const void* WgT, const float* bg, int32_t* topk_idx, float* topk_w, int32_t* fail,
                       hipStream_t st)
 {
-    if (!rows_pay(D)) return false;
     auto go = [&](auto cg, auto nb) { launch_rows<decltype(cg)::value, decltype(nb)::value>(D, (const u16*)X, (const u16*)WgT, bg, topk_idx, topk_w, fail, st); };
     using C1 = std::integral_constant<int, 1>;
     using C8 = std::integral_constant<int, 8>;
@@ -393,7 +393,6 @@ bool launch_gate_rows(const moe_desc_t& D, const void* X, const void* WgT, const
     else if (D.E <= 64) go(std::integral_constant<int, 4>{}, C1{});
     else if (D.E <= 128) go(C8{}, C1{});
     else go(C8{}, std::integral_constant<int, 2>{});
-    return true;
 }
 
 }  // namespace moe

@@ -550,15 +550,20 @@ __global__ __launch_bounds__(256) void gate_scores_all(double* __restrict__ logi
 }
 
 // Whether a workgroup per token (gate_small.hip) beats the tiled kernels: estimates of both in microseconds, the 4 of a pair of events
-// included, fitted to 20266 calls measured both ways (bf16 and fp32, 29 expert counts from 1 to 1024, d 64 to 8192, 1 to 4096 tokens,
-// k 1, 2 and 8, with and without stored logits).  The kernel picked is 0.4 % slower than the better one on average; where it is
-// the small one, it is more than 10 % slower than the tiled one in 41 of 13821 calls.
+// included, fitted to calls measured both ways (29 expert counts from 1 to 1024, d 64 to 8192, 1 to 4096 tokens, k 1, 2 and 8; 20266 of them before
+// gate_rows.hip: the kernel picked was 0.4 % slower than the better one on average).
 //   small: every round of 256 tokens reads the gate matrix and selects k times in one wavefront; up to 256 experts two workgroups
 //          share a compute unit where their LDS allows.  A matrix of at most 32 KB stays in the vector cache.
 //   tiled: the time does not depend on the token count until the chip is full.
+// bf16, 17 to 256 experts, logits not stored: the estimate is that of the kernel that would run, gate_rows.hip's or, with features or tokens beyond it,
+// gate_bf16.hip's; below 256 features the latter's either way, which keeps the small kernel a little long.  Over 5280 calls (64 to 4096
+// tokens, d 32 to 16384, N(0,1) rows) the kernel picked is slower than the better one by 0.7 % on average below 256 features (36 of 1650 calls run in the
+// small one at 1.1 to 1.33 of the other's time), by 0.5 % up to d 4480, by 6 % up to 8192, and by half at 16384, where the error bound leaves so many
+// candidates that gate_bf16.hip takes far longer than its estimate.  (gate_rows.hip's estimate beyond d 4480 too: 23 % up to 8192; 64 experts, k 8, d 6144, 512
+// tokens 66 small / 235 tiled, 1024 tokens 125 / 273.)
 // Small against tiled, k 2, bf16.  8 experts: N 512, d 1024 10.6 / 11.2, N 1024, d 2048 17.3 / 16.4, N 2048, d 8192 77.5 / 46.3.  64 experts: N 512,
-// d 1024 17.3 / 26.1, N 1024, d 1024 28.7 / 26.1; logits stored, N 2048, d 1024 50.4 / 34.0.  256 experts: N 256, d 1024 16.2 / 33.9, N 512, d 1024
-// 36.1 / 34.5.  fp32, 24 experts: N 1024, d 1024 16.5 / 50.2, N 4096, d 1024 46.1 / 49.8, N 4096, d 256 39.3 / 19.9.
+// d 1024 17.0 / 19.6, N 1024, d 1024 28.3 / 19.7; logits stored, N 2048, d 1024 50.4 / 34.0.  256 experts: N 256, d 1024 16.0 / 31.8, N 512, d 1024
+// 35.2 / 32.1.  fp32, 24 experts: N 1024, d 1024 16.5 / 50.2, N 4096, d 1024 46.1 / 49.8, N 4096, d 256 39.3 / 19.9.
 static bool small_batch(const moe_desc_t& D, bool logits)
 {
     if (D.d > kGateSmallMaxD) return false;
@@ -580,8 +585,8 @@ static bool small_batch(const moe_desc_t& D, bool logits)
         small = 5.5 + w * round;
     }
     if (D.E <= 16) tiled = 6.4 + (bf16 ? 4.95 : 6.3) * d + (logits ? 3.0 : 0.0);
-    else if (bf16 && D.E <= 256 && !logits)                    // (gate_rows.hip from 256 features up)
-        tiled = D.d >= 256 ? 9.0 + 1.5 * k + 0.02 * D.E + 4.0 * d + 0.055 * el : 11.3 + 6.0 * d + 2.3 * k + 1.5 * k * d + 0.042 * el;
+    else if (bf16 && D.E <= 256 && !logits)                    // (the first: gate_rows.hip)
+        tiled = D.d >= 256 && gate_rows_pays(D) ? 9.0 + 1.5 * k + 0.02 * D.E + 4.0 * d + 0.055 * el : 11.3 + 6.0 * d + 2.3 * k + 1.5 * k * d + 0.042 * el;
     else if (D.E <= 32) tiled = 6.0 + 40.0 * d + 2.4 * k;
     else tiled = 9.0 + (D.E + 63) / 64 * (2.2 + 13.0 * d + 1.9 * k);
     return small <= tiled;

@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
 LINES = [(512, 1024, 8, 2, "bf16", ""), (512, 512, 12, 2, "f32", ""), (256, 96, 12, 1, "bf16", "scores"),
          (1024, 64, 24, 2, "f32", ""), (1024, 96, 29, 3, "f32", "scores"), (768, 64, 32, 4, "bf16", "scores"), (512, 64, 24, 2, "bf16", "balance"),
          (1024, 64, 40, 3, "bf16", ""), (768, 64, 100, 2, "bf16", ""), (1280, 64, 200, 8, "bf16", ""),
+         (1024, 6144, 64, 8, "bf16", ""),       # (rows that do not fit the LDS of the tiled kernel for few tokens)
          (2048, 160, 70, 3, "f32", ""), (1536, 288, 70, 2, "bf16", "scores"), (1024, 288, 300, 3, "bf16", "")]
 # and far beyond it: several workgroups per compute unit
 CASES = [(n + more, *rest, more == 0) for n, *rest in LINES for more in (0, 1)] + [
