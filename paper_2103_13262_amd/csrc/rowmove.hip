@@ -387,12 +387,29 @@ __device__ __forceinline__ bool last_to_arrive(int32_t* __restrict__ arrive, int
     __syncthreads();
     return s_last;
 }
-// Calls f for every expert without rows, on all threads.
-template <typename F> __device__ __forceinline__ void for_empty(const int32_t* __restrict__ counts, int E, F f)
+// The gate's gradients of experts without rows: zeros, written by `blocks` workgroups.  dWg holds the experts side by side, so it is walked
+// element by element: whole lines where many experts in a row have none, and nothing where all have some.  (Gate backward, bf16, in a workgroup per
+// column block that went from expert to expert: 100 tokens, d 2048, 1000 experts, top-2 226 us, so 16; 64 tokens, d 1024, 256 experts 58, 9; 2000
+// tokens, d 2048, 256 experts, most of them without rows 78, 16.)
+constexpr int kZeroElements = 4096;                    // about as many elements for a workgroup
+template <typename G>
+__device__ __forceinline__ void zero_empty(unsigned block, unsigned blocks, const int32_t* __restrict__ counts, G* __restrict__ dWg,
+                                           float* __restrict__ dbg, int d, int E)
 {
-    const int lane = threadIdx.x & 63;
-    for (int e0 = 0; e0 < E; e0 += 64)
-        for (unsigned long long m = __ballot(e0 + lane < E && counts[min(e0 + lane, E - 1)] == 0); m; m &= m - 1) f(e0 + __ffsll(m) - 1);
+    bool some = false;
+    for (int e = threadIdx.x; e < E; e += 512) some = some || counts[e] == 0;
+    if (!__syncthreads_or(some)) return;
+    const unsigned first = block * 512 + threadIdx.x, step = blocks * 512, skip = step % (unsigned)E;
+    unsigned e = first % (unsigned)E;
+#pragma unroll 4
+    for (size_t i = first; i < (size_t)d * E; i += step) {
+        if (counts[e] == 0) dWg[i] = 0;
+        e += skip;
+        if (e >= (unsigned)E) e -= E;
+    }
+    if (block == 0 && dbg)
+        for (int q = threadIdx.x; q < E; q += 512)
+            if (counts[q] == 0) dbg[q] = 0.f;
 }
 // Sum over pieces first .. next - 1 of part[q][c], in ascending order.
 __device__ __forceinline__ float sum_pieces(const float* __restrict__ part, int first, int next, int d, int c)
@@ -431,9 +448,10 @@ __global__ __launch_bounds__(512) void dwg_partial(const void* __restrict__ Xs, 
 // Plain column sums of two row matrices over the same segments (the gradients of both layers' biases), side by side in one launch:
 // the column blocks of the first, then those of the second, going round from piece to piece so that an XCD (workgroup number
 // modulo 8) does not get the same ones of all pieces.
-// An expert's pieces are added up by the last of their workgroups; what has no rows is left to one more
-// workgroup per column block.  With the additions in a launch of their own, and the gate's (below)
+// An expert's pieces are added up by the last of their workgroups; experts without rows are left to more workgroups
+// behind, one for kZeroExperts experts and a column block.  With the additions in a launch of their own, and the gate's (below)
 // likewise, a training step of 1000 tokens, 8 experts, d 768, h 3072, top-2 took 280 us, now 277.5.
+constexpr int kZeroExperts = 16;
 struct ColumnSums { const void* src; float* part; float* out; int width, cpr; };
 __device__ __forceinline__ void put_sum(float* out, float s, int accumulate) { *out = accumulate ? *out + s : s; }
 template <typename T>
@@ -449,8 +467,10 @@ __global__ __launch_bounds__(512) void segment_sums(ColumnSums a, ColumnSums b, 
     const int col = x < first ? x : x - first, c = col * 64 * V + (int)threadIdx.x;
     const bool mine = (int)threadIdx.x < 64 * V && c < s.width;
     if (piece >= pieces) {                          // experts without rows
-        if (piece > pieces || accumulate) return;
-        for_empty(counts, E, [&](int e) { if (mine) s.out[(size_t)e * s.width + c] = 0.f; });
+        if (accumulate || piece - pieces > E / kZeroExperts) return;
+        const int e0 = (int)(piece - pieces) * kZeroExperts;
+        for (int e = e0; e < min(e0 + kZeroExperts, E); ++e)
+            if (counts[e] == 0 && mine) s.out[(size_t)e * s.width + c] = 0.f;
         return;
     }
     const Segment sg = segment_partial<T, true>(s.src, nullptr, nullptr, counts, offsets, P64, s.part, nullptr, E, s.width, s.cpr, (int)piece, col);
@@ -510,7 +530,7 @@ __global__ __launch_bounds__(256) void gate_bwd_tail(int fgx, const float* __res
 }
 
 // Gate backward in one launch, for a call that has the transposed gate matrix already: workgroups of pieces first, each expert's sums added
-// up by the last of them; then a workgroup per column block for the experts without rows; then dX.  None of these reads
+// up by the last of them; then `zeros` workgroups for the experts without rows; then dX.  None of these reads
 // what another writes.  Bound by latency in small batches, by HBM in large ones.  A step against one whose sums are added up in a second
 // launch beside dX: 256 tokens, d 64, 4 experts, fp32 42.6 -> 41.1 us; 16384 tokens, d 512, 256 experts, top-1 507.6 -> 505.1; 8192, d 1024, 64
 // experts 1426 -> 1423.
@@ -518,15 +538,19 @@ template <typename T, typename G, int K>
 __global__ __launch_bounds__(512) void gate_bwd_whole(const void* __restrict__ Xs, const float* __restrict__ dl, const int32_t* __restrict__ perm,
                                                       const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
                                                       const int32_t* __restrict__ P64, float* __restrict__ part, float* __restrict__ bpart,
-                                                      int32_t* __restrict__ arrive, int pieces, int cols, G* __restrict__ dWg, float* __restrict__ dbg,
+                                                      int32_t* __restrict__ arrive, int pieces, int cols, int zeros, G* __restrict__ dWg, float* __restrict__ dbg,
                                                       int d, int E, int accumulate, const void* __restrict__ dXs, const void* __restrict__ WgT,
                                                       const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ pos, void* __restrict__ dX,
                                                       long N, int k, int cpr)
 {
     constexpr int V = Vec<T>::N;
-    const int nsum = (pieces + 1) * cols;
+    const int nsum = pieces * cols, front = nsum + zeros;
+    if ((int)blockIdx.x >= front) {
+        gate_bwd_dx_body<T, K, 512>((long)blockIdx.x - front, (long)gridDim.x - front, dXs, WgT, dl, topk_idx, pos, dX, N, k, cpr);
+        return;
+    }
     if ((int)blockIdx.x >= nsum) {
-        gate_bwd_dx_body<T, K, 512>((long)blockIdx.x - nsum, (long)gridDim.x - nsum, dXs, WgT, dl, topk_idx, pos, dX, N, k, cpr);
+        zero_empty(blockIdx.x - nsum, zeros, counts, dWg, dbg, d, E);
         return;
     }
     // (as in dwg_partial: the column blocks of a piece are neighbours, and two of them change places every four pieces)
@@ -543,14 +567,6 @@ __global__ __launch_bounds__(512) void gate_bwd_whole(const void* __restrict__ X
             dWg[i] = s;
         }
     };
-    if (piece == pieces) {                              // experts without rows
-        if (accumulate) return;
-        for_empty(counts, E, [&](int e) {
-            if (mine) put(e, 0.f);
-            if (dbg && col == 0 && threadIdx.x == 0) dbg[e] = 0.f;
-        });
-        return;
-    }
     const Segment sg = segment_partial<T, true>(Xs, dl, perm, counts, offsets, P64, part, bpart, E, d, cpr, piece, col);
     if (sg.e < 0 || !last_to_arrive(arrive + sg.e * cols + col, sg.next - sg.first)) return;
     if (mine) put(sg.e, sum_pieces(part, sg.first, sg.next, d, c));
@@ -671,7 +687,9 @@ void launch_gate_bwd_whole(const moe_desc_t& D, const WsLayout& L, const void* X
                            const int32_t* counts, const int32_t* offsets, void* dX, void* dWg, float* dbg, char* ws, hipStream_t st)
 {
     const int cpr = (int)((size_t)D.d * dtype_size(D.dtype) / 16), cols = (cpr + 63) / 64;
-    const long dx_blocks = std::min<long>(((long)D.N * cpr + 511) / 512, 256 * 16), blocks = (L.dwg_pieces + 1) * cols + dx_blocks;
+    const long dx_blocks = std::min<long>(((long)D.N * cpr + 511) / 512, 256 * 16);
+    const int zeros = D.accumulate ? 0 : (int)std::min<long>(((long)D.d * D.E + kZeroElements - 1) / kZeroElements, 1024);
+    const long blocks = L.dwg_pieces * cols + zeros + dx_blocks;
     if (blocks > 4 << 20) {                             // (a launch holds less than 2^32 threads)
         launch_gate_bwd(D, L, Xs, dXs, Wg, dl, topk_idx, pos, perm, counts, offsets, dX, dWg, dbg, ws, st);
         return;
@@ -682,7 +700,7 @@ void launch_gate_bwd_whole(const moe_desc_t& D, const WsLayout& L, const void* X
         using G = decltype(gv);
         with_k(D.k, [&](auto kc) {
             hipLaunchKernelGGL((gate_bwd_whole<T, G, decltype(kc)::value>), dim3((unsigned)blocks), dim3(512), 0, st, Xs, dl, perm, counts, offsets,
-                               P64, (float*)(ws + L.dwg_part), (float*)(ws + L.dbg_part), (int32_t*)(ws + L.arrive), (int)L.dwg_pieces, cols,
+                               P64, (float*)(ws + L.dwg_part), (float*)(ws + L.dbg_part), (int32_t*)(ws + L.arrive), (int)L.dwg_pieces, cols, zeros,
                                (G*)dWg, dbg, D.d, D.E, D.accumulate, dXs, (const void*)(ws + L.WgT), topk_idx, pos, dX, (long)D.N, D.k, cpr);
         });
     };
@@ -702,7 +720,7 @@ void launch_bias_sums(const moe_desc_t& D, const WsLayout& L, const int32_t* cou
     const int cols = (a.cpr + 63) / 64 + (b.cpr + 63) / 64;
     if (!cols) return;
     const int32_t* P64 = (const int32_t*)(ws + L.tileP) + tile_height_index(64) * (D.E + 1);
-    const dim3 pg = piece_grid(L.dwg_pieces + 1, cols);
+    const dim3 pg = piece_grid(L.dwg_pieces + (D.accumulate ? 0 : (D.E + kZeroExperts - 1) / kZeroExperts), cols);
     auto launch = [&](auto kern) {
         hipLaunchKernelGGL(kern, pg, dim3(512), 0, st, a, b, counts, offsets, P64, D.E, (int32_t*)(ws + L.arrive), L.dwg_pieces, D.accumulate);
     };
