@@ -20,6 +20,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) double f64x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef unsigned short u16;
 
@@ -33,13 +34,13 @@ static_assert(kCand > kMaxK && kTokW * 32 == 64, "32 lanes per token must hold t
 
 // CG column groups of NB blocks of 16 experts, KP parts of the reduction: CG KP wavefronts.  LDS: the tokens' rows (16 x dp features, in
 // 16-byte chunks; chunk c of row r lies at place c ^ r of its group of 16, so that the rows of a fragment read fall into different
-// banks), the parts' fp32 logits [KP][16][16 CG NB + 1] (then one token's fp64 logits), the candidates' expert ids, the parts' largest S, and
-// the tokens of (4).
+// banks), the parts' fp32 logits [KP][16][16 CG NB + 1] (then the fp64 ones of eight tokens), the candidates' expert ids, the parts' largest S, and
+// which tokens are left to (4).
 template <int CG, int NB> struct Lds {
     static constexpr int KP = kWaves / CG, E16 = 16 * CG * NB;
     static constexpr int kLogits = (KP * kTok * (E16 + 1) * 4 + 15) / 16 * 16;
-    static constexpr int kOther = kLogits + kTok * kCand * 4 + 16 * 4 + (kTok + 1) * 4 + 12;
-    static_assert(kLogits >= E16 * 8, "a token's logits in fp64");
+    static constexpr int kOther = kLogits + kTok * kCand * 4 + 16 * 4 + 16;
+    static_assert(kLogits >= KP * kWaves * E16 * 8, "the parts' fp64 logits of a token per wavefront");
 };
 constexpr int kLdsBytes = 160 * 1024;
 inline int padded(int d) { return (d + 127) / 128 * 128; }
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(kWaves * 64, 4) void gate_rows_kernel(const u16* __
     float (*s_logit)[kTok][L::E16 + 1] = (float (*)[kTok][L::E16 + 1])other;
     int (*s_cand)[kCand] = (int (*)[kCand])(other + L::kLogits);
     int* s_maxabs = (int*)(other + L::kLogits + kTok * kCand * 4);  // [KP] bit patterns of the parts' largest S
-    int* s_left = s_maxabs + 16;                                    // how many tokens are left to (4), and which
+    unsigned* s_left = (unsigned*)(s_maxabs + 16);                  // bit r: token r is left to (4)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cg = wave % CG, kp = wave / CG;
     const long t0 = (long)blockIdx.x * kTok;
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(kWaves * 64, 4) void gate_rows_kernel(const u16* __
         }
     }
     if (tid < KP) s_maxabs[tid] = 0;
-    if (tid == 0) s_left[0] = 0;
+    if (tid == 0) *s_left = 0;
     float bias_sel[NC];                                             // the biases of experts lane + 64 c, for the selection below
 #pragma unroll
     for (int c = 0; c < NC; ++c) bias_sel[c] = (bg && lane + 64 * c < E) ? bg[lane + 64 * c] : 0.f;
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(kWaves * 64, 4) void gate_rows_kernel(const u16* __
         }
         n_cand[q] = band < INFINITY && n >= k && n <= kCand ? n : 0;
         if (!n_cand[q] && lane == 0 && t0 + r < N) {
-            s_left[1 + atomicAdd(&s_left[0], 1)] = r;
+            atomicOr(s_left, 1u << r);
             fail[1 + atomicAdd(fail, 1)] = (int32_t)(t0 + r);
         }
     }
@@ -322,34 +323,63 @@ __global__ __launch_bounds__(kWaves * 64, 4) void gate_rows_kernel(const u16* __
         select_k<1, 32>(mine, my_e, k, n_mine > 0 && t0 + r < N, t0 + r, topk_idx, topk_w);
     }
 
-    // ---- (4): all E logits in fp64, four experts at a time and wavefront (their loads are in flight together)
-    double* const s_l64 = (double*)s_logit;
-    const int left = s_left[0];                                     // (uniform over the workgroup)
-    for (int n = 0; n < left; ++n) {
-        const int r = s_left[1 + n];
-        auto row = [&](int c) { return token(r, c); };
-        __syncthreads();                                            // the logits of the token before are done with
-        for (int e0 = wave * 4; e0 < E; e0 += kWaves * 4) {
-            const u16* w[4];
+    // ---- (4): all logits of all 16 tokens in fp64 on the matrix cores (v_mfma_f64_16x16x4_f64; operand lane l: row / column l % 16 at depth l / 16,
+    // result register v of lane l: row 4 v + l / 16, column l % 16), the parts as in (1), every expert's sum in the same order; then eight
+    // tokens at a time through LDS, a wavefront each.  Such tokens come together: padding is a block of zero rows, a row that is not finite unsettles its
+    // workgroup.  (1500 tokens, d 1024, 256 experts, gate_prep included: 33 us, with 16 zero rows side by side 72; one token after the other
+    // 340, in gate_fix_kernel behind the slab kernel 173.  4096 tokens, d 2048, 64 experts, half of them zero: 69, 166 and 155; all logits equal 93, 189 and 267.)
+    const unsigned left = *s_left;                                  // (uniform over the workgroup)
+    if (left == 0) return;
+    f64x4 sum[NB][2];                                               // two chains, so that a step does not wait for the one before
 #pragma unroll
-            for (int u = 0; u < 4; ++u) w[u] = WgT + (size_t)min(e0 + u, E - 1) * d;
-            double s[4];
-            dots_fp64<4, 64>(row, w, d, lane, s);
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                for (int off = 32; off > 0; off >>= 1) s[u] += __shfl_xor(s[u], off, 64);
-                if (bg && e0 + u < E) s[u] += (double)bg[e0 + u];
-                if (lane == 0 && e0 + u < E) s_l64[e0 + u] = s[u] == s[u] ? s[u] : -INFINITY;
-            }
+        for (int v = 0; v < 4; ++v) { sum[b][0][v] = 0.0; sum[b][1][v] = 0.0; }
+    auto multiply64 = [&](int s, const u32x4 (&w)[FLY][NB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < FLY; ++i) {
+            if (s + i >= s1) break;
+            const u32x4 a = token(frow, (s + i) * 4 + fq);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    sum[b][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(wide_lo(a[q]), wide_lo(w[i][b][q]), sum[b][0], 0, 0, 0);
+                    sum[b][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(wide_hi(a[q]), wide_hi(w[i][b][q]), sum[b][1], 0, 0, 0);
+                }
         }
+    };
+    fetch(s0, wv[0]);
+    for (int s = s0; s < s1; s += 2 * FLY) {
+        fetch(s + FLY, wv[1]);
+        multiply64(s, wv[0]);
+        fetch(s + 2 * FLY, wv[0]);
+        multiply64(s + FLY, wv[1]);
+    }
+    double (*const s_l64)[kWaves][L::E16] = (double (*)[kWaves][L::E16])s_logit;
+#pragma unroll
+    for (int half = 0; half < kTok / kWaves; ++half) {
+        if (half) __syncthreads();                                  // the logits of the tokens before are done with
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+                s_l64[kp][4 * v + fq][(cg * NB + b) * 16 + frow] = sum[b][0][2 * half + v] + sum[b][1][2 * half + v];
         __syncthreads();
-        if (wave == 0) {
+        const int r = half * kWaves + wave;
+        if (left >> r & 1) {
             double v[NC]; int id[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                const bool in = lane + 64 * c < E;
-                v[c] = in ? s_l64[lane + 64 * c] : -INFINITY;
-                id[c] = in ? lane + 64 * c : kNone;
+                const int e = lane + 64 * c;
+                v[c] = -INFINITY; id[c] = kNone;
+                if (e < E) {
+                    double l = s_l64[0][wave][e];
+#pragma unroll
+                    for (int p = 1; p < KP; ++p) l += s_l64[p][wave][e];
+                    if (bg) l += (double)bg[e];
+                    v[c] = l == l ? l : -INFINITY; id[c] = e;
+                }
             }
             select_k<NC, 64>(v, id, k, true, t0 + r, topk_idx, topk_w);
         }
