@@ -146,15 +146,22 @@ template <class Product> inline int half_round_slices(const Product& rows, const
 
 // A weight gradient in a launch of its own: whether tiles of 128 x 256 beat those of 256 x 256.  A tile's time is mostly that of its gradient's way to
 // memory, so what counts is how much of the last round of tiles (256 at a time) is empty; but a tile half as high reads nearly as much.
-// Both sides' times of 59 products (1 to 200 experts, 5 to 2500 rows each, K 256 to 5700, 500 to 5900 columns), rounds of either in brackets:
+// Both sides' times (1 to 200 experts, 2 to 2900 rows each, K 256 to 5700, 500 to 6100 columns), rounds of either in brackets:
 //   * a single round of the smaller ones: 0.68 to 0.88 of the time (88 and 132 tiles, added up in fp32: 66 -> 45 us; 105 and 189: 17 -> 14);
-//   * a third more rounds of the smaller ones at most (3 and 4): 0.87 to 0.95 (88 -> 77, 28 -> 26);
-//   * half as many more (2 and 3, 4 and 6) where fp32 gradients are added to, which is read as well: 0.89 and 1.0; otherwise 0.95 to 1.13.
+//   * as many rounds of either, up to 1000 rows per expert: 91 products, 0.90 on average, 0.69 to 1.09; three with more rows 0.77 to 1.20;
+//   * a third more rounds of the smaller ones (3 and 4), up to 500 rows, an expert's tiles a multiple of eight, so that every XCD gets as many: 11
+//     products, 0.91, 0.84 to 1.0; 85 others 0.96, up to 1.11 (16 experts, K 544, 2752 columns: 24 -> 26); added up in fp32 whatever the tiles: 10, 0.86;
+//   * half as many more (2 and 3, 4 and 6) where fp32 gradients are added to, which is read as well, up to 500 rows: 49, 0.94, 0.84 to 1.04; with more
+//     rows 54, 1.0, up to 1.2 (822 rows, 5 experts, K 672, 5024 columns: 65 -> 77).
 // Beyond: 0.97 to 1.26.
 template <class Product> constexpr bool half_tiles_pay(const Product& a)
 {
-    const long columns = a.E * wide_columns(a), whole = (columns * ((a.K + 255) / 256) + 255) / 256, half = (columns * ((a.K + 127) / 128) + 255) / 256;
-    return half <= 1 || half * 3 <= whole * 4 || (a.accumulate && a.out_f32 && half * 2 <= whole * 3);
+    const long columns = a.E * wide_columns(a), high = (a.K + 127) / 128, whole = (columns * ((a.K + 255) / 256) + 255) / 256, half = (columns * high + 255) / 256;
+    if (half <= 1) return true;
+    if (half == whole) return a.M < 1000L * a.E;
+    if (a.M >= 500L * a.E) return false;
+    if (a.accumulate && a.out_f32) return half * 2 <= whole * 3;
+    return half * 3 <= whole * 4 && wide_columns(a) * high % 8 == 0;
 }
 
 // 64-bit offsets, 96 rows per expert and more: whether the two size classes beat 64 x 256 tiles.  Millions of columns: always (one expert, 100 to
