@@ -2,6 +2,8 @@
 import os
 import subprocess
 
+from test_gpu_half_tiles import CUT, ROWS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 HEAD = r"""
@@ -28,6 +30,39 @@ int main()
 """
 
 
+RANGES = r"""
+bool behind(const Product& rows, const Product& cols) { return pair_pays(rows, 256) && !few_rows(rows) && half_round(cols); }
+int main()
+{
+    // the layers whose ranges are tested on the device: d, h, experts, rows in all
+    const long layers[][4] = {%s};
+    for (auto& l : layers) {
+        const int E = (int)l[2], rows = (int)(l[3] / E);
+        Product by_d = product(rows, E, (int)l[0], (int)l[1]), by_h = product(rows, E, (int)l[1], (int)l[0]);
+        by_d.M = by_h.M = l[3];
+        // dZ (over d) beside dW2 (h high), dXs (over h) beside dW1 (d high)
+        assert(behind(by_d, by_h) && behind(by_h, by_d));
+        assert(half_round_slices(by_d, by_h) > 1 && half_round_slices(by_h, by_d) > 1);
+    }
+    // a range for each of 256 workgroups at most, and a counter and a place for each range's sum
+    long cut = 0;
+    for (int E : {1, 2, 3, 5, 8, 16, 40, 120, 224})
+        for (int rows = 1024; rows <= 300000; rows += 1 + rows / 3)
+            for (int K = 32; K <= 6000; K += 32 + K / 3)
+                for (int Nout = 32; Nout <= 6000; Nout += 32 + Nout / 3) {
+                    const Product cols = product(rows, E, K, Nout), dxs = product(rows, E, Nout, K);
+                    if (!behind(dxs, cols)) continue;
+                    const int s = half_round_slices(dxs, cols);
+                    const long tiles = E * wide_columns(cols) * ((K + 127) / 128);
+                    assert(s >= 1 && s <= 8 && tiles <= 256 && tiles * s <= 256);
+                    cut += s > 1;
+                }
+    assert(cut > 100);
+    return 0;
+}
+"""
+
+
 def _run(tmp_path, program):
     (tmp_path / "tiles.cpp").write_text(HEAD + program)
     subprocess.run(["g++", "-std=c++20", "-I" + os.path.join(ROOT, "paper_2103_13262_amd", "csrc"), str(tmp_path / "tiles.cpp"), "-o", str(tmp_path / "tiles")], check=True)
@@ -36,3 +71,8 @@ def _run(tmp_path, program):
 
 def test_both_sides_of_the_line(tmp_path):
     _run(tmp_path, LINES)
+
+
+def test_ranges(tmp_path):
+    layers = ", ".join("{%d, %d, %d, %d}" % (d, h, len(ROWS[r]), sum(ROWS[r])) for r, d, h in CUT)
+    _run(tmp_path, RANGES % layers)
