@@ -72,12 +72,13 @@ struct WsLayout {
 // phase never overwrites a partial sum of the first that its successor has not read yet.
 constexpr int kSkPhases = 2;
 // A word of sk_flags is zero between launches, unless a wait was given up: then a "partial sum ready" that came too late stays set until the
-// next moe_plan.  The small tiles count their slices' arrivals in the bits below it, so that one left behind does not count as an arrival.
+// next moe_plan.  The small tiles and the weight gradients' ranges count arrivals in the bits below it, so that one left behind does not count as an
+// arrival; whoever arrives last clears the word.
 constexpr int kPartialReady = 1 << 16;
 // The control block of a workspace, in int32 words from its start.  The plan step zeroes all of it and then sets
 // by_expert and skewed; the grouped products read and update the rest.
 enum Ctl {
-    kCtlFlags = 0,                                             // [kSkPhases][kMaxPersistentWgs] kPartialReady, or arrivals of slices
+    kCtlFlags = 0,                                             // [kSkPhases][kMaxPersistentWgs] kPartialReady, or arrivals of slices or ranges
     kCtlError = kCtlFlags + kSkPhases * kMaxPersistentWgs,     // status word: 1 if a bounded wait ran out
     kCtlByExpert = kCtlError + 1,                              // 1: the weight gradients give every XCD whole experts
     kCtlClock = kCtlError + 2,                                 // two int64: shader cycles, 100 MHz ticks (8-byte aligned)
@@ -233,8 +234,8 @@ struct GemmArgs {
     const int32_t* tileP;  // [4][E+1]
     const int32_t* order;  // [E]
     const int32_t* cls;    // [kClsTables][E+1] size-class tables of the plan step, or NULL (bf16 row products only)
-    void* sk_part;         // partial sums: of the persistent kernels one tile per phase and workgroup; of the small tiles one per tile and slice
-    int32_t* sk_flags;     // one word per phase and persistent workgroup (kPartialReady) or per small tile (arrivals), see kPartialReady
+    void* sk_part;         // partial sums: of the persistent kernels one tile per phase and workgroup; of the small tiles one per tile and slice, of the weight gradients one per tile and range
+    int32_t* sk_flags;     // one word per phase and persistent workgroup (kPartialReady), or per small tile or weight-gradient tile (arrivals), see kPartialReady
     int32_t* sk_error;
     const int32_t* by_expert;  // 1: the weight-gradient products give every XCD whole experts (decided by the plan step)
     long long* clock_probe;    // [2]: shader cycles and 100 MHz ticks of workgroup 0 of the last launch

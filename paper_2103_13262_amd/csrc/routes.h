@@ -105,19 +105,23 @@ template <class Product> constexpr bool pair_pays(const Product& rows, int workg
 // A weight gradient that follows a rows product in one launch: whether its tiles are so few that half as high ones still make a single round, over
 // reductions long enough to matter.  Both sides' times of the launch, 153 drawn products with at most 256 of the smaller tiles: 0.67 to 1.0 with 1024 rows
 // per expert and more and up to 224 of them, with a few up to 1.13 (0.84 on average; one expert, 9768 rows, K 1408, 384 columns: 178 -> 119 us; 10 experts,
-// 3079 rows, K 448, 960 columns: 118 -> 102); 0.93 to 1.06 with fewer rows; 0.89 to 1.18 with more tiles.
+// 3079 rows, K 448, 960 columns: 118 -> 102); 0.93 to 1.06 with fewer rows; 0.89 to 1.18 with more tiles.  Of 237 more inside the line (rows not cut, see
+// below) 22 are slower by over 2 %, by up to 22 % (1429 rows, one expert, K 5088, 800 columns: 50 -> 62; the whole step 0.99), 0.84 on average: mostly even loads
+// where the larger tiles just fit the workgroups that the rows product's last round leaves free and the smaller do not.  Skewed loads of such sizes take 0.66 to
+// 0.75, and the host does not know which it has.
 template <class Product> constexpr bool half_round(const Product& a)
 {
     return a.M >= 1024L * a.E && a.E * wide_columns(a) * ((a.K + 127) / 128) <= 224;
 }
 
 // Into how many ranges those tiles' rows are cut (at most eight, and one range for each of 256 workgroups), from an estimate of the launch in
-// microseconds: the rows product's tiles (1.7 a block of 64, and 12) leave `free` workgroups of their last round to start on the ranges at
-// once (0.37 a block of 32 rows, and 8), the others come when it ends; a tile's last workgroup adds its ranges' sums up (3 each, and 6).  Cut only
-// where that is 5 % better.  Against no cuts, 65 drawn launches (1100 to 12600 rows per expert, 18 to 128 tiles) cut once into as many ranges as a rule without the
-// rows product gave: the 26 where this estimate is better took 0.44 to 0.98 of the time (one expert, 9768 rows, K 384, 1408 columns: 122 -> 54 us; 5948 rows, 3
-// experts: 110 -> 75), the others 0.82 to 1.25.  With the
-// ranges that it gives now the 88 launches of that sweep take 0.92 of the time on average, the slowest of them 1.05.
+// microseconds, by the experts' mean rows: the rows product's tiles (1.7 a block of 64, and 12) leave `free` workgroups of their last round to start on
+// the ranges at once (0.37 a block of 32 rows, and 8), the others come when it ends; a tile's last workgroup adds its ranges' sums up (3 each, and 6).  Cut
+// only where that is 5 % better.  Against no cuts, 65 drawn launches (1100 to 12600 rows per expert, 18 to 128 tiles) cut once into as many ranges as a
+// rule without the rows product gave: the 26 where this estimate is better took 0.44 to 0.98 of the time (one expert, 9768 rows, K 384, 1408 columns: 122
+// -> 54 us; 5948 rows, 3 experts: 110 -> 75), the others 0.82 to 1.25.  With the ranges that it gives now the 88 launches of that sweep take 0.92 of the
+// time on average, the slowest of them 1.05.  Skewed loads, where the largest expert gets fewer ranges than its rows would want (51 layers of 2 to 12
+// experts, up to nearly all rows in one), against 256 x 256 tiles without ranges: 0.25 to 1.01.
 template <class Product> inline int half_round_slices(const Product& rows, const Product& cols)
 {
     const long tiles = cols.E * wide_columns(cols) * ((cols.K + 127) / 128), big = wide_tiles(rows), rounds = std::max(1L, (big + 255) / 256);

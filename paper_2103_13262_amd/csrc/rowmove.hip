@@ -266,9 +266,10 @@ __device__ __forceinline__ void gate_bwd_dx_body(long block, long blocks, const 
 
 // ---- dWg[:,e] = sum over rows r of segment e of dl[perm[r]] * Xs[r,:]  (fixed order) ----------
 // Every expert's segment is cut into pieces of 64 rows (the 64-row tile table of the plan step), so the
-// work per workgroup is the same however skewed the load is.  grid: piece_grid; each thread
-// owns one 16-byte column piece and walks the rows of its piece; a second kernel adds an expert's pieces
-// in ascending order.
+// work per workgroup is the same however skewed the load is.  Each thread owns one 16-byte column piece and walks
+// the rows of its piece; an expert's pieces are added in ascending order, by the last of their workgroups to arrive
+// (gate_bwd_whole, segment_sums) or by a second kernel (dwg_partial's gate_bwd_tail).
+
 // 16 bytes to where the XCDs' caches meet.  (The wait states keep the next instruction from overwriting the data registers while the
 // store still reads them: the compiler sees to that for its own stores but cannot see into an assembly statement.)
 __device__ __forceinline__ void store_shared(float* p, const float4 v)
@@ -278,7 +279,7 @@ __device__ __forceinline__ void store_shared(float* p, const float4 v)
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 2" :: "v"(p), "v"(w) : "memory");
 }
 
-// SHARED: another workgroup of the launch reads the sums (segment_arrive).  Returns the piece's segment, e = -1 past the last piece.
+// SHARED: another workgroup of the launch reads the sums (last_to_arrive, sum_pieces).  Returns the piece's segment, e = -1 past the last piece.
 template <typename T, bool SHARED>
 __device__ __forceinline__ Segment segment_partial(const void* __restrict__ Xs, const float* __restrict__ dl, const int32_t* __restrict__ perm,
                                                 const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
@@ -532,8 +533,7 @@ __global__ __launch_bounds__(256) void gate_bwd_tail(int fgx, const float* __res
 // Gate backward in one launch, for a call that has the transposed gate matrix already: workgroups of pieces first, each expert's sums added
 // up by the last of them; then `zeros` workgroups for the experts without rows; then dX.  None of these reads
 // what another writes.  Bound by latency in small batches, by HBM in large ones.  A step against one whose sums are added up in a second
-// launch beside dX: 256 tokens, d 64, 4 experts, fp32 42.6 -> 41.1 us; 16384 tokens, d 512, 256 experts, top-1 507.6 -> 505.1; 8192, d 1024, 64
-// experts 1426 -> 1423.
+// launch beside dX: 256 tokens, d 64, 4 experts, fp32 42.6 -> 41.1 us; 8192 tokens and more: within what two runs differ by.
 template <typename T, typename G, int K>
 __global__ __launch_bounds__(512) void gate_bwd_whole(const void* __restrict__ Xs, const float* __restrict__ dl, const int32_t* __restrict__ perm,
                                                       const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
